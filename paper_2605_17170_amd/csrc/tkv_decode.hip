@@ -60,10 +60,6 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
-#ifndef TKV_WAVES_PER_EU
-#define TKV_WAVES_PER_EU 3
-#endif
-
 constexpr float kTau = 4.0f;   // rescale when a logit exceeds the reference maximum by this much (log2 units)
 // Softmax weights are carried in fp16 as W = P * 2^kPExp (P <= 2^kTau), so that small weights stay clear
 // of the fp16 subnormal grid; numerator and denominator share the factor.
@@ -196,9 +192,8 @@ template <> struct LdsExtra<true> {
     alignas(16) uint4 qp[kGroups][64];                   // q * 2^E in the slot order of qo, without the slot factors
 };
 template <bool KC> struct alignas(16) Lds : LdsExtra<KC> {
-    // Per-channel INT2 keys reuse ks and kz while INT2 pages run: ks holds the K scale plane (512 B) and the
-    // K zero plane (512 B) of the page as stored, kz a plane of zeros (the INT4 pages, which come later in
-    // an item, overwrite all three with their own staging).
+    // Per-channel INT2 keys reuse ks while INT2 pages run: the K scale plane (512 B) and the K zero plane (512 B) of
+    // the page as stored (the INT4 pages, which come later in an item, overwrite them with their own staging).
     alignas(16) float ks[kPageTokens * kGroups];         // K scale * F, fp32 [token][group]
     // Operands of the PV phase, 16-byte chunks of eight fp16 (the tokens of one k-slot octet), one array so that
     // a lane-dependent index can choose between staged data and the constants:
@@ -206,9 +201,6 @@ template <bool KC> struct alignas(16) Lds : LdsExtra<KC> {
     //   kPvS + (blk*4 + quad)*4 + g   V scale * 2^(kVExp - pos)
     //   kPvZero   zeros;   kPvOne   ones
     alignas(16) uint4 pv[kPvChunks];
-    // K zero, four fp16 per token (per-channel INT2 keys, which also use it as a plane of zeros; otherwise the K
-    // zeros travel between lanes without a copy in LDS)
-    alignas(16) uint2 kz[KC ? kPageTokens : 2];
     // B operands of the QK^T MFMAs: per group and lane (per-channel INT2 keys), or 8 x (16 entries + zeros) (build_q_operand)
     alignas(16) uint4 qo[KC ? kGroups : 2][KC ? 64 : 4 * kQyStride];
     alignas(16) float alpha[16];
@@ -217,7 +209,6 @@ template <bool KC> struct alignas(16) Lds : LdsExtra<KC> {
     __device__ __forceinline__ float (*zl())[8] { return reinterpret_cast<float(*)[8]>(qo); }
     __device__ __forceinline__ uint4 *kc_scale() { return reinterpret_cast<uint4 *>(ks); }
     __device__ __forceinline__ uint4 *kc_zero() { return reinterpret_cast<uint4 *>(ks) + 32; }
-    __device__ __forceinline__ uint4 *kc_nil() { return reinterpret_cast<uint4 *>(kz); }
 };
 
 // q * 2^E is staged in LDS as fp16 [head][128 channels].  The operand build reads the same channels of all eight
@@ -267,27 +258,26 @@ __device__ __forceinline__ void build_q_operand(const void *qf /* the staged q (
             lds.qp[g][lane] = make_uint4(rp[0], rp[1], rp[2], rp[3]);
         }
     } else {
+        // 8 x 16 entries, two per lane: lane (sub, head, g) makes those of the two halves of group g
         uint4 *qy = reinterpret_cast<uint4 *>(lds.qo);
-        const int sub = q4 & 1, ent = sub * 8 + (lane & 7);   // lanes that differ in lane & 8 or q4 & 2 write the same entry
+        const int sub = (lane >> 3) & 1, g = q4;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int hg = 0; hg < 2; ++hg) {
+            uint32_t r[4];
+            if (BITS == 4) {
+                // registers: (n0,n4) (n1,n5)/16 (n2,n6) (n3,n7)/16 of the 8-channel word 2*hg + sub of the group
+                const uint4 c = *reinterpret_cast<const uint4 *>(qb + qf_chunk<KC>(h, g * 4 + 2 * hg + sub));   // channels (0,1) (2,3) (4,5) (6,7)
+                r[0] = __builtin_amdgcn_perm(c.z, c.x, 0x05040100u);
+                r[1] = pk_mul(__builtin_amdgcn_perm(c.z, c.x, 0x07060302u), 0x2c002c00u);
+                r[2] = __builtin_amdgcn_perm(c.w, c.y, 0x05040100u);
+                r[3] = pk_mul(__builtin_amdgcn_perm(c.w, c.y, 0x07060302u), 0x2c002c00u);
+            } else {
+                int2_pairs(g, hg, sub, r);
 #pragma unroll
-            for (int hg = 0; hg < 2; ++hg) {
-                uint32_t r[4];
-                if (BITS == 4) {
-                    // registers: (n0,n4) (n1,n5)/16 (n2,n6) (n3,n7)/16 of the 8-channel word 2*hg + sub of the group
-                    const uint4 c = *reinterpret_cast<const uint4 *>(qb + qf_chunk<KC>(h, g * 4 + 2 * hg + sub));   // channels (0,1) (2,3) (4,5) (6,7)
-                    r[0] = __builtin_amdgcn_perm(c.z, c.x, 0x05040100u);
-                    r[1] = pk_mul(__builtin_amdgcn_perm(c.z, c.x, 0x07060302u), 0x2c002c00u);
-                    r[2] = __builtin_amdgcn_perm(c.w, c.y, 0x05040100u);
-                    r[3] = pk_mul(__builtin_amdgcn_perm(c.w, c.y, 0x07060302u), 0x2c002c00u);
-                } else {
-                    int2_pairs(g, hg, sub, r);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) r[k] = pk_mul(r[k], kSlot2[k]);
-                }
-                qy[(g * 2 + hg) * kQyStride + ent] = make_uint4(r[0], r[1], r[2], r[3]);
+                for (int k = 0; k < 4; ++k) r[k] = pk_mul(r[k], kSlot2[k]);
             }
+            qy[(g * 2 + hg) * kQyStride + (lane & 15)] = make_uint4(r[0], r[1], r[2], r[3]);
+        }
         if (lane < 16) qy[(lane & 7) * kQyStride + (lane < 8 ? kQyZero0 : kQyZero1)] = make_uint4(0u, 0u, 0u, 0u);
     }
 }
@@ -299,55 +289,67 @@ template <int BITS> struct PageRegs {
     uint4 vw[BITS];       // V codes: 16-byte chunks, one word per 16-channel tile; [blk*2 + chunk] (INT4), [chunk] (INT2)
     uint2 ksc, vsc, vzc;  // this lane's four entries of the K scale / V scale / V zero planes
     uint2 kzc;            // K zero of token `lane`, four groups
-    uint32_t bm;          // bit_map entry of the page
 };
 
-// The loads of one record come in two parts, issued as soon as the registers they land in are free: the
-// metadata planes and the K codes after the QK^T phase of the previous page, the V codes after its PV phase.
-template <int BITS>
-__device__ __forceinline__ void load_page_meta(PageRegs<BITS> &pr, const uint8_t *__restrict__ rec,
-                                               const uint8_t *__restrict__ bit_map, int page, int lane, int opaque_zero)
+// A record as a buffer: base address and size in scalar registers, so that a load needs one 32-bit lane offset.  Size 0
+// makes every load of it return zeros without touching memory: that is how a wavefront runs past its last page
+// without a branch around the loads (a branch would make the compiler wait for all of them in every iteration).  A
+// wavefront that asked for its last record again instead, as it used to, read 9 % more than the cache holds at eleven
+// pages per wavefront (8 sequences of 32768 tokens: step 51.3 -> 49.1 us) and twice as much at one.
+typedef __amdgpu_buffer_rsrc_t Record;
+template <int BITS> __device__ __forceinline__ Record record_at(const uint8_t *__restrict__ rec, bool wanted)
 {
-    using R = Rec<BITS>;
-    pr.ksc = reinterpret_cast<const uint2 *>(rec + R::kKScale)[lane];
-    pr.vsc = reinterpret_cast<const uint2 *>(rec + R::kVScale)[lane];
-    pr.vzc = reinterpret_cast<const uint2 *>(rec + R::kVZero)[lane];
-    // `opaque_zero` is 0 in a register the compiler cannot see through: the load stays a per-lane load whose
-    // result is waited for where it is used, not a scalar value that is fetched back right behind the request
-    pr.bm = bit_map[page + opaque_zero];
-    pr.kzc = reinterpret_cast<const uint2 *>(rec + R::kKZero)[lane];
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(rec), 0, wanted ? Rec<BITS>::kBytes : 0, 0x00027000);
 }
-// Index (16-byte chunks) of part i of this lane's K codes / V codes in the record's code plane.
-template <int BITS, bool KC> __device__ __forceinline__ int kcode_chunk(int i, int lane)
+__device__ __forceinline__ uint2 buffer_load8(Record r, int lane_offset, int plane)
+{
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, lane_offset, plane, 0);
+    return make_uint2(v.x, v.y);
+}
+__device__ __forceinline__ uint4 buffer_load16_once(Record r, int lane_offset, int plane)   // non-temporal, as load_once
+{
+    const uint4v v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_offset, plane, 2 /* nt */);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+// Index (16-byte chunks) of part 0 of this lane's K codes in the record's code plane, and how far on part i is.
+template <int BITS, bool KC> __device__ __forceinline__ int kcode_chunk(int lane)
 {
     const int r16 = lane & 15, q4 = lane >> 4;
-    if constexpr (KC && BITS == 2) return i * 32 + (q4 >> 1) * 16 + r16;   // tile i
+    if constexpr (KC && BITS == 2) return (q4 >> 1) * 16 + r16;
     // k-slots 0..15 of an MFMA are the first token set (tile 2*blk), 16..31 the second (tile 2*blk + 1); a lane
     // holds eight channels: octet q4 & 1 of half group hg; i = blk*2 + hg
-    const int tile = 2 * (i >> 1) + (q4 >> 1), hg = i & 1;
-    return BITS == 4 ? tile * 64 + (2 * hg + (q4 & 1)) * 16 + r16 : (tile * 2 + hg) * 16 + r16;
+    return BITS == 4 ? (q4 >> 1) * 64 + (q4 & 1) * 16 + r16 : (q4 >> 1) * 32 + r16;
 }
-template <int BITS> __device__ __forceinline__ int vcode_chunk(int i, int lane)
+template <int BITS, bool KC> constexpr int kcode_part(int i)
 {
-    // Columns 0..7 of the PV MFMAs are channels of groups 0 and 1, columns 8..15 of groups 2 and 3: lane
-    // (c, quad) reads the chunks of channel half c >> 3, at its own column (even i) and at column c ^ 8 (odd i);
-    // INT4: i = blk*2 + chunk, INT2: i = chunk (a word holds both blocks)
-    const int base = ((lane & 8) << 3) + (lane & 48) + ((lane & 15) ^ ((i & 1) << 3));
-    return BITS == 4 ? (i >> 1) * 128 + base : base;
+    if (KC && BITS == 2) return i * 32;   // tile i
+    return BITS == 4 ? (i >> 1) * 128 + (i & 1) * 32 : (i >> 1) * 64 + (i & 1) * 16;
 }
-template <int BITS, bool KC>
-__device__ __forceinline__ void load_page_k(PageRegs<BITS> &pr, const uint8_t *__restrict__ rec, int lane)
+// Columns 0..7 of the PV MFMAs are channels of groups 0 and 1, columns 8..15 of groups 2 and 3: lane
+// (c, quad) reads the chunks of channel half c >> 3, at its own column (even i) and at column c ^ 8 (odd i);
+// INT4: i = blk*2 + chunk, INT2: i = chunk (a word holds both blocks)
+__device__ __forceinline__ int vcode_chunk(int lane) { return ((lane & 8) << 3) + (lane & 48) + (lane & 15); }
+
+// The loads of one record come in two parts, so that each can be issued as soon as the registers it lands in are
+// free: the metadata planes and the K codes, and the V codes.
+template <int BITS, bool KC> __device__ __forceinline__ void load_page_k(PageRegs<BITS> &pr, Record rec, int lane)
 {
-    const uint4 *kc = reinterpret_cast<const uint4 *>(rec + Rec<BITS>::kKCodes);
+    using R = Rec<BITS>;
+    pr.ksc = buffer_load8(rec, lane * 8, R::kKScale);
+    pr.vsc = buffer_load8(rec, lane * 8, R::kVScale);
+    pr.vzc = buffer_load8(rec, lane * 8, R::kVZero);
+    pr.kzc = buffer_load8(rec, lane * 8, R::kKZero);
+    const int at = kcode_chunk<BITS, KC>(lane) * 16;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) pr.kw[i] = load_once(kc + kcode_chunk<BITS, KC>(i, lane));
+    for (int i = 0; i < 4; ++i) pr.kw[i] = buffer_load16_once(rec, at, R::kKCodes + 16 * kcode_part<BITS, KC>(i));
 }
-template <int BITS>
-__device__ __forceinline__ void load_page_v(PageRegs<BITS> &pr, const uint8_t *__restrict__ rec, int lane)
+template <int BITS> __device__ __forceinline__ void load_page_v(PageRegs<BITS> &pr, Record rec, int lane)
 {
-    const uint4 *vc = reinterpret_cast<const uint4 *>(rec + Rec<BITS>::kVCodes);
+    using R = Rec<BITS>;
+    const int at = vcode_chunk(lane) * 16;
 #pragma unroll
-    for (int i = 0; i < BITS; ++i) pr.vw[i] = load_once(vc + vcode_chunk<BITS>(i, lane));
+    for (int i = 0; i < BITS; ++i) pr.vw[i] = buffer_load16_once(rec, at ^ ((i & 1) << 7), R::kVCodes + (BITS == 4 ? (i >> 1) * 2048 : 0));
 }
 // Lane constants of the page loop.
 struct LaneConst {
@@ -359,7 +361,6 @@ struct LaneConst {
     int vs_st;            // 8-byte slot of Lds::pv (behind kPvS) where this lane stages its four V scales
     uint32_t vrot[2];     // INT4 V unpack: rotate amounts that bring registers 0, 1 / 2, 3 of the operand into place
     uint32_t vmask[4];    // INT2 V unpack: field masks of operand registers 0..3
-    int opaque_zero;      // 0, opaque to the compiler
     int tok0;             // two token sets: first token of this lane's four within a 32-token block
     int qy_ent;           // ... entry of this lane in a q operand of the QK^T MFMAs (or one of the two zero entries)
     float zmul;           // per-channel INT2 keys: 2^-24 in head columns 0..7, 0 in columns 8..15
@@ -442,32 +443,36 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
         // score = sum_c (q_c s_c) code + sum_c q_c z_c with s, z of the token's block.  q s is formed per block
         // in two fp16 pieces, exactly (q has 8 significant bits, s 11): head columns 0..7 take
         // fp16(q s), columns 8..15 the remainder q s - fp16(q s); the columns of a head are added after the
-        // MFMAs.  Lanes of the hi columns read their "rounded product to subtract" from a plane of zeros.
-        const uint4 *sxp = r16 >= 8 ? lds.kc_scale() : lds.kc_nil();
+        // MFMAs.  What is subtracted is formed from a q that is zero in the hi columns.
+        const uint32_t lo_cols = r16 >= 8 ? 0xffffffffu : 0u;
         const uint32_t rot = (q4 & 1) ? 5u : 29u;   // this lane's 16 codes of a word are its upper / lower half
-        // operands of both blocks first: the zero-term chains run on the matrix core while the VALU forms q s
-        floatx4 z[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        uint32_t b[2][4][4];
+        // Zero term, sum_c q_c z_c of the two blocks: rows 0..7 of the A operand are block 0, rows 8..15 block 1.
+        // Group by group, the LDS reads of the next group under way while a group is computed; four accumulation chains
+        // (one per 16-token tile) and that of the zero term.
+        struct Operands { uint4 qp, qo, zc, sc[2]; } op;
+        auto fetch = [&](int g) {
+            op.qo = lds.qo[g][lane];
+            op.sc[0] = lds.kc_scale()[g * 4 + q4];
+            op.sc[1] = lds.kc_scale()[(4 + g) * 4 + q4];
+            op.qp = lds.qp[g][lane];
+            op.zc = lds.kc_zero()[((r16 >> 3) * 4 + g) * 4 + q4];
+        };
+        floatx4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) S[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+        fetch(0);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const uint4 qp = lds.qp[g][lane], qo = lds.qo[g][lane];
+            half8 b[2];
 #pragma unroll
             for (int blk = 0; blk < 2; ++blk) {
-                const int mi = (blk * 4 + g) * 4 + q4;
-                const uint4 zc = lds.kc_zero()[mi];
-                z[blk] = mfma(as_half8(zc.x, zc.y, zc.z, zc.w), as_half8(qp.x, qp.y, qp.z, qp.w), z[blk]);   // every row: sum_c q_c z_c
-                const uint4 sc = lds.kc_scale()[mi], sx = sxp[mi];
-                b[blk][g][0] = pk_rem(qo.x, sc.x, pk_mul(qo.x, sx.x));
-                b[blk][g][1] = pk_rem(qo.y, sc.y, pk_mul(qo.y, sx.y));
-                b[blk][g][2] = pk_rem(qo.z, sc.z, pk_mul(qo.z, sx.z));
-                b[blk][g][3] = pk_rem(qo.w, sc.w, pk_mul(qo.w, sx.w));
+                const uint4 sc = op.sc[blk], qo = op.qo;
+                b[blk] = as_half8(pk_rem(qo.x, sc.x, pk_mul(qo.x & lo_cols, sc.x)), pk_rem(qo.y, sc.y, pk_mul(qo.y & lo_cols, sc.y)),
+                                  pk_rem(qo.z, sc.z, pk_mul(qo.z & lo_cols, sc.z)), pk_rem(qo.w, sc.w, pk_mul(qo.w & lo_cols, sc.w)));
             }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) S[e] = z[e >> 1] * lc.zmul;   // to the unit of the code products, hi columns only
-        // four independent accumulation chains (one per 16-token tile)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
+            z = mfma(as_half8(op.zc.x, op.zc.y, op.zc.z, op.zc.w), as_half8(op.qp.x, op.qp.y, op.qp.z, op.qp.w), z);
+            if (g < 3) fetch(g + 1);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t wg = g == 0 ? pr.kw[e].x : g == 1 ? pr.kw[e].y : g == 2 ? pr.kw[e].z : pr.kw[e].w;
@@ -475,8 +480,17 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
                 // the matrix core drops product bits that fall below its alignment window
                 const uint32_t ws = __builtin_amdgcn_alignbit(wg, wg, rot);   // w >> 5 or w << 3, stray bits fall outside the masks
                 const half8 a = as_half8(ws & 0x00180018u, ws & 0x00600060u, ws & 0x01800180u, ws & 0x06000600u);
-                S[e] = mfma(a, as_half8(b[e >> 1][g][0], b[e >> 1][g][1], b[e >> 1][g][2], b[e >> 1][g][3]), S[e]);
+                S[e] = mfma(a, b[e >> 1], S[e]);
             }
+        }
+        // every row of a block's half holds the same sum; lanes 0..31 hold that of block 0, lanes 32..63 that of block 1
+        const float zmine = z[0] * lc.zmul;   // to the unit of the code products, hi columns only
+        const float zother = __shfl_xor(zmine, 32);
+        const float zb[2] = {lane < 32 ? zmine : zother, lane < 32 ? zother : zmine};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) S[e][i] += zb[e >> 1];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
 #pragma unroll
@@ -656,61 +670,79 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
     after_pv();
 }
 
-// What stays the same for every page of a work item, and the pages of one width in it (positions in the
-// sequence's page list).
+// What stays the same for every page of a work item.
 struct ItemCtx {
     const uint8_t *__restrict__ pool;
     const uint8_t *__restrict__ bit_map;
     const int32_t *__restrict__ pages;   // the sequence's page list
-    int kvh, n_kv_heads, n_pages_int2, n_pages_total, lane, opaque_zero;
+    int pb, pe;                          // the item's range of it
+    int np2, np4;                        // pages of the sequence: the INT2 pages come first
+    int last2, last4;                    // valid tokens of the last page of either width
+    int kvh, n_kv_heads, n_pages_int2, n_pages_total, lane;
     int32_t *status;
 };
-struct WidthRange {
-    int pb, pe;                  // positions in the page list
-    int last_index, last_valid;  // position of the width's last page in the sequence and its number of valid tokens
-    int page_lo, page_hi;        // the pool's page ids
+// The pages of an item, 64 at a time in registers: lane l holds list position base + l.  The page id, the check against
+// its pool, the bit_map entry, the address arithmetic and the token count of a page cost one lane each, once, instead
+// of two loads and some thirty scalar instructions on the way from page to page.
+struct PageBatch {
+    int base;
+    uint32_t at;   // where this wavefront's record of the page starts in the pool, in units of kRecordUnit
+    int nv;        // number of valid tokens; 0: the page is run with every token masked
+    uint32_t bm;
 };
-// Page id of list position pi (already loaded) and its number of valid tokens.  A page id outside its pool cannot
-// be addressed: it is flagged, a valid page is read instead and skipped.
-__device__ __forceinline__ int validate_page(const ItemCtx &cx, const WidthRange &wr, int pi, int &page)
+constexpr int kRecordUnitLog2 = 11;   // record sizes and arena sizes are multiples of it
+static_assert(Rec<2>::kBytes % (1 << kRecordUnitLog2) == 0 && Rec<4>::kBytes % (1 << kRecordUnitLog2) == 0, "record unit");
+// Requests the ids of positions base .. base + 63.
+__device__ __forceinline__ int batch_ids(const ItemCtx &cx, PageBatch &pb, int base)
 {
-    const bool ok = page >= wr.page_lo && page < wr.page_hi;
-    if (!ok) {
-        if (cx.status && cx.lane == 0)
-            atomicOr(cx.status, page < 0 || page >= cx.n_pages_total ? TKV_STATUS_PAGE_RANGE : TKV_STATUS_BITMAP_MISMATCH);
-        page = wr.page_lo;
-    }
-    return ok ? (pi == wr.last_index ? wr.last_valid : kPageTokens) : 0;
+    pb.base = base;
+    return cx.pages[base + cx.lane < cx.pe ? base + cx.lane : cx.pe - 1];
 }
-// State handed from start_pages to run_pages: the first record's registers, the next page's id.
-template <int BITS> struct Started {
-    PageRegs<BITS> pr;
-    int nv, page_next, nv_next;
-};
-// Requests the first record of a width.
-template <int BITS, bool KC>
-__device__ __forceinline__ void start_pages(const ItemCtx &cx, const WidthRange &wr, Started<BITS> &s0)
+// Checks the ids.  A page id outside its pool cannot be addressed: it is flagged, a valid page is read instead and
+// none of its tokens count.  Requests the bit_map entries.
+__device__ __forceinline__ void batch_check(const ItemCtx &cx, PageBatch &pb, int page)
 {
-    int page = __builtin_amdgcn_readfirstlane(cx.pages[wr.pb]);
-    s0.nv = validate_page(cx, wr, wr.pb, page);
-    const int pi1 = wr.pb + 1 < wr.pe ? wr.pb + 1 : wr.pb;
-    s0.page_next = __builtin_amdgcn_readfirstlane(cx.pages[pi1]);
-    s0.nv_next = validate_page(cx, wr, pi1, s0.page_next);
-    const uint8_t *rec = cx.pool + record_offset(page, cx.kvh, cx.n_kv_heads, cx.n_pages_int2);
-    load_page_meta<BITS>(s0.pr, rec, cx.bit_map, page, cx.lane, cx.opaque_zero);
-    load_page_k<BITS, KC>(s0.pr, rec, cx.lane);
-    load_page_v<BITS>(s0.pr, rec, cx.lane);
+    const int pi = pb.base + cx.lane;
+    const bool is2 = pi < cx.np2;
+    const int lo = is2 ? 0 : cx.n_pages_int2, hi = is2 ? cx.n_pages_int2 : cx.n_pages_total;
+    const bool ok = page >= lo && page < hi;
+    if (!ok && pi < cx.pe && cx.status)
+        atomicOr(cx.status, page < 0 || page >= cx.n_pages_total ? TKV_STATUS_PAGE_RANGE : TKV_STATUS_BITMAP_MISMATCH);
+    pb.nv = ok ? (pi == cx.np2 - 1 ? cx.last2 : pi == cx.np2 + cx.np4 - 1 ? cx.last4 : kPageTokens) : 0;
+    // (lanes beyond the item repeat its last page, whose width need not be theirs; they are never used)
+    const int at = ok ? page : (lo < cx.n_pages_total ? lo : 0);
+    pb.at = (uint32_t)(record_offset(at, cx.kvh, cx.n_kv_heads, cx.n_pages_int2) >> kRecordUnitLog2);
+    pb.bm = cx.bit_map[at];
+}
+// A page that was never written, or written at the other width, counts no tokens.
+__device__ __forceinline__ void batch_finish(const ItemCtx &cx, PageBatch &pb)
+{
+    const int pi = pb.base + cx.lane;
+    const bool written = pb.bm == (pi < cx.np2 ? 2u : 4u);
+    if (!written && pb.nv > 0 && pi < cx.pe && cx.status) atomicOr(cx.status, TKV_STATUS_BITMAP_MISMATCH);
+    pb.nv = written ? pb.nv : 0;
+}
+__device__ __forceinline__ void batch_seek(const ItemCtx &cx, PageBatch &pb, int pi)
+{
+    if (__builtin_expect(pi - pb.base >= 64, 0)) {
+        const int page = batch_ids(cx, pb, pi);
+        batch_check(cx, pb, page);
+        batch_finish(cx, pb);
+    }
+}
+__device__ __forceinline__ int batch_valid(const PageBatch &pb, int pi) { return __builtin_amdgcn_readlane(pb.nv, pi - pb.base); }
+template <int BITS> __device__ __forceinline__ Record batch_record(const ItemCtx &cx, const PageBatch &pb, int pi, bool wanted)
+{
+    const uint64_t at = (uint32_t)__builtin_amdgcn_readlane((int)pb.at, pi - pb.base);
+    return record_at<BITS>(cx.pool + (at << kRecordUnitLog2), wanted);
 }
 
+// The pages [pi, pe) of one width.  `pr` holds (or has requested) the record of page pi.
 template <int BITS, bool KC>
-__device__ __forceinline__ void run_pages(const ItemCtx &cx, const WidthRange &wr, Started<BITS> &s0, int item_end, int item_pages,
-                                          half8 qz, LaneConst lc, WaveState &st, Lds<KC> &lds)
+__device__ __forceinline__ void run_pages(const ItemCtx &cx, PageBatch &batch, int pi, int pe, PageRegs<BITS> &pr, half8 qz, LaneConst lc,
+                                          WaveState &st, Lds<KC> &lds)
 {
-    const uint8_t *__restrict__ pool = cx.pool;
-    const uint8_t *__restrict__ bit_map = cx.bit_map;
-    const int32_t *__restrict__ pages = cx.pages;
-    const int pb = wr.pb, pe = wr.pe, kvh = cx.kvh, n_kv_heads = cx.n_kv_heads, n_pages_int2 = cx.n_pages_int2, lane = cx.lane;
-    int32_t *status = cx.status;
+    const int lane = cx.lane;
     // A V code enters the MFMA as code * 2^(pos - 24), pos = lowest bit of its field after the unpack shift; the
     // staged scale of the slot carries 2^(kVExp - pos).  This lane stages plane entries 4*lane .. 4*lane+3 =
     // k-slots 4*(lane&1) + 0..3, i.e. operand registers 2*(lane&1) (first pair) and 2*(lane&1) + 1 (second pair).
@@ -733,57 +765,52 @@ __device__ __forceinline__ void run_pages(const ItemCtx &cx, const WidthRange &w
     }
     // One register set: every part of the next record is requested as soon as the registers it lands in
     // are dead, so about one page per wavefront is in flight while the current one is computed.
-    PageRegs<BITS> &pr = s0.pr;
-    int nv = s0.nv, page_next = s0.page_next, nv_next = s0.nv_next;
-    int quartile = -1;
-    for (int pi = pb; pi < pe; ++pi) {
+    int nv = batch_valid(batch, pi);
+    int prio_end = 0;   // list position at which the priority changes next
+    const int item_pages = cx.pe - cx.pb;
+    for (; pi < pe; ++pi) {
         // Wavefronts that share a SIMD are served oldest first; left alone, the oldest finishes long before
         // the others and the SIMD ends its work with one wavefront.  The priority follows the share of the
-        // item still to do, so the wavefronts of a SIMD advance together.
-        const int q = (4 * (item_end - pi) - 1) / item_pages;   // 3 .. 0
-        if (__builtin_expect(q != quartile, 0)) {
-            quartile = q;
-            if (q >= 3) __builtin_amdgcn_s_setprio(3);
-            else if (q == 2) __builtin_amdgcn_s_setprio(2);
-            else if (q == 1) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
+        // item still to do (three quarters and more, a half, a quarter, less), so the wavefronts of a SIMD advance together.
+        if (__builtin_expect(pi >= prio_end, 0)) {
+            const int left4 = 4 * (cx.pe - pi) - 1;
+            int q;
+            if (left4 >= 3 * item_pages) { q = 3; __builtin_amdgcn_s_setprio(3); }
+            else if (left4 >= 2 * item_pages) { q = 2; __builtin_amdgcn_s_setprio(2); }
+            else if (left4 >= item_pages) { q = 1; __builtin_amdgcn_s_setprio(1); }
+            else { q = 0; __builtin_amdgcn_s_setprio(0); }
+            // the first position with 4 * (pe - position) - 1 < q * item_pages
+            prio_end = cx.pe - ((q * item_pages) >> 2);
         }
-        // The id of the page after next is requested now, as a per-lane load (`opaque_zero`), and turned into a
-        // scalar at the end of this page: its latency never stands between two pages.  The last page requests its
-        // own record again: no branch around the loads.
-        const int pi_next2 = pi + 2 < pe ? pi + 2 : pe - 1;
-        const int pgv = pages[pi_next2 + lc.opaque_zero];
-        const uint8_t *rec_next = pool + record_offset(page_next, kvh, n_kv_heads, n_pages_int2);
-        const uint32_t bm = pr.bm;
+        // The last page asks for nothing (an empty record).
+        const bool wanted = pi + 1 < pe;
+        const int next = wanted ? pi + 1 : pi;
+        batch_seek(cx, batch, next);
+        const Record rec = batch_record<BITS>(cx, batch, next, wanted);
+        const int nv_next = batch_valid(batch, next);
         auto after_qk = [&]() {
             __builtin_amdgcn_sched_barrier(0);   // keep the reloads below the last use of the registers they overwrite
-            load_page_meta<BITS>(pr, rec_next, bit_map, page_next, lane, lc.opaque_zero);
-            load_page_k<BITS, KC>(pr, rec_next, lane);
+            load_page_k<BITS, KC>(pr, rec, lane);
         };
         auto after_pv = [&]() {
             __builtin_amdgcn_sched_barrier(0);
-            load_page_v<BITS>(pr, rec_next, lane);
+            load_page_v<BITS>(pr, rec, lane);
         };
-        // the bit_map entry arrives with the page: a mismatch skips the whole page
-        if (__any(bm != BITS) && nv > 0) {
-            if (status && lane == 0) atomicOr(status, TKV_STATUS_BITMAP_MISMATCH);
-            nv = 0;
-        }
         // a page with no valid token still runs (every token masked by count): no second path through the loop
         compute_page<BITS, KC>(pr, nv, lane, qz, lc, st, lds, after_qk, after_pv);
         nv = nv_next;
-        page_next = __builtin_amdgcn_readfirstlane(pgv);
-        nv_next = validate_page(cx, wr, pi_next2, page_next);
     }
 }
 
 // KC: the INT2 keys of the pool are quantised per channel over 32-token blocks (Sec. 3.2.1).
+// The grid is (kv heads, items): the workgroups of an item are launched one behind the other, without a division to
+// find the item.
 template <bool KC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PER_EU, TKV_WAVES_PER_EU))) void tkv_decode_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void tkv_decode_kernel(
     const uint8_t *__restrict__ pool, const uint8_t *__restrict__ bit_map, const uint16_t *__restrict__ q,
     const int32_t *__restrict__ page_indptr, const int32_t *__restrict__ page_ids,
     const int32_t *__restrict__ n_tok_int2, const int32_t *__restrict__ n_tok_int4,
-    const int32_t *__restrict__ items, int batch, int n_kv_heads, int n_q_heads, int n_pages_int2, int n_pages_int4,
+    const int32_t *__restrict__ items, int n_items, int batch, int n_kv_heads, int log2_r, int n_pages_int2, int n_pages_int4,
     float kappa, float *__restrict__ acc_ws, float *__restrict__ ml_ws, int32_t *status
     )
 {
@@ -795,22 +822,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PE
     if constexpr (KC) qf = lds.ks;
     else qf = lds.qf;
     const int lane = threadIdx.x, r16 = lane & 15, q4 = lane >> 4;
-    const int item = blockIdx.x / n_kv_heads, kvh = blockIdx.x % n_kv_heads;
-    const int R = n_q_heads / n_kv_heads;
+    const int item = blockIdx.y + blockIdx.z * gridDim.y, kvh = blockIdx.x;
+    if (item >= n_items) return;
+    const int R = 1 << log2_r, n_q_heads = n_kv_heads << log2_r;
     const int seq = items[4 * item];
     // The partial of this item goes to slot items[4*item + 3] of the workspace: items are listed in launch order,
     // the slots of a sequence are contiguous (the merge reads them by sequence).
     const int slot = items[4 * item + 3];
-    const bool slot_ok = slot >= 0 && slot < (int)(gridDim.x / n_kv_heads);
-    if (seq < 0 || seq >= batch || !slot_ok) {
-        // malformed item: an empty partial (m = -inf, l = 0), which the merge ignores, and a status bit; with a slot
-        // outside the workspace nothing can be written, and whoever owns the slot it should have named reads what
-        // the workspace held before
-        for (int h = 0; h < R && slot_ok; ++h) {
+    const bool slot_ok = slot >= 0 && slot < n_items;
+    auto write_empty = [&]() {
+        for (int h = 0; h < R; ++h) {
             const size_t ph = (size_t)slot * n_q_heads + kvh * R + h;
             reinterpret_cast<float2 *>(acc_ws + ph * kHeadDim)[lane] = make_float2(0.0f, 0.0f);
             if (lane == 0) reinterpret_cast<float2 *>(ml_ws)[ph] = make_float2(-INFINITY, 0.0f);
         }
+    };
+    if (seq < 0 || seq >= batch || !slot_ok) {
+        // malformed item: an empty partial (m = -inf, l = 0), which the merge ignores, and a status bit; with a slot
+        // outside the workspace nothing can be written, and whoever owns the slot it should have named reads what
+        // the workspace held before
+        if (slot_ok) write_empty();
         if (status && lane == 0) atomicOr(status, TKV_STATUS_BAD_ITEM);
         return;
     }
@@ -824,23 +855,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PE
     const int n_pages_total = n_pages_int2 + n_pages_int4;
     // INT2 pages of the range, then INT4 pages: each page runs one dequantisation path
     const int e2 = pe < np2 ? pe : np2, b4 = pb > np2 ? pb : np2;
-    const bool has2 = pb < e2, has4 = b4 < pe;
-    int opaque_zero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(opaque_zero));
-    const ItemCtx cx = {pool, bit_map, pages, kvh, n_kv_heads, n_pages_int2, n_pages_total, lane, opaque_zero, status};
-    const WidthRange wr2 = {pb, e2, np2 - 1, n2 - (np2 - 1) * kPageTokens, 0, n_pages_int2};
-    const WidthRange wr4 = {b4, pe, np2 + np4 - 1, n4 - (np4 - 1) * kPageTokens, n_pages_int2, n_pages_total};
-    Started<2> s2;
-    Started<4> s4;
+    bool has2 = pb < e2, has4 = b4 < pe;
+    // tokens of a width whose pool has no pages at all: nothing to read
+    if ((has2 && n_pages_int2 == 0) || (has4 && n_pages_int4 == 0)) {
+        if (status && lane == 0) atomicOr(status, TKV_STATUS_PAGE_RANGE);
+        has2 = has2 && n_pages_int2 > 0;
+        has4 = has4 && n_pages_int4 > 0;
+    }
+    if (!(has2 || has4)) {   // an item without pages
+        write_empty();
+        return;
+    }
+    const ItemCtx cx = {pool, bit_map, pages, pb, pe, np2, np4, n2 - (np2 - 1) * kPageTokens, n4 - (np4 - 1) * kPageTokens,
+                        kvh, n_kv_heads, n_pages_int2, n_pages_total, lane, status};
+    PageBatch list = {pb, 0, 0, 0};
+    PageRegs<2> s2;
+    PageRegs<4> s4;
 
     // ---- q: load the R heads, common power-of-two normalisation, group sums ----
     // lane l holds channels 2l, 2l+1 of every head
+    uint32_t q2[8];
+#pragma unroll
+    for (int h = 0; h < 8; ++h)   // (heads beyond R: head 0 again, not used)
+        q2[h] = reinterpret_cast<const uint32_t *>(q + ((size_t)seq * n_q_heads + kvh * R + (h < R ? h : 0)) * kHeadDim)[lane];
+    batch_check(cx, list, batch_ids(cx, list, pb));
     float qv[8][2];
     float amax = 0.0f;
 #pragma unroll
     for (int h = 0; h < 8; ++h) {
-        uint32_t two = 0;
-        if (h < R) two = reinterpret_cast<const uint32_t *>(q + ((size_t)seq * n_q_heads + kvh * R + h) * kHeadDim)[lane];
+        const uint32_t two = h < R ? q2[h] : 0;
         qv[h][0] = __uint_as_float(two << 16);
         qv[h][1] = __uint_as_float(two & 0xffff0000u);
         amax = fmaxf(amax, fmaxf(fabsf(qv[h][0]), fabsf(qv[h][1])));
@@ -860,7 +903,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PE
     lc.zmul = r16 >= 8 ? 0.0f : 0x1p-24f;
     lc.vs_idx = kPvS + q4 * 4 + 2 * (r16 >> 3);
     lc.vs_st = lane;
-    lc.opaque_zero = opaque_zero;
     lc.vrot[0] = lc.vrot[1] = 0;
     lc.vmask[0] = lc.vmask[1] = lc.vmask[2] = lc.vmask[3] = 0;
     lc.tok0 = 16 * (r16 >> 3) + 4 * q4;
@@ -873,12 +915,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PE
         const uint32_t c = lane == 1 ? 0x3c003c00u : 0u;
         lds.pv[kPvZero + lane] = make_uint4(c, c, c, c);
     }
-    // q * 2^E to LDS; per-group sums of the unscaled q: lanes 16g .. 16g+15 hold group g
+    // q * 2^E to LDS
 #pragma unroll
-    for (int h = 0; h < 8; ++h) {
-        qf_store<KC>(qf, h, lane, pack_h2(qv[h][0] * two_e, qv[h][1] * two_e));   // exact: q has 8 significant bits
-        const float sum = row_sum(qv[h][0] + qv[h][1]);
-        if (r16 == 0) lds.zl()[h][q4] = sum;   // [head][group]
+    for (int h = 0; h < 8; ++h) qf_store<KC>(qf, h, lane, pack_h2(qv[h][0] * two_e, qv[h][1] * two_e));   // exact: q has 8 significant bits
+    lds_order();
+    {
+        // sums of q over the groups, one MFMA per group: row = head, the 32 channels of the group against a column of ones
+        floatx4 gsum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const uint4 a = *reinterpret_cast<const uint4 *>(static_cast<const char *>(qf) + qf_chunk<KC>(r16 & 7, g * 4 + q4));
+            const uint32_t one = r16 == g ? 0x3c003c00u : 0u;
+            gsum = mfma(as_half8(a.x, a.y, a.z, a.w), as_half8(one, one, one, one), gsum);
+        }
+        const float undo = ldexpf(1.0f, -E);
+        if (q4 < 2 && r16 < 4)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lds.zl()[4 * q4 + i][r16] = gsum[i] * undo;   // [head][group]
     }
     lds_order();
     const int hcol = (r16 & 7) & (R - 1);   // head of this lane's column (columns beyond R repeat heads)
@@ -910,19 +963,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PE
     st.m_ref = -INFINITY;
     st.sat = 0;
 
+    batch_finish(cx, list);
     if (has2) {
         build_q_operand<2, KC>(qf, hcol, q4, lane, lds);
         LaneConst lc2 = lc;
         if constexpr (KC) {
             lc2.kappa = lc.kappa * lc.F;   // the power of two that the K scale carries otherwise
-            lds.kc_nil()[lane & 31] = make_uint4(0u, 0u, 0u, 0u);
         }
-        start_pages<2, KC>(cx, wr2, s2);
+        const Record rec = batch_record<2>(cx, list, pb, true);
+        load_page_k<2, KC>(s2, rec, lane);
+        load_page_v<2>(s2, rec, lane);
         lds_order();
-        run_pages<2, KC>(cx, wr2, s2, pe, pe - pb, qz, lc2, st, lds);
+        run_pages<2, KC>(cx, list, pb, e2, s2, qz, lc2, st, lds);
     }
     if (has4) {
-        start_pages<4, KC>(cx, wr4, s4);
+        batch_seek(cx, list, b4);
+        const Record rec = batch_record<4>(cx, list, b4, true);
+        load_page_k<4, KC>(s4, rec, lane);
+        load_page_v<4>(s4, rec, lane);
         if (KC && has2) {   // the INT2 pages have used that memory since
             lds_order();
 #pragma unroll
@@ -936,7 +994,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PE
         }
         build_q_operand<4, KC>(qf, hcol, q4, lane, lds);
         lds_order();
-        run_pages<4, KC>(cx, wr4, s4, pe, pe - pb, qz, lc, st, lds);
+        run_pages<4, KC>(cx, list, b4, pe, s4, qz, lc, st, lds);
     }
 
     // ---- write the partial (m, l, acc) of this item ------------------------------
@@ -956,7 +1014,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TKV_WAVES_PE
     // head so that heads h and h + 4, written by the same instruction, fall on different banks.
     constexpr int kOutRow = kHeadDim + 4;
     static_assert(sizeof(LdsExtra<KC>) + sizeof(float) * kPageTokens * kGroups + sizeof(uint4) * kPvChunks >= 8 * kOutRow * sizeof(float),
-                  "the output tile must fit in what precedes kz, qo (= zl()) and alpha in Lds");
+                  "the output tile must fit in what precedes qo (= zl()) and alpha in Lds");
     float *tile = reinterpret_cast<float *>(&lds);
     if ((q4 >> 1) == hb) {   // the quadrants whose rows and columns belong to the same pair of groups
 #pragma unroll
@@ -1083,11 +1141,13 @@ int tkv_launch_decode_split(const tkv_desc *desc, const void *pool, const uint8_
     float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
     const float kappa = sm_scale * 1.44269504088896340736f;
     auto kernel = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL ? tkv_decode_kernel<true> : tkv_decode_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_items * desc->n_kv_heads)), dim3(64), 0,
-                       (hipStream_t)stream, (const uint8_t *)pool, bit_map, (const uint16_t *)q, page_indptr,
-                       page_ids, n_tok_int2, n_tok_int4, items, batch, desc->n_kv_heads, n_q_heads,
-                       desc->n_pages_int2, desc->n_pages_int4, kappa, acc_ws, ml_ws, status
-                       );
+    int log2_r = 0;   // 1, 2, 4 or 8 query heads per kv head
+    while ((desc->n_kv_heads << log2_r) < n_q_heads) ++log2_r;
+    constexpr int kMaxY = 65535;
+    const dim3 grid((unsigned)desc->n_kv_heads, (unsigned)(n_items < kMaxY ? n_items : kMaxY), (unsigned)((n_items + kMaxY - 1) / kMaxY));
+    hipLaunchKernelGGL(kernel, grid, dim3(64), 0, (hipStream_t)stream, (const uint8_t *)pool, bit_map, (const uint16_t *)q, page_indptr,
+                       page_ids, n_tok_int2, n_tok_int4, items, n_items, batch, desc->n_kv_heads, log2_r,
+                       desc->n_pages_int2, desc->n_pages_int4, kappa, acc_ws, ml_ws, status);
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
 
