@@ -3,15 +3,23 @@
 // paged pool (paper Sec. 3.2.1 for the quantisation scheme, Sec. 3.2.2-3.2.3
 // for the two pools and the per-token bitwidth array).
 //
-// One workgroup of 256 threads owns one (destination page, kv head) record.
-// Thread (slot = tid/4, group = tid%4) quantises one group of 32 channels of
-// the token bound for that slot, for K and for V, entirely in registers: a
-// group is 64 contiguous bytes of the input, so min/max need no cross-lane
-// step.  K words go straight to HBM (a wavefront's stores for one word index
-// are 256 contiguous bytes, written with non-temporal stores).  V codes are transposed through LDS, because
-// the V plane packs tokens, not channels, into a word; for a page that arrives whole, the V words and the two V
-// metadata planes, which are adjacent in the record, are put together in LDS and leave in 16-byte non-temporal
-// stores, one KiB per instruction of a wavefront.
+// Two workgroups of 256 threads per (destination page, kv head) record, one for its K planes and one for its V planes.
+// Thread (slot = tid/4, group = tid%4) quantises one group of 32 channels of the token bound for that slot; a group
+// is 64 contiguous bytes of the input, so min/max need no cross-lane step.
+//
+// What bounds it: HBM for whole pages (512 B read and 96 / 160 B written per token and head), the chain of dependent
+// loads (arguments -> slots -> rows -> result) for a few tokens.  Hence
+//  - the rows go straight to LDS, whole 128-byte lines per instruction and non-temporal, without a register, and all
+//    that can be asked for at once is: the slots, then tags, rows and the V words that may have to be merged;
+//  - K and V apart: a workgroup holds 16 KiB of LDS and eight are resident per compute unit, each in a phase of its
+//    own.  65 536 tokens x 8 heads, inputs not in any cache: 67.1 us with both in one workgroup and 64-byte runs per thread
+//    through registers, 63.1 with rows through LDS (32 KiB, five resident), 59.1 apart (5.6 TB/s; with ordinary
+//    loads 62.9, with ordinary stores 60.7); per-channel keys 69.4 -> 60.1; one token for each of 32 sequences 6.0 -> 4.5.
+//
+// K words go straight to HBM (a wavefront's stores for one word index are 256 contiguous bytes, written with
+// non-temporal stores).  V codes are transposed through LDS, because the V plane packs tokens, not channels, into a
+// word; for a page that arrives whole, the V words and the two V metadata planes, which are adjacent in the record,
+// are put together in LDS and leave in 16-byte non-temporal stores, one KiB per instruction of a wavefront.
 //
 // Arithmetic is IEEE binary32 without fused multiply-add so that the codes,
 // scales and zero-points match a scalar CPU evaluation bit for bit:
@@ -19,8 +27,6 @@
 //   code = clamp(rint((x - zero) * (1 / scale)), 0, 2^b - 1), 0 if scale == 0.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
-
-#include <type_traits>
 
 #include "tkv_internal.h"
 #include "tkv_layout.h"
@@ -93,13 +99,26 @@ __device__ __forceinline__ GroupQ quantize_values(const float (&f)[32])
     return out;
 }
 
+constexpr int kRowBytes = kHeadDim * 2, kRowPieces = kRowBytes / 16;   // a row: one token of one kv head, of K or of V
+// The rows are fetched by the wavefront that uses them (wavefront w: slots 16 w .. 16 w + 15), straight into LDS: one
+// instruction moves four rows, sixteen lanes to a row, 1 KiB that is contiguous in LDS.  A thread then reads four
+// consecutive 16-byte pieces of its row; piece p of row r sits at place p ^ (r & 3), so that the lanes of neighbouring
+// rows read from different banks.
+__device__ __forceinline__ void fetch_row_pieces(uint4 *lds_wave, int i, const uint16_t *__restrict__ row, int lane)
+{
+    const uint4 *src = reinterpret_cast<const uint4 *>(row) + ((lane & 15) ^ (lane >> 4));
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)(lds_wave + 64 * i), 16, 0, 2 /* nt */);
+}
+__device__ __forceinline__ int piece_at(int slot, int p) { return slot * kRowPieces + (p ^ (slot & 3)); }
+
 template <int BITS>
-__device__ __forceinline__ GroupQ quantize_group(const uint4 *src)
+__device__ __forceinline__ GroupQ quantize_group(const uint4 *rows, int slot, int g)
 {
     float f[32];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint4 v = src[i];
+        const uint4 v = rows[piece_at(slot, 4 * g + i)];
         const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -110,79 +129,60 @@ __device__ __forceinline__ GroupQ quantize_group(const uint4 *src)
     return quantize_values<BITS>(f);
 }
 
-// LDS of the per-channel key path: the bf16 keys of the page [slot][channel], then their codes one per byte.
-struct KcLds {
-    alignas(16) uint16_t kt[kPageTokens][kHeadDim];
-    alignas(16) uint8_t kcodes[kPageTokens][kHeadDim];
-    int n_in_block[2];
-};
-struct NoLds {};
+// V codes of the page, one per byte: row of slot s, where the K rows of the same wavefront were.  144-byte rows: the four
+// quads that one instruction of the transpose reads lie four rows apart and must not meet on the same banks.
+__device__ __forceinline__ int code_row(int slot) { return (slot >> 4) * 16 * kRowBytes + (slot & 15) * 144; }
+// 16-byte piece c of the V words and V metadata planes of a whole page, on their way out: the 112 pieces behind the
+// code rows in each wavefront's part of the row area.
+__device__ __forceinline__ int out_piece(int c)
+{
+    const int part = (c >= 112 ? 1 : 0) + (c >= 224 ? 1 : 0);
+    return part * 16 * kRowPieces + 144 + (c - 112 * part);
+}
+static_assert((Rec<4>::kCodeBytes + 2 * kMetaBytes) / 16 <= 3 * 112, "the pieces of an INT4 page fit behind the code rows of three wavefronts");
+// Token (slot) of code position p in a V word of (block of 32 tokens, quad); INT2 words hold both blocks.
+template <int BITS> __device__ __forceinline__ constexpr int v_token(int blk, int quad, int p)
+{
+    const int j = BITS == 4 ? 2 * (p & 3) + (p >> 2) : 2 * (p & 3) + (p >> 3);
+    return 32 * (BITS == 4 ? blk : (p & 7) >> 2) + 16 * (j >> 2) + 4 * quad + (j & 3);
+}
 
-// KC: keys per channel over each block of 32 slots (INT2 pages only); `valid` is then uniform over a block.
-template <int BITS, bool KC, class KL>
-__device__ __forceinline__ void append_record(uint8_t *rec, const uint16_t *K, const uint16_t *V, int src,
-                                              bool valid, int head, int n_kv_heads,
-                                              uint32_t (*lds_codes)[32], uint8_t *lds_valid, uint4 *lds_vout, KL &kl)
+// The K planes of a record.  `mask`: the slots that receive a token, the same in all four wavefronts.
+// KC: keys per channel over each block of 32 slots (INT2 pages only); the mask then holds whole blocks.
+template <int BITS, bool KC>
+__device__ __forceinline__ void append_k(uint8_t *rec, uint64_t mask, uint4 *rows)
 {
     using R = Rec<BITS>;
     const int tid = threadIdx.x, slot = tid >> 2, g = tid & 3;
     const int tile = slot >> 4, row = slot & 15;
-    if (g == 0) lds_valid[slot] = valid;
-    uint16_t v_scale = 0, v_zero = 0;
-    if (valid) {
-        const size_t e = ((size_t)src * n_kv_heads + head) * kHeadDim + g * kGroup;
-        if constexpr (KC) {
-            // the keys wait in LDS until the whole block is there
-            const uint4 *ksrc = reinterpret_cast<const uint4 *>(K + e);
-            uint4 *kdst = reinterpret_cast<uint4 *>(&kl.kt[slot][g * kGroup]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) kdst[i] = ksrc[i];
-        } else {
-            const GroupQ kq = quantize_group<BITS>(reinterpret_cast<const uint4 *>(K + e));
-            uint32_t *kc = reinterpret_cast<uint32_t *>(rec + R::kKCodes);
-            constexpr int words = BITS;   // 32-bit words of codes per group: 4 (INT4) or 2 (INT2)
-            // these stores of a wavefront fill whole lines (256 contiguous bytes per word index, 128 per plane)
-#pragma unroll
-            for (int w = 0; w < words; ++w) store_once(&kc[((tile * words + w) * 16 + row) * 4 + g], kq.words[w]);
-            store_once(&reinterpret_cast<uint16_t *>(rec + R::kKScale)[slot * 4 + g], kq.scale);
-            store_once(&reinterpret_cast<uint16_t *>(rec + R::kKZero)[slot * 4 + g], kq.zero);
-        }
-
-        const GroupQ vq = quantize_group<BITS>(reinterpret_cast<const uint4 *>(V + e));
-        const int mi = vmeta_index(slot, g);
-        v_scale = vq.scale;
-        v_zero = vq.zero;
-        // the two V metadata planes (2 x 512 B) are put together behind the V words in the staging area
-        uint16_t *meta = reinterpret_cast<uint16_t *>(lds_vout + R::kCodeBytes / 16);
-        meta[mi] = vq.scale;
-        meta[kMetaBytes / 2 + mi] = vq.zero;
-        uint4 *dst = reinterpret_cast<uint4 *>(&lds_codes[slot][g * 8]);
-        dst[0] = make_uint4(vq.bytes[0], vq.bytes[1], vq.bytes[2], vq.bytes[3]);
-        dst[1] = make_uint4(vq.bytes[4], vq.bytes[5], vq.bytes[6], vq.bytes[7]);
-    }
-    const bool page_full = __syncthreads_and(valid);   // every slot of the page arrives in this call
+    const bool valid = (mask >> slot) & 1;
+    uint32_t *kc = reinterpret_cast<uint32_t *>(rec + R::kKCodes);
+    constexpr int words = BITS;   // 32-bit words of codes per group: 4 (INT4) or 2 (INT2)
     if constexpr (KC) {
+        __syncthreads();   // every row is there
         // thread (block, channel): the block's 32 token values of one channel are one quantisation group
-        {
-            const int blk = tid >> 7, c = tid & 127;
-            if (kl.n_in_block[blk] == kGroup) {
-                float f[32];
+        const int blk = tid >> 7, c = tid & 127;
+        const bool there = (mask >> (32 * blk)) & 1;
+        GroupQ kq;
+        if (there) {
+            float f[32];
+            const uint16_t *kt = reinterpret_cast<const uint16_t *>(rows);
 #pragma unroll
-                for (int i = 0; i < 32; ++i) f[i] = __uint_as_float((uint32_t)kl.kt[32 * blk + i][c] << 16);
-                const GroupQ kq = quantize_values<BITS>(f);
-                const int mi = kcmeta_index(blk, c);
-                reinterpret_cast<uint16_t *>(rec + R::kKScale)[mi] = kq.scale;
-                reinterpret_cast<uint16_t *>(rec + R::kKZero)[mi] = kq.zero;
-#pragma unroll
-                for (int i = 0; i < 32; ++i) kl.kcodes[32 * blk + i][c] = (uint8_t)(kq.bytes[i >> 2] >> (8 * (i & 3)));
-            }
+            for (int i = 0; i < 32; ++i) f[i] = __uint_as_float((uint32_t)kt[8 * piece_at(32 * blk + i, c >> 3) + (c & 7)] << 16);
+            kq = quantize_values<BITS>(f);
+            const int mi = kcmeta_index(blk, c);
+            reinterpret_cast<uint16_t *>(rec + R::kKScale)[mi] = kq.scale;
+            reinterpret_cast<uint16_t *>(rec + R::kKZero)[mi] = kq.zero;
         }
+        __syncthreads();   // every row is read; their place takes the codes, one per byte [slot][channel]
+        uint8_t *kcodes = reinterpret_cast<uint8_t *>(rows);
+        if (there)
+#pragma unroll
+            for (int i = 0; i < 32; ++i) kcodes[(32 * blk + i) * kHeadDim + c] = (uint8_t)(kq.bytes[i >> 2] >> (8 * (i & 3)));
         __syncthreads();
         // thread (slot, group) again: its token's 32 codes of the group, packed as in the per-token layout
         if (valid) {
-            const uint4 *cb = reinterpret_cast<const uint4 *>(&kl.kcodes[slot][g * kGroup]);
-            uint32_t *kc = reinterpret_cast<uint32_t *>(rec + R::kKCodes);
-            constexpr int words = BITS;
+            const uint4 *cb = reinterpret_cast<const uint4 *>(kcodes + slot * kHeadDim + g * kGroup);
             constexpr int per_word = 32 / BITS;
             uint32_t wv[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -198,17 +198,45 @@ __device__ __forceinline__ void append_record(uint8_t *rec, const uint16_t *K, c
                     }
             }
 #pragma unroll
-            for (int w = 0; w < words; ++w) kc[((tile * words + w) * 16 + row) * 4 + g] = wv[w];
+            for (int w = 0; w < words; ++w) store_once(&kc[((tile * words + w) * 16 + row) * 4 + g], wv[w]);
         }
+    } else if (valid) {
+        const GroupQ kq = quantize_group<BITS>(rows, slot, g);
+        // these stores of a wavefront fill whole lines (256 contiguous bytes per word index, 128 per plane)
+#pragma unroll
+        for (int w = 0; w < words; ++w) store_once(&kc[((tile * words + w) * 16 + row) * 4 + g], kq.words[w]);
+        store_once(&reinterpret_cast<uint16_t *>(rec + R::kKScale)[slot * 4 + g], kq.scale);
+        store_once(&reinterpret_cast<uint16_t *>(rec + R::kKZero)[slot * 4 + g], kq.zero);
     }
-    // V codes: one 32-bit word = one channel x (8 | 16) tokens of one quad
-    const uint8_t *codes = reinterpret_cast<const uint8_t *>(lds_codes);
-    uint32_t *vc = reinterpret_cast<uint32_t *>(rec + R::kVCodes);
+}
+
+// The V planes.  `old`: this thread's V words as they are, if the page does not arrive whole.
+template <int BITS>
+__device__ __forceinline__ void append_v(uint8_t *rec, uint64_t mask, const uint32_t (&old)[4], uint4 *rows)
+{
+    using R = Rec<BITS>;
+    const int tid = threadIdx.x, slot = tid >> 2, g = tid & 3;
+    const bool valid = (mask >> slot) & 1;
+    uint8_t *codes = reinterpret_cast<uint8_t *>(rows);
+    uint16_t v_scale = 0, v_zero = 0;
+    if (valid) {
+        const GroupQ vq = quantize_group<BITS>(rows, slot, g);
+        v_scale = vq.scale;
+        v_zero = vq.zero;
+        uint4 *dst = reinterpret_cast<uint4 *>(codes + code_row(slot) + g * kGroup);
+        dst[0] = make_uint4(vq.bytes[0], vq.bytes[1], vq.bytes[2], vq.bytes[3]);
+        dst[1] = make_uint4(vq.bytes[4], vq.bytes[5], vq.bytes[6], vq.bytes[7]);
+    }
+    __syncthreads();   // all V codes are there, all V rows read
+    const int mi = vmeta_index(slot, g);
     constexpr int n_words = R::kCodeBytes / 4;
-    if (page_full) {
+    if (mask == ~0ull) {
         // Whole page: a thread transposes four adjacent channels x the (8 | 16) tokens of one word with 32-bit
         // LDS reads (a row of the byte tile holds the token's codes in channel order), merges 2 | 4 tokens per
-        // byte and finishes with a 4 x 4 byte transpose; no read-modify-write.
+        // byte and finishes with a 4 x 4 byte transpose; no read-modify-write.  The V words and the two V metadata
+        // planes are put together behind the code rows.
+        reinterpret_cast<uint16_t *>(rows + out_piece(R::kCodeBytes / 16 + (mi >> 3)))[mi & 7] = v_scale;
+        reinterpret_cast<uint16_t *>(rows + out_piece((R::kCodeBytes + kMetaBytes) / 16 + (mi >> 3)))[mi & 7] = v_zero;
         constexpr int n_units = n_words / 4;   // 256 (INT4) / 128 (INT2)
         if (tid < n_units) {
             const int k = tid & 3, n4 = (tid >> 2) & 3, quad = (tid >> 4) & 3, h = (tid >> 6) & 1;
@@ -219,67 +247,49 @@ __device__ __forceinline__ void append_record(uint8_t *rec, const uint16_t *K, c
             for (int b = 0; b < 4; ++b) {
                 m[b] = 0;
 #pragma unroll
-                for (int e = 0; e < 8 / BITS; ++e) {
-                    const int p = (8 / BITS) * b + e;   // position of the token in the word
-                    int t;
-                    if (BITS == 4) {
-                        const int j = 2 * (p & 3) + (p >> 2);
-                        t = 32 * blk + 16 * (j >> 2) + 4 * quad + (j & 3);
-                    } else {
-                        const int j = 2 * (p & 3) + (p >> 3);
-                        t = 32 * ((p & 7) >> 2) + 16 * (j >> 2) + 4 * quad + (j & 3);
-                    }
-                    m[b] |= *reinterpret_cast<const uint32_t *>(codes + t * kHeadDim + c0) << (BITS * e);
-                }
+                for (int e = 0; e < 8 / BITS; ++e)
+                    m[b] |= *reinterpret_cast<const uint32_t *>(codes + code_row(v_token<BITS>(blk, quad, (8 / BITS) * b + e)) + c0) << (BITS * e);
             }
             // byte i of m[b] = byte b of the word of channel c0 + i
             const uint32_t t01 = __builtin_amdgcn_perm(m[1], m[0], 0x05010400u), u01 = __builtin_amdgcn_perm(m[1], m[0], 0x07030602u);
             const uint32_t t23 = __builtin_amdgcn_perm(m[3], m[2], 0x05010400u), u23 = __builtin_amdgcn_perm(m[3], m[2], 0x07030602u);
             const uint32_t wv[4] = {__builtin_amdgcn_perm(t23, t01, 0x05040100u), __builtin_amdgcn_perm(t23, t01, 0x07060302u),
                                     __builtin_amdgcn_perm(u23, u01, 0x05040100u), __builtin_amdgcn_perm(u23, u01, 0x07060302u)};
-            const int base = (((BITS == 4 ? blk * 2 : 0) + h) * 4 + quad) * 64;
-            uint32_t *vs = reinterpret_cast<uint32_t *>(lds_vout);
+            const int first = (((BITS == 4 ? blk * 2 : 0) + h) * 4 + quad) * 16 + 4 * n4;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) vs[base + (4 * n4 + i) * 4 + k] = wv[i];
+            for (int i = 0; i < 4; ++i) reinterpret_cast<uint32_t *>(rows + out_piece(first + i))[k] = wv[i];
         }
         __syncthreads();
-        // The V words and the two V metadata planes are adjacent in the record: one run of 16-byte stores,
-        // every instruction of a wavefront a whole KiB, written once
+        // one run of 16-byte stores, every instruction of a wavefront a whole KiB, written once
         constexpr int n_chunks = (R::kCodeBytes + 2 * kMetaBytes) / 16;   // 192 (INT2) / 320 (INT4)
         uint4 *dst = reinterpret_cast<uint4 *>(rec + R::kVCodes);
 #pragma unroll
-        for (int c = tid; c < n_chunks; c += 256) store_once(dst + c, lds_vout[c]);
+        for (int c = tid; c < n_chunks; c += 256) store_once(dst + c, rows[out_piece(c)]);
         return;
     }
+    // A page that arrives in parts: a thread's words change in the fields of the tokens that arrive.  The tokens of a
+    // word share the quad, which is the number of the wavefront: wavefronts without any have nothing to do.
     if (valid) {
-        const int mi = vmeta_index(slot, g);
         reinterpret_cast<uint16_t *>(rec + R::kVScale)[mi] = v_scale;
         reinterpret_cast<uint16_t *>(rec + R::kVZero)[mi] = v_zero;
     }
+    uint32_t *vc = reinterpret_cast<uint32_t *>(rec + R::kVCodes);
+    const int quad = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
-    for (int widx = tid; widx < n_words; widx += 256) {
-        const int jl = widx & 3, n = (widx >> 2) & 15, quad = (widx >> 6) & 3, jh = (widx >> 8) & 1;
-        const int blk = widx >> 9;   // INT4 only (0 for INT2)
+    for (int i = 0; i < n_words / 256; ++i) {
+        const int widx = tid + 256 * i;
+        const int jl = widx & 3, n = (widx >> 2) & 15, jh = i & 1, blk = i >> 1;
         const int c = (jh * 4 + jl) * 16 + n;
-        uint32_t val = 0, mask = 0;
+        uint32_t field = 0;   // the bits of the word that change
 #pragma unroll
-        for (int p = 0; p < 32 / BITS; ++p) {
-            int t;
-            if (BITS == 4) {
-                const int j = 2 * (p & 3) + (p >> 2);
-                t = 32 * blk + 16 * (j >> 2) + 4 * quad + (j & 3);
-            } else {
-                const int j = 2 * (p & 3) + (p >> 3);
-                t = 32 * ((p & 7) >> 2) + 16 * (j >> 2) + 4 * quad + (j & 3);
-            }
-            const uint32_t field = ((1u << BITS) - 1u) << (BITS * p);
-            if (lds_valid[t]) {
-                val |= (uint32_t)codes[t * kHeadDim + c] << (BITS * p);
-                mask |= field;
-            }
-        }
-        if (mask == 0xffffffffu) vc[widx] = val;
-        else if (mask) vc[widx] = (vc[widx] & ~mask) | val;
+        for (int p = 0; p < 32 / BITS; ++p)
+            if ((mask >> v_token<BITS>(blk, quad, p)) & 1) field |= ((1u << BITS) - 1u) << (BITS * p);
+        if (field == 0) continue;
+        uint32_t val = 0;
+#pragma unroll
+        for (int p = 0; p < 32 / BITS; ++p)   // (the rows of other tokens hold anything)
+            val |= ((uint32_t)codes[code_row(v_token<BITS>(blk, quad, p)) + c] & ((1u << BITS) - 1u)) << (BITS * p);
+        vc[widx] = (old[i] & ~field) | (val & field);
     }
 }
 
@@ -287,50 +297,74 @@ template <bool KC>
 __global__ __launch_bounds__(256) void tkv_append_kernel(
     uint8_t *__restrict__ pool, uint8_t *__restrict__ bit_map, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const uint8_t *__restrict__ tag_bits, int n_tokens,
-    const int32_t *__restrict__ work_pages, const int32_t *__restrict__ work_src, int n_kv_heads,
+    const int32_t *__restrict__ work_pages, const int32_t *__restrict__ work_src, int n_work, int n_kv_heads,
     int n_pages_int2, int n_pages_int4, int32_t *status)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t lds_codes[kPageTokens][32];
-    __shared__ uint8_t lds_valid[kPageTokens];
-    // a whole page's V words and V metadata planes in record order, on their way to 16-byte stores
-    __shared__ uint4 lds_vout[(Rec<4>::kCodeBytes + 2 * kMetaBytes) / 16];
-    __shared__ typename std::conditional<KC, KcLds, NoLds>::type kl;
-    const int w = blockIdx.x / n_kv_heads, head = blockIdx.x % n_kv_heads;
+    __shared__ uint4 rows[kPageTokens * kRowPieces];
+    const int w = blockIdx.y + blockIdx.z * gridDim.y, head = blockIdx.x >> 1;
+    const bool is_v = blockIdx.x & 1;
+    if (w >= n_work) return;
+    // All arguments at once: a launch of a few tokens is a chain of dependent loads, and each argument fetched where it
+    // is first used would be one more.
+    asm volatile("" :: "s"(pool), "s"(bit_map), "s"(K), "s"(V), "s"(tag_bits), "s"(status));
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t *__restrict__ srcs = work_src + (size_t)w * kPageTokens;
     const int page = work_pages[w];
+    const int src = srcs[lane];   // every wavefront looks at all 64 slots
+    int row_src[4];               // and fetches pieces of four rows per lane
+#pragma unroll
+    for (int i = 0; i < 4; ++i) row_src[i] = srcs[16 * wave + 4 * i + (lane >> 4)];
     if (page < 0 || page >= n_pages_int2 + n_pages_int4) {
-        if (status && threadIdx.x == 0) atomicOr(status, TKV_STATUS_PAGE_RANGE);
+        if (status && tid == 0) atomicOr(status, TKV_STATUS_PAGE_RANGE);
         return;
     }
     const int bits = page < n_pages_int2 ? 2 : 4;
-    const int slot = threadIdx.x >> 2;
-    const int src = work_src[(size_t)w * kPageTokens + slot];
-    bool valid = src >= 0 && src < n_tokens;
-    if (valid && tag_bits[src] != bits) {
-        valid = false;
-        if (status && (threadIdx.x & 3) == 0) atomicOr(status, TKV_STATUS_TAG_MISMATCH);
-    }
     uint8_t *rec = pool + record_offset(page, head, n_kv_heads, n_pages_int2);
-    if constexpr (KC) {
-        if (bits == 2) {
-            // a block of 32 slots is quantised in one piece: it takes part whole or not at all
-            if (threadIdx.x < 2) kl.n_in_block[threadIdx.x] = 0;
-            __syncthreads();
-            if ((threadIdx.x & 3) == 0 && valid) atomicAdd(&kl.n_in_block[slot >> 5], 1);
-            __syncthreads();
-            const int n = kl.n_in_block[slot >> 5];
-            if (n != 0 && n != kGroup) {
-                valid = false;
-                if (status && (threadIdx.x & 127) == 0) atomicOr(status, TKV_STATUS_BLOCK_PARTIAL);
-            }
-            append_record<2, true>(rec, K, V, src, valid, head, n_kv_heads, lds_codes, lds_valid, lds_vout, kl);
-        } else {
-            append_record<4, false>(rec, K, V, src, valid, head, n_kv_heads, lds_codes, lds_valid, lds_vout, kl);
+    const bool in = src >= 0 && src < n_tokens;
+    uint8_t tag = 0;
+    if (in) tag = tag_bits[src];
+    const size_t stride = (size_t)n_kv_heads * kHeadDim;
+    const uint16_t *from = (is_v ? V : K) + head * kHeadDim;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (row_src[i] >= 0 && row_src[i] < n_tokens) fetch_row_pieces(rows + 16 * wave * kRowPieces, i, from + (size_t)row_src[i] * stride, lane);
+    // the V words of a page that does not arrive whole, in case they change
+    uint32_t old[4] = {0, 0, 0, 0};
+    auto fetch_old = [&]() {
+        const uint32_t *vc = reinterpret_cast<const uint32_t *>(rec + (bits == 2 ? Rec<2>::kVCodes : Rec<4>::kVCodes)) + tid;
+        old[0] = vc[0];
+        old[1] = vc[256];
+        if (bits == 4) {
+            old[2] = vc[512];
+            old[3] = vc[768];
         }
-    } else {
-        if (bits == 2) append_record<2, false>(rec, K, V, src, valid, head, n_kv_heads, lds_codes, lds_valid, lds_vout, kl);
-        else append_record<4, false>(rec, K, V, src, valid, head, n_kv_heads, lds_codes, lds_valid, lds_vout, kl);
+    };
+    const bool in_parts = is_v && __ballot(in) != ~0ull;
+    if (in_parts) fetch_old();
+    const bool fits = in && tag == bits;
+    uint64_t mask = __ballot(fits);
+    if (in && !fits && status && wave == 0) atomicOr(status, TKV_STATUS_TAG_MISMATCH);
+    if (is_v && mask != ~0ull && !in_parts) fetch_old();   // only where tags contradict the page
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the rows this wavefront fetched are in LDS
+    if (KC && bits == 2) {
+        // a block of 32 slots is quantised in one piece: it takes part whole or not at all
+        uint64_t whole = 0;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const uint32_t half = (uint32_t)(mask >> (32 * b));
+            if (half == 0xffffffffu) whole |= 0xffffffffull << (32 * b);
+            else if (half != 0 && status && tid == 0) atomicOr(status, TKV_STATUS_BLOCK_PARTIAL);
+        }
+        mask = whole;
     }
-    if (head == 0 && __syncthreads_or(valid) && threadIdx.x == 0) bit_map[page] = (uint8_t)bits;
+    if (is_v) {
+        if (bits == 2) append_v<2>(rec, mask, old, rows);
+        else append_v<4>(rec, mask, old, rows);
+    } else {
+        if (bits == 2) append_k<2, KC>(rec, mask, rows);
+        else append_k<4, false>(rec, mask, rows);
+    }
+    if (blockIdx.x == 0 && tid == 0 && mask != 0) bit_map[page] = (uint8_t)bits;
 }
 
 } // namespace
@@ -339,15 +373,12 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
                       const uint8_t *tag_bits, int32_t n_tokens, const int32_t *work_pages,
                       const int32_t *work_src, int32_t n_work, int32_t *status, void *stream)
 {
-    const dim3 grid((unsigned)(n_work * desc->n_kv_heads)), block(256);
+    constexpr int kMaxY = 65535;
+    const dim3 grid((unsigned)desc->n_kv_heads * 2, (unsigned)(n_work < kMaxY ? n_work : kMaxY), (unsigned)((n_work + kMaxY - 1) / kMaxY));
     const bool kc = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL;
     auto kernel = kc ? tkv_append_kernel<true> : tkv_append_kernel<false>;
-    // The kernel is bound by the memory system, which serves four resident workgroups per compute unit
-    // slightly faster than the eight that would fit (cfg2: 282 vs 294 us; 3 -> 282, 2 -> 339, 6 -> 286): unused
-    // dynamic LDS holds the residency at four.  The per-channel-key kernel's own 33 KB do the same.
-    const size_t pad_lds = kc ? 0 : 24 * 1024;
-    hipLaunchKernelGGL(kernel, grid, block, pad_lds, (hipStream_t)stream, (uint8_t *)pool, bit_map,
-                       (const uint16_t *)K, (const uint16_t *)V, tag_bits, n_tokens, work_pages, work_src,
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, (hipStream_t)stream, (uint8_t *)pool, bit_map,
+                       (const uint16_t *)K, (const uint16_t *)V, tag_bits, n_tokens, work_pages, work_src, n_work,
                        desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4, status);
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }

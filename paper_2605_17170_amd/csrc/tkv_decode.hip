@@ -131,16 +131,8 @@ template <int CTRL> __device__ __forceinline__ float row_dpp(float v)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
-// Sum / maximum over a row of 16 lanes, in every lane of the row: neighbours, pairs, quads, halves
+// Maximum over a row of 16 lanes, in every lane of the row: neighbours, pairs, quads, halves
 // (quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror).
-__device__ __forceinline__ float row_sum(float v)
-{
-    v += row_dpp<0xB1>(v);
-    v += row_dpp<0x4E>(v);
-    v += row_dpp<0x141>(v);
-    v += row_dpp<0x140>(v);
-    return v;
-}
 __device__ __forceinline__ float row_max(float v)
 {
     v = fmaxf(v, row_dpp<0xB1>(v));
