@@ -3,17 +3,18 @@
 // listed slot, dequantises it into FP16 and writes dense K / V rows in the
 // caller's token order, ready for an FP16 prefill attention kernel.
 //
-// A workgroup of 256 threads handles one (page, kv head) record at a time, the
-// mirror image of the append kernel, and loops over records with the next
-// record's loads already in flight.  Thread (slot = tid/4, part = tid%4) produces
-// channels 32*i + 8*part .. +7 of its token for the four groups i: one
-// 16-byte load fetches its K codes of all four groups.  Its four 16-byte
-// pieces of a row would each fill a quarter of a line; mirror-image threads of
-// two neighbouring slots trade pieces instead, so that eight lanes write one
-// whole 128-byte line per store instruction, and the stores are non-temporal
-// (the output is written once).  V is stored channel-major (a word holds several
-// tokens of one channel), so the V words are expanded into an LDS byte tile
-// first and each thread reads its token's codes back.
+// Two workgroups of 256 threads per (page, kv head) record, the mirror image of the append kernel: one writes the K
+// rows, one the V rows.  Thread (slot = tid/4, part = tid%4) produces channels 32*i + 8*part .. +7 of its token for
+// the four groups i.  For K one 16-byte load fetches the codes of all four groups, and nothing goes through LDS.  V
+// is stored channel-major (a word holds several tokens of one channel), so the V words are expanded into an LDS byte
+// tile first and each thread reads its token's codes back.  A thread's four 16-byte pieces of a row would each fill a
+// quarter of a line; mirror-image threads of two neighbouring slots trade pieces instead, so that eight lanes write
+// one whole 128-byte line per store instruction, and the stores are non-temporal (the output is written once).
+//
+// Bound by the HBM write stream (82 % of its bytes).  One record per workgroup with everything it reads requested at
+// once, eight workgroups to a compute unit, and an order of the workgroups that keeps the writes together (see the
+// launcher): 65 536 tokens x 8 heads 61.2 -> 53.7 us, per-channel keys 68.9 -> 54.2, against three looping workgroups
+// per compute unit that staged the next record in registers.
 //
 // Value: binary16 nearest-even of the exact code * scale + zero.  The fp16
 // fused multiply-add gives exactly that: code, scale and zero are fp16
@@ -30,34 +31,37 @@ using namespace tkv;
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
-// Two code bytes of w (BYTE and BYTE + 1) as a pair of fp16 numbers: the byte under the bit pattern 0x6400
-// is 1024 + code (the fp16 spacing there is 1), and subtracting 1024 is exact.
-template <int BYTE> __device__ __forceinline__ half2_t code_pair(uint32_t w)
+// A code under the bit pattern 0x6400 is the fp16 number 1024 + code (the fp16 spacing there is 1), and subtracting 1024
+// is exact: two codes in bits 0.. and 16.. of x, the rest of which is masked away, as a pair of fp16 numbers.
+template <int BITS> __device__ __forceinline__ half2_t code_pair(uint32_t x)
 {
-    // v_perm_b32 picks bytes from {w, 0x64646464}: selector bytes 4..7 address w, 0 the constant
-    constexpr uint32_t sel = (4u + BYTE) | (0u << 8) | ((5u + BYTE) << 16) | (0u << 24);
-    const uint32_t biased = __builtin_amdgcn_perm(w, 0x64646464u, sel);
+    constexpr uint32_t m = ((1u << BITS) - 1u) * 0x00010001u;
     const half2_t k = {(_Float16)1024.0f, (_Float16)1024.0f};
-    return __builtin_bit_cast(half2_t, biased) - k;
+    return __builtin_bit_cast(half2_t, (x & m) | 0x64006400u) - k;
 }
-// Eight codes (one per byte of lo, hi) times scale plus zero -> eight fp16 values.
-__device__ __forceinline__ uint4 dequant8(uint32_t lo, uint32_t hi, _Float16 s, _Float16 z)
+__device__ __forceinline__ uint32_t fma2(half2_t c, uint32_t s, uint32_t z)   // c * s + z, one rounding
 {
-    const half2_t sv = {s, s}, zv = {z, z};
-    return make_uint4(__builtin_bit_cast(uint32_t, __builtin_elementwise_fma(code_pair<0>(lo), sv, zv)),
-                      __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(code_pair<2>(lo), sv, zv)),
-                      __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(code_pair<0>(hi), sv, zv)),
-                      __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(code_pair<2>(hi), sv, zv)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(c, __builtin_bit_cast(half2_t, s), __builtin_bit_cast(half2_t, z)));
 }
-// The same with one (scale, zero) pair per code: s01 .. s67 and z01 .. z67 are fp16 pairs in code order.
-__device__ __forceinline__ uint4 dequant8_each(uint32_t lo, uint32_t hi, const uint32_t (&sp)[4], const uint32_t (&zp)[4])
+// Low halves of a and b, high halves of a and b.
+__device__ __forceinline__ uint32_t lows(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t highs(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+// Eight codes, 0..3 packed from bit 0 and 4..7 from bit 16 of x, to fp16 values.  s, z: the fp16 pairs (scale, zero) of
+// codes (k, k + 4), k = 0..3.
+template <int BITS> __device__ __forceinline__ uint4 dequant8(uint32_t x, const uint32_t (&s)[4], const uint32_t (&z)[4])
 {
-    auto f = [](half2_t c, uint32_t s, uint32_t z) {
-        return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(c, __builtin_bit_cast(half2_t, s), __builtin_bit_cast(half2_t, z)));
-    };
-    return make_uint4(f(code_pair<0>(lo), sp[0], zp[0]), f(code_pair<2>(lo), sp[1], zp[1]),
-                      f(code_pair<0>(hi), sp[2], zp[2]), f(code_pair<2>(hi), sp[3], zp[3]));
+    uint32_t v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = fma2(code_pair<BITS>(x >> (BITS * k)), s[k], z[k]);
+    return make_uint4(lows(v[0], v[1]), lows(v[2], v[3]), highs(v[0], v[1]), highs(v[2], v[3]));
 }
+template <int BITS> __device__ __forceinline__ uint4 dequant8(uint32_t x, uint32_t s, uint32_t z)   // the same pair for all
+{
+    const uint32_t sv[4] = {s, s, s, s}, zv[4] = {z, z, z, z};
+    return dequant8<BITS>(x, sv, zv);
+}
+// Half i & 1 of the 16-bit halves of v, twice.
+__device__ __forceinline__ uint32_t twice(uint32_t v, int i) { return __builtin_amdgcn_perm(v, v, (i & 1) ? 0x07060706u : 0x05040504u); }
 
 // Value of the lane that mirrors this one within its group of eight lanes (lane ^ 7).
 __device__ __forceinline__ uint32_t half_mirror(uint32_t v)
@@ -92,210 +96,142 @@ __device__ __forceinline__ void store_row(uint16_t *__restrict__ out, int dst, b
     }
 }
 
-// Eight consecutive sub-byte codes starting at bit `shift` of w -> one code per byte.
-template <int BITS> __device__ __forceinline__ void spread8(uint32_t w, int shift, uint32_t &lo, uint32_t &hi)
-{
-    constexpr uint32_t m = (1u << BITS) - 1u;
-    const uint32_t v = w >> shift;
-    lo = (v & m) | (((v >> BITS) & m) << 8) | (((v >> (2 * BITS)) & m) << 16) | (((v >> (3 * BITS)) & m) << 24);
-    hi = ((v >> (4 * BITS)) & m) | (((v >> (5 * BITS)) & m) << 8) | (((v >> (6 * BITS)) & m) << 16) |
-         (((v >> (7 * BITS)) & m) << 24);
-}
-
-// What one thread requests from HBM for one (page, kv head) record.  The requests of the next record are
-// issued before the current one is processed, so that a compute unit always has loads and stores in flight
-// (workgroups that start together would otherwise all read, then all compute, then all store).
-struct Stage {
-    uint4 kw;         // K codes of this thread's token: its 8 channels of each of the four groups
-    uint2 ksc, kzc;   // K scale / K zero of the token, four groups (per-token keys)
-    uint4 km;         // per-channel keys: 16 bytes of the K scale | K zero planes (threads 0..63)
-    uint4 vw;         // V words of four adjacent channels (threads 0..n_quads-1)
-    uint2 vm;         // 8 bytes of the V scale | V zero planes (threads 0..127)
-    int dst;          // output row of this thread's slot, or -1
-    int page;         // workgroup-uniform; -1 = page id outside the pool, nothing was requested
-    int bm;           // bit_map entry of the page
-};
-static_assert(sizeof(Stage) % 4 == 0, "plain dwords");
-
 // KC: the keys of an INT2 record are quantised per channel over blocks of 32 slots.
 template <int BITS, bool KC>
-__device__ __forceinline__ void load_planes(Stage &st, const uint8_t *__restrict__ rec)
+__device__ __forceinline__ void gather_k(const uint8_t *__restrict__ rec, uint16_t *__restrict__ K_out, int dst, bool valid, int head,
+                                         int n_kv_heads, uint4 *lds)
 {
     using R = Rec<BITS>;
     const int tid = threadIdx.x, slot = tid >> 2, part = tid & 3;
     const int tile = slot >> 4, row = slot & 15;
-    const uint4 *kc = reinterpret_cast<const uint4 *>(rec + R::kKCodes);
     // INT4: chunk (tile*4 + part)*16 + row = word `part` (8 channels) of the four groups
     // INT2: chunk (tile*2 + part/2)*16 + row = word part/2 (16 channels); this thread takes half part%2
     // read once, and an instruction of a wavefront covers 1 KiB (INT4) or 512 B (INT2) of whole lines
-    st.kw = load_once(kc + (BITS == 4 ? (tile * 4 + part) * 16 + row : (tile * 2 + (part >> 1)) * 16 + row));
-    if constexpr (KC) {
-        if (tid < 64) st.km = reinterpret_cast<const uint4 *>(rec + R::kKScale)[tid];   // 512 B scale, 512 B zero
+    const uint4 kw = load_once(reinterpret_cast<const uint4 *>(rec + R::kKCodes) +
+                               (BITS == 4 ? (tile * 4 + part) * 16 + row : (tile * 2 + (part >> 1)) * 16 + row));
+    const uint32_t w[4] = {kw.x, kw.y, kw.z, kw.w};
+    // INT4: nibbles 0..3 and 4..7 already lie in the two halves of the word.  INT2: the bytes of this thread's half move there.
+    auto spread = [&](uint32_t x) { return BITS == 4 ? x : __builtin_amdgcn_perm(x, x, (part & 1) ? 0x0c070c06u : 0x0c050c04u); };
+    uint4 kv[4];
+    if constexpr (!KC) {
+        const uint2 ksc = reinterpret_cast<const uint2 *>(rec + R::kKScale)[slot], kzc = reinterpret_cast<const uint2 *>(rec + R::kKZero)[slot];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) kv[i] = dequant8<BITS>(spread(w[i]), twice(i < 2 ? ksc.x : ksc.y, i), twice(i < 2 ? kzc.x : kzc.y, i));
     } else {
-        st.ksc = reinterpret_cast<const uint2 *>(rec + R::kKScale)[slot];
-        st.kzc = reinterpret_cast<const uint2 *>(rec + R::kKZero)[slot];
+        if (tid < 64) lds[tid] = reinterpret_cast<const uint4 *>(rec + R::kKScale)[tid];   // 512 B scale, 512 B zero
+        __syncthreads();
+        // channels 32*i + 8*part + j: chunks (block, group i, quarter 2*(part/2) + j/4) of the planes, fp16
+        // half part%2 of word j%4
+        const uint4 *sp4 = lds + (slot >> 5) * 16 + 2 * (part >> 1);
+        const uint4 *zp4 = sp4 + 32;
+        const uint32_t sel = (part & 1) ? 0x07060302u : 0x05040100u;   // v_perm: the chosen halves of (second, first)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint4 s0 = sp4[4 * i], s1 = sp4[4 * i + 1], z0 = zp4[4 * i], z1 = zp4[4 * i + 1];
+            const uint32_t sp[4] = {__builtin_amdgcn_perm(s1.x, s0.x, sel), __builtin_amdgcn_perm(s1.y, s0.y, sel),
+                                    __builtin_amdgcn_perm(s1.z, s0.z, sel), __builtin_amdgcn_perm(s1.w, s0.w, sel)};
+            const uint32_t zp[4] = {__builtin_amdgcn_perm(z1.x, z0.x, sel), __builtin_amdgcn_perm(z1.y, z0.y, sel),
+                                    __builtin_amdgcn_perm(z1.z, z0.z, sel), __builtin_amdgcn_perm(z1.w, z0.w, sel)};
+            kv[i] = dequant8<BITS>(spread(w[i]), sp, zp);
+        }
     }
-    if (tid < 128) st.vm = reinterpret_cast<const uint2 *>(rec + R::kVScale)[tid];   // 512 B scale, 512 B zero
+    store_row(K_out, dst, valid, kv, slot, part, head, n_kv_heads);
+}
+
+// V codes of the page, one per byte, in LDS: 144-byte rows, because the four quads that one instruction writes lie four
+// rows apart and must not meet on the same banks; then the V scale plane and the V zero plane as stored.
+constexpr int kCodeRow = 144;
+struct VLds {
+    alignas(16) uint8_t codes[kPageTokens * kCodeRow];
+    alignas(16) uint16_t meta[2 * kPageTokens * kGroups];
+};
+
+template <int BITS>
+__device__ __forceinline__ void gather_v(const uint8_t *__restrict__ rec, uint16_t *__restrict__ V_out, int dst, bool valid, int head,
+                                         int n_kv_heads, VLds &lds)
+{
+    using R = Rec<BITS>;
+    const int tid = threadIdx.x, slot = tid >> 2, part = tid & 3;
     constexpr int n_quads = R::kCodeBytes / 16;   // 256 (INT4) / 128 (INT2)
     if (tid < n_quads) {
+        // four words of four adjacent channels c0 .. c0 + 3, so that a token's four codes go out as one 32-bit write
         const uint32_t *vc = reinterpret_cast<const uint32_t *>(rec + R::kVCodes);
         const int jl = tid & 3, nq = (tid >> 2) & 3, quad = (tid >> 4) & 3, jh = (tid >> 6) & 1;
         const int blk = tid >> 7;   // INT4 only (0 for INT2)
         const int widx = jl + 16 * nq + 64 * quad + 256 * jh + 512 * blk;   // word of channel c0; c0 + k is 4*k words on
-        st.vw = make_uint4(vc[widx], vc[widx + 4], vc[widx + 8], vc[widx + 12]);
-    }
-}
-
-template <bool KC>
-__device__ __forceinline__ void load_stage(Stage &st, int r, const uint8_t *__restrict__ pool,
-                                           const uint8_t *__restrict__ bit_map, const int32_t *__restrict__ work_pages,
-                                           const int32_t *__restrict__ work_dst, int n_kv_heads, int n_pages_int2,
-                                           int n_pages_int4, int32_t *status)
-{
-    const int w = r / n_kv_heads, head = r % n_kv_heads;
-    const int page = work_pages[w];
-    if (page < 0 || page >= n_pages_int2 + n_pages_int4) {
-        if (status && threadIdx.x == 0) atomicOr(status, TKV_STATUS_PAGE_RANGE);
-        st = Stage{};
-        st.page = -1;
-        return;
-    }
-    st.page = page;
-    st.dst = work_dst[(size_t)w * kPageTokens + (threadIdx.x >> 2)];
-    st.bm = bit_map[page];
-    const uint8_t *rec = pool + record_offset(page, head, n_kv_heads, n_pages_int2);
-    if (page < n_pages_int2) load_planes<2, KC>(st, rec);
-    else load_planes<4, false>(st, rec);
-}
-
-struct GatherLds {
-    alignas(16) uint8_t codes[kPageTokens][kHeadDim];     // V codes, one per byte [token][channel]
-    alignas(16) uint16_t vmeta[2 * kPageTokens * kGroups];   // V scale plane, V zero plane, as stored
-    alignas(16) uint4 kmeta[64];                           // per-channel keys: K scale plane, K zero plane
-};
-
-template <int BITS, bool KC>
-__device__ __forceinline__ void gather_record(const Stage &st, uint16_t *__restrict__ K_out, uint16_t *__restrict__ V_out,
-                                              bool valid, int head, int n_kv_heads, GatherLds &lds)
-{
-    using R = Rec<BITS>;
-    const int tid = threadIdx.x, slot = tid >> 2, part = tid & 3;
-
-    // ---- V planes -> LDS: scale and zero as stored, codes one per byte [token][channel]
-    if (tid < 128) reinterpret_cast<uint2 *>(lds.vmeta)[tid] = st.vm;
-    if constexpr (KC) {
-        if (tid < 64) lds.kmeta[tid] = st.km;
-    }
-    // four words of four adjacent channels at a time, so that a token's four codes go out as one 32-bit write
-    constexpr int n_quads = R::kCodeBytes / 16;
-    if (tid < n_quads) {
-        const int jl = tid & 3, nq = (tid >> 2) & 3, quad = (tid >> 4) & 3, jh = (tid >> 6) & 1;
-        const int blk = tid >> 7;
         const int c0 = (jh * 4 + jl) * 16 + 4 * nq;
-        const uint32_t w0 = st.vw.x, w1 = st.vw.y, w2 = st.vw.z, w3 = st.vw.w;
-        constexpr uint32_t m = (1u << BITS) - 1u;
+        const uint32_t w[4] = {vc[widx], vc[widx + 4], vc[widx + 8], vc[widx + 12]};
+        // byte b of a word holds 8 / BITS positions; position e of every byte, then the 4 x 4 bytes transposed
 #pragma unroll
-        for (int p = 0; p < 32 / BITS; ++p) {
-            int t;
-            if (BITS == 4) {
-                const int j = 2 * (p & 3) + (p >> 2);
-                t = 32 * blk + 16 * (j >> 2) + 4 * quad + (j & 3);
-            } else {
-                const int j = 2 * (p & 3) + (p >> 3);
-                t = 32 * ((p & 7) >> 2) + 16 * (j >> 2) + 4 * quad + (j & 3);
+        for (int e = 0; e < 8 / BITS; ++e) {
+            constexpr uint32_t m = ((1u << BITS) - 1u) * 0x01010101u;
+            uint32_t x[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[k] = (w[k] >> (BITS * e)) & m;
+            const uint32_t t01 = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), u01 = __builtin_amdgcn_perm(x[1], x[0], 0x07030602u);
+            const uint32_t t23 = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u), u23 = __builtin_amdgcn_perm(x[3], x[2], 0x07030602u);
+            const uint32_t four[4] = {lows(t01, t23), highs(t01, t23), lows(u01, u23), highs(u01, u23)};
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int p = (8 / BITS) * b + e;   // position of the token in the word
+                const int j = BITS == 4 ? 2 * (p & 3) + (p >> 2) : 2 * (p & 3) + (p >> 3);
+                const int t = 32 * (BITS == 4 ? blk : (p & 7) >> 2) + 16 * (j >> 2) + 4 * quad + (j & 3);
+                *reinterpret_cast<uint32_t *>(&lds.codes[t * kCodeRow + c0]) = four[b];
             }
-            const uint32_t four = ((w0 >> (BITS * p)) & m) | (((w1 >> (BITS * p)) & m) << 8) |
-                                  (((w2 >> (BITS * p)) & m) << 16) | (((w3 >> (BITS * p)) & m) << 24);
-            *reinterpret_cast<uint32_t *>(&lds.codes[t][c0]) = four;
         }
     }
-
-    // ---- K: this thread's 8 channels of each group (per-token keys need nothing from LDS)
-    const uint32_t w[4] = {st.kw.x, st.kw.y, st.kw.z, st.kw.w};
-    if constexpr (!KC) {
-        uint4 kv[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t sc = i < 2 ? st.ksc.x : st.ksc.y, zc = i < 2 ? st.kzc.x : st.kzc.y;
-            const _Float16 s = __builtin_bit_cast(_Float16, (uint16_t)(sc >> (16 * (i & 1))));
-            const _Float16 z = __builtin_bit_cast(_Float16, (uint16_t)(zc >> (16 * (i & 1))));
-            uint32_t lo, hi;
-            spread8<BITS>(w[i], BITS == 4 ? 0 : 16 * (part & 1), lo, hi);
-            kv[i] = dequant8(lo, hi, s, z);
-        }
-        store_row(K_out, st.dst, valid, kv, slot, part, head, n_kv_heads);
-    }
+    if (tid < 128) reinterpret_cast<uint2 *>(lds.meta)[tid] = reinterpret_cast<const uint2 *>(rec + R::kVScale)[tid];   // 512 B scale, 512 B zero
     __syncthreads();
-    if constexpr (KC) {
-        {
-            uint4 kv[4];
-            // channels 32*i + 8*part + j: chunks (block, group i, quarter 2*(part/2) + j/4) of the planes, fp16
-            // half part%2 of word j%4
-            const uint4 *sp4 = lds.kmeta + (slot >> 5) * 16 + 2 * (part >> 1);
-            const uint4 *zp4 = sp4 + 32;
-            const uint32_t sel = (part & 1) ? 0x07060302u : 0x05040100u;   // v_perm: the chosen halves of (second, first)
+    uint4 vv[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint4 s0 = sp4[4 * i], s1 = sp4[4 * i + 1], z0 = zp4[4 * i], z1 = zp4[4 * i + 1];
-                const uint32_t sp[4] = {__builtin_amdgcn_perm(s0.y, s0.x, sel), __builtin_amdgcn_perm(s0.w, s0.z, sel),
-                                        __builtin_amdgcn_perm(s1.y, s1.x, sel), __builtin_amdgcn_perm(s1.w, s1.z, sel)};
-                const uint32_t zp[4] = {__builtin_amdgcn_perm(z0.y, z0.x, sel), __builtin_amdgcn_perm(z0.w, z0.z, sel),
-                                        __builtin_amdgcn_perm(z1.y, z1.x, sel), __builtin_amdgcn_perm(z1.w, z1.z, sel)};
-                uint32_t lo, hi;
-                spread8<BITS>(w[i], 16 * (part & 1), lo, hi);
-                kv[i] = dequant8_each(lo, hi, sp, zp);
-            }
-            store_row(K_out, st.dst, valid, kv, slot, part, head, n_kv_heads);
-        }
-    }
-    // ---- V: codes from the byte tile, scale / zero from the staged planes
-    {
-        uint4 vv[4];
+    for (int i = 0; i < 4; ++i) {
+        const int mi = vmeta_index(slot, i);
+        const uint2 cb = *reinterpret_cast<const uint2 *>(&lds.codes[slot * kCodeRow + 32 * i + 8 * part]);
+        // codes 0..3 and 4..7 one per byte; code_pair wants (k, k + 4) in the halves of a word
+        const uint32_t s = lds.meta[mi] * 0x00010001u, z = lds.meta[kPageTokens * kGroups + mi] * 0x00010001u;
+        uint32_t v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int mi = vmeta_index(slot, i);
-            const _Float16 s = __builtin_bit_cast(_Float16, lds.vmeta[mi]);
-            const _Float16 z = __builtin_bit_cast(_Float16, lds.vmeta[kPageTokens * kGroups + mi]);
-            const uint2 cb = *reinterpret_cast<const uint2 *>(&lds.codes[slot][32 * i + 8 * part]);
-            vv[i] = dequant8(cb.x, cb.y, s, z);
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t sel = 0x0c000c04u + k * 0x00010001u;   // byte k of lo, zero, byte k of hi, zero
+            v[k] = fma2(code_pair<BITS>(__builtin_amdgcn_perm(cb.x, cb.y, sel)), s, z);
         }
-        store_row(V_out, st.dst, valid, vv, slot, part, head, n_kv_heads);
+        vv[i] = make_uint4(lows(v[0], v[1]), lows(v[2], v[3]), highs(v[0], v[1]), highs(v[2], v[3]));
     }
+    store_row(V_out, dst, valid, vv, slot, part, head, n_kv_heads);
 }
 
-// Workgroup b handles records b, b + gridDim.x, ... (record = work page * n_kv_heads + head).  The LDS tile is
-// double-buffered: one barrier per record (a thread can be at most one record ahead of the slowest).
 template <bool KC>
 __global__ __launch_bounds__(256) void tkv_gather_kernel(
     const uint8_t *__restrict__ pool, const uint8_t *__restrict__ bit_map, const int32_t *__restrict__ work_pages,
-    const int32_t *__restrict__ work_dst, int n_records, int n_kv_heads, int n_pages_int2, int n_pages_int4,
+    const int32_t *__restrict__ work_dst, int n_work, int first_head, int n_kv_heads, int n_pages_int2, int n_pages_int4,
     uint16_t *__restrict__ K_out, uint16_t *__restrict__ V_out, int n_tokens, int32_t *status)
 {
-    __shared__ GatherLds lds[2];
-    int r = blockIdx.x;
-    if (r >= n_records) return;
-    Stage cur{}, nxt{};
-    load_stage<KC>(cur, r, pool, bit_map, work_pages, work_dst, n_kv_heads, n_pages_int2, n_pages_int4, status);
-    nxt = cur;
-    int buf = 0;
-    for (; r < n_records; r += gridDim.x) {
-        const int rn = r + gridDim.x;
-        if (rn < n_records)
-            load_stage<KC>(nxt, rn, pool, bit_map, work_pages, work_dst, n_kv_heads, n_pages_int2, n_pages_int4, status);
-        if (cur.page >= 0) {
-            const int bits = cur.page < n_pages_int2 ? 2 : 4;
-            // a page that was never written, or written at another width, has been read (its address is valid)
-            // and nothing of it is stored
-            const bool written = cur.bm == bits;
-            if (!written && status && threadIdx.x == 0) atomicOr(status, TKV_STATUS_BITMAP_MISMATCH);
-            const bool valid = written && cur.dst >= 0 && cur.dst < n_tokens;
-            if (written && cur.dst >= n_tokens && status && (threadIdx.x & 3) == 0) atomicOr(status, TKV_STATUS_DST_RANGE);
-            const int head = r % n_kv_heads;
-            if (bits == 2) gather_record<2, KC>(cur, K_out, V_out, valid, head, n_kv_heads, lds[buf]);
-            else gather_record<4, false>(cur, K_out, V_out, valid, head, n_kv_heads, lds[buf]);
-            buf ^= 1;
-        }
-        cur = nxt;
+    __shared__ VLds lds;
+    // grid (8, heads, 2 * blocks of eight pages): see the launcher
+    const int n_blocks = gridDim.z >> 1;
+    const bool is_v = blockIdx.z >= n_blocks;
+    const int w = (blockIdx.z - (is_v ? n_blocks : 0)) * 8 + blockIdx.x, head = first_head + blockIdx.y;
+    if (w >= n_work) return;
+    const int page = work_pages[w];
+    const int dst = work_dst[(size_t)w * kPageTokens + (threadIdx.x >> 2)];
+    if (page < 0 || page >= n_pages_int2 + n_pages_int4) {
+        if (status && threadIdx.x == 0) atomicOr(status, TKV_STATUS_PAGE_RANGE);
+        return;
+    }
+    const int bits = page < n_pages_int2 ? 2 : 4;
+    const uint8_t *rec = pool + record_offset(page, head, n_kv_heads, n_pages_int2);
+    // a page that was never written, or written at another width, is read (its address is valid) and nothing of it
+    // is stored
+    const bool written = bit_map[page] == bits;
+    if (!written && status && threadIdx.x == 0) atomicOr(status, TKV_STATUS_BITMAP_MISMATCH);
+    const bool valid = written && dst >= 0 && dst < n_tokens;
+    if (written && dst >= n_tokens && status && (threadIdx.x & 3) == 0) atomicOr(status, TKV_STATUS_DST_RANGE);
+    if (is_v) {
+        if (bits == 2) gather_v<2>(rec, V_out, dst, valid, head, n_kv_heads, lds);
+        else gather_v<4>(rec, V_out, dst, valid, head, n_kv_heads, lds);
+    } else {
+        if (bits == 2) gather_k<2, KC>(rec, K_out, dst, valid, head, n_kv_heads, reinterpret_cast<uint4 *>(&lds));
+        else gather_k<4, false>(rec, K_out, dst, valid, head, n_kv_heads, reinterpret_cast<uint4 *>(&lds));
     }
 }
 
@@ -305,23 +241,22 @@ int tkv_launch_gather(const tkv_desc *desc, const void *pool, const uint8_t *bit
                       const int32_t *work_dst, int32_t n_work, void *K_out, void *V_out, int32_t n_tokens,
                       int32_t *status, void *stream)
 {
-    // A few looping workgroups per compute unit, fewer than would fit: the kernel is bound by the HBM write
-    // stream (82 % of its bytes are stores), and on MI355X that stream runs faster with few concurrent
-    // writers (cfg2, per-token keys: 271 / 243 / 243 / 249 us with 2 / 3 / 4 / 6 workgroups per unit).
     const bool kc = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL;
     auto kernel = kc ? tkv_gather_kernel<true> : tkv_gather_kernel<false>;
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0 ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu <= 0)
-        return TKV_ERR_HIP;
-    const int wanted = 3;
-    per_cu = per_cu < wanted ? per_cu : wanted;
-    const int n_records = n_work * desc->n_kv_heads;
-    const int n_blocks = n_records < cus * per_cu ? n_records : cus * per_cu;
-    const dim3 grid((unsigned)n_blocks), block(256);
-    hipLaunchKernelGGL(kernel, grid, block, 0, (hipStream_t)stream, (const uint8_t *)pool, bit_map,
-                       work_pages, work_dst, n_records, desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4,
-                       (uint16_t *)K_out, (uint16_t *)V_out, n_tokens, status);
+    // Which workgroup does what, and when: workgroups are dealt to the eight XCDs in turn, so the first grid dimension is
+    // the XCD: it writes the rows of all heads of a page one behind the other (2 KiB per token at eight heads), and
+    // all K rows are written before the V rows.  65 536 tokens x 8 heads: 53.7 us (6.1 TB/s; a plain 1 : 4 stream reaches
+    // 6.2) against 61.2 with K and V of a record side by side, 54.5 with the heads of a page spread over the XCDs and
+    // 69.9 with both: two write streams at a time cost more than anything else here.
+    constexpr int kMaxPages = 8 * (65535 / 2), kMaxHeads = 65535;   // of one launch, by the limits of the grid
+    for (int page = 0; page < n_work; page += kMaxPages)
+        for (int head = 0; head < desc->n_kv_heads; head += kMaxHeads) {
+            const int n = n_work - page < kMaxPages ? n_work - page : kMaxPages;
+            const int h = desc->n_kv_heads - head < kMaxHeads ? desc->n_kv_heads - head : kMaxHeads;
+            hipLaunchKernelGGL(kernel, dim3(8, (unsigned)h, 2 * (unsigned)((n + 7) / 8)), dim3(256), 0, (hipStream_t)stream,
+                               (const uint8_t *)pool, bit_map, work_pages + page, work_dst + (size_t)page * kPageTokens, n, head,
+                               desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4, (uint16_t *)K_out, (uint16_t *)V_out, n_tokens,
+                               status);
+        }
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
