@@ -297,12 +297,12 @@ template <bool KC>
 __global__ __launch_bounds__(256) void tkv_append_kernel(
     uint8_t *__restrict__ pool, uint8_t *__restrict__ bit_map, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const uint8_t *__restrict__ tag_bits, int n_tokens,
-    const int32_t *__restrict__ work_pages, const int32_t *__restrict__ work_src, int n_work, int n_kv_heads,
+    const int32_t *__restrict__ work_pages, const int32_t *__restrict__ work_src, int n_work, int first_head, int n_kv_heads,
     int n_pages_int2, int n_pages_int4, int32_t *status)
 {
     __shared__ uint4 rows[kPageTokens * kRowPieces];
-    const int w = blockIdx.y + blockIdx.z * gridDim.y, head = blockIdx.x >> 1;
-    const bool is_v = blockIdx.x & 1;
+    const int w = blockIdx.z * 8 + blockIdx.x, head = first_head + (blockIdx.y >> 1);   // grid (8, 2 * heads, blocks of eight pages): see the launcher
+    const bool is_v = blockIdx.y & 1;
     if (w >= n_work) return;
     // All arguments at once: a launch of a few tokens is a chain of dependent loads, and each argument fetched where it
     // is first used would be one more.
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(256) void tkv_append_kernel(
         if (bits == 2) append_k<2, KC>(rec, mask, rows);
         else append_k<4, false>(rec, mask, rows);
     }
-    if (blockIdx.x == 0 && tid == 0 && mask != 0) bit_map[page] = (uint8_t)bits;
+    if (head == 0 && !is_v && tid == 0 && mask != 0) bit_map[page] = (uint8_t)bits;
 }
 
 } // namespace
@@ -373,12 +373,20 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
                       const uint8_t *tag_bits, int32_t n_tokens, const int32_t *work_pages,
                       const int32_t *work_src, int32_t n_work, int32_t *status, void *stream)
 {
-    constexpr int kMaxY = 65535;
-    const dim3 grid((unsigned)desc->n_kv_heads * 2, (unsigned)(n_work < kMaxY ? n_work : kMaxY), (unsigned)((n_work + kMaxY - 1) / kMaxY));
     const bool kc = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL;
     auto kernel = kc ? tkv_append_kernel<true> : tkv_append_kernel<false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, (hipStream_t)stream, (uint8_t *)pool, bit_map,
-                       (const uint16_t *)K, (const uint16_t *)V, tag_bits, n_tokens, work_pages, work_src, n_work,
-                       desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4, status);
+    // Workgroups are dealt to the eight XCDs in turn: the first grid dimension is the XCD, which reads the rows of all heads
+    // of a page one behind the other (2 KiB per token at eight heads).  65 536 tokens x 8 heads: 57.5 us against 59.2
+    // with the heads of a page spread over the XCDs; K before V, as the gather does it, makes no difference here.
+    constexpr int kMaxPages = 8 * 65535, kMaxHeads = 65535 / 2;   // of one launch, by the limits of the grid
+    for (int page = 0; page < n_work; page += kMaxPages)
+        for (int head = 0; head < desc->n_kv_heads; head += kMaxHeads) {
+            const int n = n_work - page < kMaxPages ? n_work - page : kMaxPages;
+            const int h = desc->n_kv_heads - head < kMaxHeads ? desc->n_kv_heads - head : kMaxHeads;
+            hipLaunchKernelGGL(kernel, dim3(8, 2 * (unsigned)h, (unsigned)((n + 7) / 8)), dim3(256), 0, (hipStream_t)stream,
+                               (uint8_t *)pool, bit_map, (const uint16_t *)K, (const uint16_t *)V, tag_bits, n_tokens, work_pages + page,
+                               work_src + (size_t)page * kPageTokens, n, head, desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4,
+                               status);
+        }
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
