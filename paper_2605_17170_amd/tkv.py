@@ -154,18 +154,29 @@ def _np(a, dtype):
 
 
 def _dev(t):
-    """Device pointer of a torch tensor (None -> NULL)."""
+    """Device pointer of a torch tensor (None -> NULL), as the plain value that the argument types convert."""
     if t is None:
-        return C.c_void_p(None)
+        return None
     assert t.is_contiguous(), "device arguments must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_torch = None
 
 
 def _stream(stream):
+    """The stream handle; None: torch's current stream.  torch.cuda.current_stream() builds a Stream object for every
+    call, 2.7 us of the 5.4 us that marshalling a gather took; the handle alone is 0.3 us."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(getattr(stream, "cuda_stream", stream))
+        global _torch
+        if _torch is None:
+            import torch
+            _torch = torch
+        raw = getattr(_torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(_torch.cuda.current_device())
+        stream = _torch.cuda.current_stream()
+    return getattr(stream, "cuda_stream", stream)
 
 
 class Prepared:
