@@ -354,32 +354,62 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
         else lo = mid + 1;
     }
     const int64_t per_item = lo;   // with more non-empty sequences than target_items: one item each
+    // Where part k of n of a sequence of p2 + p4 pages ends that begins at page `begin`: parts of equal cost, rounded
+    // down to whole pages, at least a page each and a page left for every later part.
+    auto part_end = [&](int64_t p2, int64_t p4, int64_t n, int64_t k, int64_t begin) {
+        const int64_t pages = p2 + p4, goal = (kCost2 * p2 + kCost4 * p4) * (k + 1) / n;
+        int64_t end = goal < kCost2 * p2 ? goal / kCost2 : p2 + (goal - kCost2 * p2) / kCost4;
+        end = std::min(std::max(end, begin + 1), pages - (n - 1 - k));
+        return k == n - 1 ? pages : end;
+    };
+    auto cost_of = [&](int64_t p2, int64_t begin, int64_t end) {
+        const int64_t a2 = std::max<int64_t>(0, std::min(end, p2) - begin);
+        return kCost2 * a2 + kCost4 * (end - begin - a2);
+    };
+    auto heaviest_part = [&](int64_t p2, int64_t p4, int64_t n) {
+        int64_t most = 0, begin = 0;
+        for (int64_t k = 0; k < n; ++k) {
+            const int64_t end = part_end(p2, p4, n, k, begin);
+            most = std::max(most, cost_of(p2, begin, end));
+            begin = end;
+        }
+        return most;
+    };
+    std::vector<int32_t> n_parts(batch, 0);
+    int64_t heaviest = 0;
+    for (int32_t b = 0; b < batch; ++b) {
+        const int64_t p2 = ceil_div(n_tok_int2[b], kPageTokens), p4 = ceil_div(n_tok_int4[b], kPageTokens);
+        if (p2 + p4 == 0) continue;
+        n_parts[b] = (int32_t)std::min<int64_t>(p2 + p4, (kCost2 * p2 + kCost4 * p4 + per_item - 1) / per_item);
+        heaviest = std::max(heaviest, heaviest_part(p2, p4, n_parts[b]));
+    }
+    // Parts of equal cost, rounded to whole pages, are a mixture of k and k + 1 pages, and every item pays for the
+    // preparation of q and for its partial, which weigh as much as a page.  The launch takes as long as its longest
+    // items: with few pages per item every item gets as many as those have, and there are up to half as many.
+    // Measured (us per call, equal parts -> full items, at a mean of x pages per equal part): 8 kv heads x = 1.03
+    // 18.2 -> 15.3, 1.6 19.3 -> 18.3, 2.2 23.3 -> 22.1, 3.2 24.8 -> 23.8, 5.1 30.0 -> 30.1, 10.1 49.3 -> 48.4; one head 1.1
+    // 16.8 -> 14.6, 2.05 20.1 -> 18.0, 8.1 37.7 -> 38.2, 11.5 47.7 -> 47.2.  At 43 pages the sum of the items on a SIMD
+    // decides, and items that are full leave some with two of them: 170.0 -> 172.6.  Single pages cannot be cut differently.
+    // (More items than the device's 256 x 12 wavefronts hold at once were asked for as such: equal parts.)
+    constexpr int64_t kResident = 256 * 12;
+    const bool full = heaviest > kCost4 && heaviest <= 16 * kCost4 && (int64_t)target_items * desc->n_kv_heads <= kResident;
+    const int64_t most = (heaviest + kCost4 - 1) / kCost4 * kCost4;
     int32_t n_items = 0;
     seq_item_indptr_out[0] = 0;
     for (int32_t b = 0; b < batch; ++b) {
-        const int32_t p2 = ceil_div(n_tok_int2[b], kPageTokens), p4 = ceil_div(n_tok_int4[b], kPageTokens);
-        const int32_t pages = p2 + p4;
-        const int64_t cost = kCost2 * p2 + kCost4 * p4;
-        if (pages > 0) {
-            const int32_t n_split = (int32_t)std::min<int64_t>(pages, (cost + per_item - 1) / per_item);
-            if (n_items + n_split > capacity) return TKV_ERR_CAPACITY;
-            int32_t begin = 0;
-            int64_t cum = 0;   // cost of pages [0, begin)
-            for (int32_t k = 0; k < n_split; ++k) {
-                const int64_t goal = cost * (k + 1) / n_split;
-                int32_t end = begin;
-                while (end < pages && (end == begin || cum + (end < p2 ? kCost2 : kCost4) <= goal)) {
-                    cum += end < p2 ? kCost2 : kCost4;
-                    ++end;
-                }
-                end = std::min(end, pages - (n_split - 1 - k));   // leave a page for every later item
-                if (k == n_split - 1) end = pages;
-                // recompute cum if the clamp moved `end` backwards
-                cum = kCost2 * std::min(end, p2) + kCost4 * std::max(0, end - p2);
-                int32_t *it = items_out + 4 * (size_t)n_items;
-                it[0] = b; it[1] = begin; it[2] = end; it[3] = n_items++;   // partial slot = place in sequence order
-                begin = end;
+        const int64_t p2 = ceil_div(n_tok_int2[b], kPageTokens), p4 = ceil_div(n_tok_int4[b], kPageTokens);
+        int64_t begin = 0;
+        for (int64_t k = 0; full ? begin < p2 + p4 : k < n_parts[b]; ++k) {
+            int64_t end;
+            if (full) {
+                for (end = begin + 1; end < p2 + p4 && cost_of(p2, begin, end + 1) <= most; ) ++end;
+            } else {
+                end = part_end(p2, p4, n_parts[b], k, begin);
             }
+            if (n_items >= capacity) return TKV_ERR_CAPACITY;
+            int32_t *it = items_out + 4 * (size_t)n_items;
+            it[0] = b; it[1] = (int32_t)begin; it[2] = (int32_t)end; it[3] = n_items++;   // partial slot = place in sequence order
+            begin = end;
         }
         seq_item_indptr_out[b + 1] = n_items;
     }
