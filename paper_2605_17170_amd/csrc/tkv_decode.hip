@@ -127,27 +127,23 @@ __device__ __forceinline__ uint32_t ror8_u32(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128 /* row_ror:8 */, 0xf, 0xf, true);
 }
 // The value of another lane of the same row of 16 lanes: CTRL is a DPP pattern under which every lane has a source.
-template <int CTRL> __device__ __forceinline__ float row_dpp(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
+template <int CTRL> __device__ __forceinline__ int row_dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
 // Maximum over a row of 16 lanes, in every lane of the row: neighbours, pairs, quads, halves
 // (quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror).
-__device__ __forceinline__ float row_max(float v)
+__device__ __forceinline__ int row_max(int v)
 {
-    v = fmaxf(v, row_dpp<0xB1>(v));
-    v = fmaxf(v, row_dpp<0x4E>(v));
-    v = fmaxf(v, row_dpp<0x141>(v));
-    v = fmaxf(v, row_dpp<0x140>(v));
-    return v;
+    v = max(v, row_dpp<0xB1>(v));
+    v = max(v, row_dpp<0x4E>(v));
+    v = max(v, row_dpp<0x141>(v));
+    return max(v, row_dpp<0x140>(v));
 }
-__device__ __forceinline__ float wave_max(float v)
+__device__ __forceinline__ int wave_max(int v)
 {
     v = row_max(v);
-    const int b = __builtin_bit_cast(int, v);
-    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 0)), r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 16));
-    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32)), r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48));
-    return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
+    const int r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
+    const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
+    const int a = r0 > r1 ? r0 : r1, b = r2 > r3 ? r2 : r3;
+    return a > b ? a : b;
 }
 // Orders this wavefront's LDS writes before its later LDS reads.  The workgroup is one wavefront
 // and LDS operations of a wavefront execute in order, so no wait and no barrier instruction is needed.
@@ -703,7 +699,10 @@ __device__ __forceinline__ void batch_check(const ItemCtx &cx, PageBatch &pb, in
     pb.nv = ok ? (pi == cx.np2 - 1 ? cx.last2 : pi == cx.np2 + cx.np4 - 1 ? cx.last4 : kPageTokens) : 0;
     // (lanes beyond the item repeat its last page, whose width need not be theirs; they are never used)
     const int at = ok ? page : (lo < cx.n_pages_total ? lo : 0);
-    pb.at = (uint32_t)(record_offset(at, cx.kvh, cx.n_kv_heads, cx.n_pages_int2) >> kRecordUnitLog2);
+    // (pools below 8 TB: 32 bits)
+    const uint32_t rec = (uint32_t)(at < cx.n_pages_int2 ? at : at - cx.n_pages_int2) * (uint32_t)cx.n_kv_heads + (uint32_t)cx.kvh;
+    constexpr uint32_t kUnits2 = Rec<2>::kBytes >> kRecordUnitLog2, kUnits4 = Rec<4>::kBytes >> kRecordUnitLog2;
+    pb.at = at < cx.n_pages_int2 ? rec * kUnits2 : (uint32_t)cx.n_pages_int2 * (uint32_t)cx.n_kv_heads * kUnits2 + rec * kUnits4;
     pb.bm = cx.bit_map[at];
 }
 // A page that was never written, or written at the other width, counts no tokens.
@@ -871,22 +870,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     for (int h = 0; h < 8; ++h)   // (heads beyond R: head 0 again, not used)
         q2[h] = reinterpret_cast<const uint32_t *>(q + ((size_t)seq * n_q_heads + kvh * R + (h < R ? h : 0)) * kHeadDim)[lane];
     batch_check(cx, list, batch_ids(cx, list, pb));
-    float qv[8][2];
-    float amax = 0.0f;
+    // (The preparation of q is what a launch of one to three pages per wavefront consists of: no branches that depend on the
+    // lane, no 64-bit arithmetic.  16 contexts of 97 to 6011 tokens 15.4 -> 15.25 us, per-channel keys at 8 x 32768, which
+    // had the most registers to spill, 54.7 -> 53.0.)
+    // Largest exponent of the heads, from the bf16 bits: |x| as an integer, plus one in the exponent, which makes NaN and
+    // infinities negative: they do not count (a head that holds one must not spoil the others)
+    typedef short short2_t __attribute__((ext_vector_type(2)));
+    short2_t big = {0, 0};
 #pragma unroll
     for (int h = 0; h < 8; ++h) {
-        const uint32_t two = h < R ? q2[h] : 0;
-        qv[h][0] = __uint_as_float(two << 16);
-        qv[h][1] = __uint_as_float(two & 0xffff0000u);
-        amax = fmaxf(amax, fmaxf(fabsf(qv[h][0]), fabsf(qv[h][1])));
+        q2[h] = h < R ? q2[h] : 0;
+        big = __builtin_elementwise_max(big, __builtin_bit_cast(short2_t, ((q2[h] & 0x7fff7fffu) + 0x00800080u)));
     }
-    amax = wave_max(amax);
+    const int top = wave_max(big[0] > big[1] ? big[0] : big[1]);   // 0x80 where all are zero
     // 2^E with max|q| * 2^E in [2^14, 2^15); E clamped so every factor stays a normal fp32
-    int ex = 0;
-    if (amax > 0.0f) { (void)frexpf(amax, &ex); }   // amax = m * 2^ex, m in [0.5, 1)
-    int E = (KC ? kKcQExp : 15) - ex;
+    int E = (KC ? kKcQExp : 15) - ((top >> 7) - 127);   // max|q| = m * 2^(exponent - 126), m in [0.5, 1)
     E = E > 100 ? 100 : (E < -100 ? -100 : E);
-    if (!(amax > 0.0f)) E = 0;
+    if (top <= 0x80) E = 0;
     const float two_e = ldexpf(1.0f, E);
     LaneConst lc;
     lc.F = ldexpf(1.0f, 24 - E);
@@ -898,7 +898,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     lc.vrot[0] = lc.vrot[1] = 0;
     lc.vmask[0] = lc.vmask[1] = lc.vmask[2] = lc.vmask[3] = 0;
     lc.tok0 = 16 * (r16 >> 3) + 4 * q4;
-    lc.qy_ent = (r16 >> 3) == (q4 >> 1) ? (q4 & 1) * 8 + (r16 & 7) : ((q4 & 1) ? kQyZero1 : kQyZero0);
+    static_assert(kQyZero0 == 24 && kQyZero1 == 16, "entry 24 - 8 * sub holds the zeros of the lanes of octet sub");
+    const int other_set = -(int)((r16 >> 3) != (q4 >> 1));
+    lc.qy_ent = (((q4 & 1) * 8 + (r16 & 7)) & ~other_set) | ((kQyZero0 - 8 * (q4 & 1)) & other_set);
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
         lc.zp_idx[blk] = r16 < 4 ? kPvZ + (blk * 4 + q4) * 4 + r16 : (r16 == 4 ? kPvOne : kPvZero);
@@ -909,21 +911,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     }
     // q * 2^E to LDS
 #pragma unroll
-    for (int h = 0; h < 8; ++h) qf_store<KC>(qf, h, lane, pack_h2(qv[h][0] * two_e, qv[h][1] * two_e));   // exact: q has 8 significant bits
+    for (int h = 0; h < 8; ++h)   // exact: q has 8 significant bits
+        qf_store<KC>(qf, h, lane, pack_h2(__uint_as_float(q2[h] << 16) * two_e, __uint_as_float(q2[h] & 0xffff0000u) * two_e));
     lds_order();
     {
-        // sums of q over the groups, one MFMA per group: row = head, the 32 channels of the group against a column of ones
-        floatx4 gsum = {0.f, 0.f, 0.f, 0.f};
+        // sums of q over the groups, one MFMA per group: row = head, the 32 channels of the group against ones
+        constexpr uint32_t kOne = 0x3c003c00u;
+        floatx4 gsum[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const uint4 a = *reinterpret_cast<const uint4 *>(static_cast<const char *>(qf) + qf_chunk<KC>(r16 & 7, g * 4 + q4));
-            const uint32_t one = r16 == g ? 0x3c003c00u : 0u;
-            gsum = mfma(as_half8(a.x, a.y, a.z, a.w), as_half8(one, one, one, one), gsum);
+            gsum[g] = mfma(as_half8(a.x, a.y, a.z, a.w), as_half8(kOne, kOne, kOne, kOne), floatx4{0.f, 0.f, 0.f, 0.f});
         }
         const float undo = ldexpf(1.0f, -E);
-        if (q4 < 2 && r16 < 4)
+        if (q4 < 2 && r16 == 0)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) lds.zl()[4 * q4 + i][r16] = gsum[i] * undo;   // [head][group]
+            for (int i = 0; i < 4; ++i)   // [head][group]
+                *reinterpret_cast<float4 *>(lds.zl()[4 * q4 + i]) = make_float4(gsum[0][i] * undo, gsum[1][i] * undo, gsum[2][i] * undo, gsum[3][i] * undo);
     }
     lds_order();
     const int hcol = (r16 & 7) & (R - 1);   // head of this lane's column (columns beyond R repeat heads)
@@ -934,18 +938,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
         // octet = lo pieces
         const float4 gs = reinterpret_cast<const float4 *>(lds.zl()[hcol])[0];
         const float sums[4] = {gs.x, gs.y, gs.z, gs.w};
-        float pc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        const bool own = (r16 >> 3) == (q4 >> 1);
+        _Float16 hi[4], mid[4], lo[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const _Float16 hi = (_Float16)sums[g];
-            const float r1 = sums[g] - (float)hi;
-            const _Float16 mid = (_Float16)r1;
-            const _Float16 lo = (_Float16)(r1 - (float)mid);
-            if (own && (q4 & 1) == 0) { pc[g] = (float)hi; pc[4 + g] = (float)mid; }
-            else if (own) { pc[g] = (float)lo; }
+            hi[g] = (_Float16)sums[g];
+            const float r1 = sums[g] - (float)hi[g];
+            mid[g] = (_Float16)r1;
+            lo[g] = (_Float16)(r1 - (float)mid[g]);
         }
-        qz = as_half8(pack_h2(pc[0], pc[1]), pack_h2(pc[2], pc[3]), pack_h2(pc[4], pc[5]), pack_h2(pc[6], pc[7]));
+        auto pair = [](_Float16 a, _Float16 b) { const half2_t v = {a, b}; return __builtin_bit_cast(uint32_t, v); };
+        const uint32_t own = (r16 >> 3) == (q4 >> 1) ? 0xffffffffu : 0u;                    // masks and no branches
+        const uint32_t first = (q4 & 1) ? 0u : own, second = (q4 & 1) ? own : 0u;
+        qz = as_half8((pair(hi[0], hi[1]) & first) | (pair(lo[0], lo[1]) & second), (pair(hi[2], hi[3]) & first) | (pair(lo[2], lo[3]) & second),
+                      pair(mid[0], mid[1]) & first, pair(mid[2], mid[3]) & first);
     }
 
     WaveState st;

@@ -66,3 +66,28 @@ def test_a_page_id_outside_its_pool_is_flagged_and_skipped(G, at, bad):
         G.assert_close(out.cpu().numpy(), ref, "without page %d of the list" % at)
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("axis", [tkv.TKV_KEYS_PER_TOKEN, tkv.TKV_KEYS_PER_CHANNEL])
+@pytest.mark.parametrize("bits", [0x0000, 0x7fc0, 0xffc1, 0x7f80, 0x0001, 0x0080], ids=["zero", "nan", "-nan", "inf", "subnormal", "smallest"])
+def test_one_odd_head_leaves_the_others_alone(G, bits, axis):
+    """The heads of a kv head share a power of two found from their exponents: a head of zeros, NaN, infinities or tiny
+    numbers must not change what the others give."""
+    q, K, V, seq_bits = G.random_case(103, [300], 8, 1)
+    q[0, 3, ::5] = bits
+    if bits in (0x0000, 0x0001, 0x0080):
+        q[0, 3, :] = bits
+    if axis == tkv.TKV_KEYS_PER_CHANNEL:
+        cache, kc = G.kc_check_append(seq_bits, K, V, 1)
+    else:
+        cache, (Kq, Vq) = G.check_append(seq_bits, K, V, 1)
+    try:
+        out = G.gpu_decode(cache, q, 2)
+        finite = bits not in (0x7fc0, 0xffc1, 0x7f80)
+        if not finite:
+            q[0, 3, :] = 0
+        ref = G.kc_decode_ref(q, kc, [300]) if axis == tkv.TKV_KEYS_PER_CHANNEL else G.decode_ref(q, Kq, Vq, [300])
+        heads = [h for h in range(8) if finite or h != 3]
+        G.assert_close(out[:, heads], ref[:, heads], "q head of %#06x" % bits)
+    finally:
+        cache.close()
