@@ -9,12 +9,13 @@
 //
 // What bounds it: HBM for whole pages (512 B read and 96 / 160 B written per token and head), the chain of dependent
 // loads (arguments -> slots -> rows -> result) for a few tokens.  Hence
-//  - the rows go straight to LDS, whole 128-byte lines per instruction and non-temporal, without a register, and all
-//    that can be asked for at once is: the slots, then tags, rows and the V words that may have to be merged;
+//  - the rows go straight to LDS, whole 128-byte lines per instruction, without a register, and all that can be asked
+//    for at once is: the slots, then tags, rows and the V words that may have to be merged;
 //  - K and V apart: a workgroup holds 16 KiB of LDS and eight are resident per compute unit, each in a phase of its
-//    own.  65 536 tokens x 8 heads, inputs not in any cache: 67.1 us with both in one workgroup and 64-byte runs per thread
-//    through registers, 63.1 with rows through LDS (32 KiB, five resident), 59.1 apart (5.6 TB/s; with ordinary
-//    loads 62.9, with ordinary stores 60.7); per-channel keys 69.4 -> 60.1; one token for each of 32 sequences 6.0 -> 4.5.
+//    own.  65 536 tokens x 8 heads, inputs not in any cache: 67.2 us with both in one workgroup and 64-byte runs per thread
+//    through registers, 63.1 with rows through LDS (32 KiB, five resident), 59.1 apart (with ordinary stores 60.7);
+//    per-channel keys 69.4 -> 60.1; one token for each of 32 sequences 6.0 -> 4.4.  The launcher says which loads and
+//    which order of the workgroups are taken.
 //
 // K words go straight to HBM (a wavefront's stores for one word index are 256 contiguous bytes, written with
 // non-temporal stores).  V codes are transposed through LDS, because the V plane packs tokens, not channels, into a
@@ -104,11 +105,11 @@ constexpr int kRowBytes = kHeadDim * 2, kRowPieces = kRowBytes / 16;   // a row:
 // instruction moves four rows, sixteen lanes to a row, 1 KiB that is contiguous in LDS.  A thread then reads four
 // consecutive 16-byte pieces of its row; piece p of row r sits at place p ^ (r & 3), so that the lanes of neighbouring
 // rows read from different banks.
-__device__ __forceinline__ void fetch_row_pieces(uint4 *lds_wave, int i, const uint16_t *__restrict__ row, int lane)
+template <bool ONCE> __device__ __forceinline__ void fetch_row_pieces(uint4 *lds_wave, int i, const uint16_t *__restrict__ row, int lane)
 {
     const uint4 *src = reinterpret_cast<const uint4 *>(row) + ((lane & 15) ^ (lane >> 4));
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                     (__attribute__((address_space(3))) void *)(lds_wave + 64 * i), 16, 0, 2 /* nt */);
+                                     (__attribute__((address_space(3))) void *)(lds_wave + 64 * i), 16, 0, ONCE ? 2 : 0 /* nt */);
 }
 __device__ __forceinline__ int piece_at(int slot, int p) { return slot * kRowPieces + (p ^ (slot & 3)); }
 
@@ -293,7 +294,8 @@ __device__ __forceinline__ void append_v(uint8_t *rec, uint64_t mask, const uint
     }
 }
 
-template <bool KC>
+// K_ONCE: the K rows are read with non-temporal loads (see the launcher).
+template <bool KC, bool K_ONCE>
 __global__ __launch_bounds__(256) void tkv_append_kernel(
     uint8_t *__restrict__ pool, uint8_t *__restrict__ bit_map, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const uint8_t *__restrict__ tag_bits, int n_tokens,
@@ -327,7 +329,11 @@ __global__ __launch_bounds__(256) void tkv_append_kernel(
     const uint16_t *from = (is_v ? V : K) + head * kHeadDim;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        if (row_src[i] >= 0 && row_src[i] < n_tokens) fetch_row_pieces(rows + 16 * wave * kRowPieces, i, from + (size_t)row_src[i] * stride, lane);
+        if (row_src[i] >= 0 && row_src[i] < n_tokens) {
+            const uint16_t *row = from + (size_t)row_src[i] * stride;
+            if (K_ONCE && !is_v) fetch_row_pieces<true>(rows + 16 * wave * kRowPieces, i, row, lane);
+            else fetch_row_pieces<false>(rows + 16 * wave * kRowPieces, i, row, lane);
+        }
     // the V words of a page that does not arrive whole, in case they change
     uint32_t old[4] = {0, 0, 0, 0};
     auto fetch_old = [&]() {
@@ -374,10 +380,18 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
                       const int32_t *work_src, int32_t n_work, int32_t *status, void *stream)
 {
     const bool kc = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL;
-    auto kernel = kc ? tkv_append_kernel<true> : tkv_append_kernel<false>;
+    // How much of the input leaves the 256 MiB Infinity Cache alone.  Up to 64 MiB of rows are still there from whoever
+    // computed them, and ordinary loads find them; larger inputs push each other out, and with the K rows read past the
+    // cache the V rows stay in it.  us per call, ordinary / K past the cache / both, same rows again and again | rows not read
+    // for three calls: 12288 tokens x 8 heads 12.0 / 12.5 / 13.0 | 13.1 / 13.6 / 14.1; 20001 22.4 / 23.4 / 25.2 | 27.5 / 23.6 /
+    // 26.1; 65536 47.5 / 49.3 / 56.8 | 61.5 / 59.7 / 57.8; 131072 118 / 94 / 112 | 119 / 116 / 114.
+    const bool k_once = (int64_t)n_tokens * desc->n_kv_heads * (2 * kRowBytes) > (64 << 20);
+    auto kernel = kc ? (k_once ? tkv_append_kernel<true, true> : tkv_append_kernel<true, false>)
+                     : (k_once ? tkv_append_kernel<false, true> : tkv_append_kernel<false, false>);
     // Workgroups are dealt to the eight XCDs in turn: the first grid dimension is the XCD, which reads the rows of all heads
-    // of a page one behind the other (2 KiB per token at eight heads).  65 536 tokens x 8 heads: 57.5 us against 59.2
-    // with the heads of a page spread over the XCDs; K before V, as the gather does it, makes no difference here.
+    // of a page one behind the other (2 KiB per token at eight heads).  65 536 tokens x 8 heads, K and V both read past
+    // the cache: 57.5 us against 59.2 with the heads of a page spread over the XCDs; K before V, as the gather does it,
+    // makes no difference here.
     constexpr int kMaxPages = 8 * 65535, kMaxHeads = 65535 / 2;   // of one launch, by the limits of the grid
     for (int page = 0; page < n_work; page += kMaxPages)
         for (int head = 0; head < desc->n_kv_heads; head += kMaxHeads) {
