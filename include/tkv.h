@@ -300,10 +300,13 @@ int tkv_gather_dequant(const tkv_desc *desc, const void *pool, const uint8_t *bi
  * cost for which the batch still splits into at most target_items items and
  * cuts every sequence into equal parts below that bound, so the number of items
  * never exceeds target_items unless there are more non-empty sequences than
- * that (then one item each).  Where the heaviest such part has two to sixteen
- * pages and target_items times the kv heads fit the device's 3072 wavefronts,
- * every item is filled to its cost instead (rounded up to whole INT4 pages):
- * fewer items, the longest no longer.
+ * that (then one item each).  Where the longest such part has two pages (or
+ * three, with at most four INT4 pages in five and, per-channel keys, a fifth of
+ * target_items to spare; or four, with per-token keys and at most two INT4
+ * pages in five) and target_items times the kv heads fit the 3072 wavefronts
+ * that a whole MI355X holds at once, every item gets as many pages as that part
+ * instead: fewer items, none with more pages than the longest equal part and,
+ * at four pages, none of a greater cost than the heaviest.
  * A plan depends only on the page COUNTS of the sequences: it stays valid while
  * tokens are appended to open pages (the kernel reads the token counts from the
  * device arrays and masks by them) and must be made again when a sequence gains

@@ -366,34 +366,49 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
         const int64_t a2 = std::max<int64_t>(0, std::min(end, p2) - begin);
         return kCost2 * a2 + kCost4 * (end - begin - a2);
     };
-    auto heaviest_part = [&](int64_t p2, int64_t p4, int64_t n) {
-        int64_t most = 0, begin = 0;
-        for (int64_t k = 0; k < n; ++k) {
-            const int64_t end = part_end(p2, p4, n, k, begin);
-            most = std::max(most, cost_of(p2, begin, end));
-            begin = end;
-        }
-        return most;
-    };
     std::vector<int32_t> n_parts(batch, 0);
-    int64_t heaviest = 0;
+    int64_t longest = 0, heaviest = 0, pages2 = 0, pages4 = 0;   // pages and cost of a part at most; pages of the batch
     for (int32_t b = 0; b < batch; ++b) {
         const int64_t p2 = ceil_div(n_tok_int2[b], kPageTokens), p4 = ceil_div(n_tok_int4[b], kPageTokens);
         if (p2 + p4 == 0) continue;
         n_parts[b] = (int32_t)std::min<int64_t>(p2 + p4, (kCost2 * p2 + kCost4 * p4 + per_item - 1) / per_item);
-        heaviest = std::max(heaviest, heaviest_part(p2, p4, n_parts[b]));
+        for (int64_t k = 0, begin = 0, end; k < n_parts[b]; ++k, begin = end) {
+            end = part_end(p2, p4, n_parts[b], k, begin);
+            longest = std::max(longest, end - begin);
+            heaviest = std::max(heaviest, cost_of(p2, begin, end));
+        }
+        pages2 += p2;
+        pages4 += p4;
     }
     // Parts of equal cost, rounded to whole pages, are a mixture of k and k + 1 pages, and every item pays for the
-    // preparation of q and for its partial, which weigh as much as a page.  The launch takes as long as its longest
-    // items: with few pages per item every item gets as many as those have, and there are up to half as many.
-    // Measured (us per call, equal parts -> full items, at a mean of x pages per equal part): 8 kv heads x = 1.03
-    // 18.2 -> 15.3, 1.6 19.3 -> 18.3, 2.2 23.3 -> 22.1, 3.2 24.8 -> 23.8, 5.1 30.0 -> 30.1, 10.1 49.3 -> 48.4; one head 1.1
-    // 16.8 -> 14.6, 2.05 20.1 -> 18.0, 8.1 37.7 -> 38.2, 11.5 47.7 -> 47.2.  At 43 pages the sum of the items on a SIMD
-    // decides, and items that are full leave some with two of them: 170.0 -> 172.6.  Single pages cannot be cut differently.
-    // (More items than the device's 256 x 12 wavefronts hold at once were asked for as such: equal parts.)
+    // preparation of q and for its partial, which weigh as much as a page.  With two to four pages per item every item
+    // gets as many as the longest equal part has: fewer items, none with more pages.  (Two or three are counted in pages:
+    // the widths differ by a seventh of a page, less than an item costs by itself.  An item of four pages costs no more
+    // than the heaviest equal part either.)
+    // Time of full items over that of equal parts, ragged and even batches, 1, 2 and 8 kv heads, least / mean / worst:
+    //   longest equal part   2 pages            3 pages            4                  5                  6 to 9             more
+    //   INT4 share to .4     .83 / .93 / 1.00   .88 / .97 / 1.01   .93 / .98 / 1.03   .93 / .99 / 1.05   .97 / .99 / 1.03   .98 / 1.00 / 1.02
+    //   .5 to .8             .83 / .86 / .89    .88 / .95 / 1.01   .97 / .99 / 1.03   .95 / .99 / 1.01   .97 / .99 / 1.03   .98 / 1.00 / 1.02
+    //   INT4 only            .83 / .93 / 1.01   .96 / 1.00 / 1.02  1.01 / 1.02 / 1.04 1.01 / 1.03 / 1.05 .99 / 1.02 / 1.04  .99 / 1.01 / 1.02
+    //   per-channel keys     .86 / .94 / 1.00   .92 / .98 / 1.05   .93 / .99 / 1.05   .92 / .99 / 1.05   .93 / .98 / 1.01   .94 / 1.00 / 1.04
+    //   ... up to 4/5 of target_items            .92 / .96 / 1.03
+    //   ... more                                 .96 / .99 / 1.05
+    // (10 to 200 batches in a field; repetitions of one plan differ by .01; four pages to .4: 105 of 186 batches more than
+    // .01 faster, 4 slower.)  Longer items have enough pages to even out by themselves, and three full ones on a SIMD take
+    // longer than a mixture, with the per-channel keys' dearer pages above all; INT4 pages wait for memory, and fewer items
+    // are fewer requests under way.  Single pages cannot be cut differently, and more items than the 256 x 12 wavefronts
+    // that a whole MI355X holds at once were asked for as such: equal parts.
     constexpr int64_t kResident = 256 * 12;
-    const bool full = heaviest > kCost4 && heaviest <= 16 * kCost4 && (int64_t)target_items * desc->n_kv_heads <= kResident;
-    const int64_t most = (heaviest + kCost4 - 1) / kCost4 * kCost4;
+    const bool per_token = desc->int2_key_axis == TKV_KEYS_PER_TOKEN;
+    bool full = (longest == 2 || (longest == 3 && pages4 <= 4 * pages2) || (longest == 4 && per_token && 3 * pages4 <= 2 * pages2)) &&
+                (int64_t)target_items * desc->n_kv_heads <= kResident;
+    if (full && longest == 3 && !per_token) {
+        int64_t n_full = 0;
+        for (int32_t b = 0; b < batch; ++b)
+            n_full += ceil_div(ceil_div(n_tok_int2[b], kPageTokens) + ceil_div(n_tok_int4[b], kPageTokens), (int32_t)longest);
+        full = 5 * n_full <= 4 * (int64_t)target_items;
+    }
+    const int64_t most = longest <= 3 ? longest * kCost4 : heaviest;
     int32_t n_items = 0;
     seq_item_indptr_out[0] = 0;
     for (int32_t b = 0; b < batch; ++b) {
@@ -402,7 +417,7 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
         for (int64_t k = 0; full ? begin < p2 + p4 : k < n_parts[b]; ++k) {
             int64_t end;
             if (full) {
-                for (end = begin + 1; end < p2 + p4 && cost_of(p2, begin, end + 1) <= most; ) ++end;
+                for (end = begin + 1; end < std::min(begin + longest, p2 + p4) && cost_of(p2, begin, end + 1) <= most; ) ++end;
             } else {
                 end = part_end(p2, p4, n_parts[b], k, begin);
             }
