@@ -13,7 +13,8 @@
 // unpacking is one AND per two codes, for K and for V.
 //
 //   QK^T  D[token, head] = sum_c code[token, c] * q[head, c].  q is converted to fp16
-//         once, scaled by a power of two (exact) and by 2^-pos per slot; the K scale
+//         once, scaled by a power of two common to the heads (exact down to 2^-31 of the
+//         largest |q|, 2^-25 with per-channel keys) and by 2^-pos per slot; the K scale
 //         (fp32, times the compensating power of two) multiplies the MFMA result.  The
 //         eight heads fill half of the 16 columns, so the columns carry two token sets:
 //         row r of a 32-token block is token r in columns 0..7 and token 16 + r in
@@ -21,7 +22,8 @@
 //         operand holding q in the k-slots of the column's own set and zeros in the
 //         others.  Scale, exponential and weight pieces are then formed once per
 //         (token, head).  The zero-point term sum_g zero[token,g] * sum_{c in g} q[head,c]
-//         is one more MFMA per block whose A operand is the stored fp16 zero plane.
+//         is one more MFMA per block whose A operand is the stored fp16 zero plane; the
+//         sums of q are fp32, in three fp16 pieces.
 //         (Per-channel INT2 keys use the columns differently, see compute_page.)
 //   PV    D[(head, half), channel] = sum_token a[head, token, g] * code[token, channel],
 //         a = W * scale[token, g], W the softmax weight: the V scale multiplies the
@@ -39,8 +41,8 @@
 //         sum_t W * zero[t, g] and the softmax denominator sum_t W come from one more
 //         pair of MFMAs per 32 tokens against the stored zero plane and a column of ones.
 //
-// Every product the MFMAs see is exact; the roundings are fp32 accumulation, the fp32
-// K-scale multiply, the 22-bit softmax weight (common to numerator and denominator) and
+// Every product the MFMAs see is exact; the roundings are fp32 accumulation (the sums of
+// q among it), the fp32 K-scale multiply, the 22-bit softmax weight (common to numerator and denominator) and
 // the two-piece a.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -128,8 +130,16 @@ __device__ __forceinline__ uint32_t ror8_u32(uint32_t v)
 }
 // The value of another lane of the same row of 16 lanes: CTRL is a DPP pattern under which every lane has a source.
 template <int CTRL> __device__ __forceinline__ int row_dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
-// Maximum over a row of 16 lanes, in every lane of the row: neighbours, pairs, quads, halves
+template <int CTRL> __device__ __forceinline__ float row_dpp(float v) { return __builtin_bit_cast(float, row_dpp<CTRL>(__builtin_bit_cast(int, v))); }
+// Sum / maximum over a row of 16 lanes, in every lane of the row: neighbours, pairs, quads, halves
 // (quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror).
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += row_dpp<0xB1>(v);
+    v += row_dpp<0x4E>(v);
+    v += row_dpp<0x141>(v);
+    return v + row_dpp<0x140>(v);
+}
 __device__ __forceinline__ int row_max(int v)
 {
     v = max(v, row_dpp<0xB1>(v));
@@ -909,26 +919,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
         const uint32_t c = lane == 1 ? 0x3c003c00u : 0u;
         lds.pv[kPvZero + lane] = make_uint4(c, c, c, c);
     }
-    // q * 2^E to LDS
+    // q * 2^E to LDS; sums of q over the groups, lanes 16 g .. 16 g + 15 hold group g.  The sums are of q itself, in 32 bits:
+    // they meet zero-points of tens.  (From the staged q on the matrix core, numbers far below the largest of their group
+    // or of the heads lose bits, and it is no faster: 16 contexts of 97 to 6011 tokens 15.4 us either way.)
+    float qsum[8];
 #pragma unroll
-    for (int h = 0; h < 8; ++h)   // exact: q has 8 significant bits
-        qf_store<KC>(qf, h, lane, pack_h2(__uint_as_float(q2[h] << 16) * two_e, __uint_as_float(q2[h] & 0xffff0000u) * two_e));
-    lds_order();
-    {
-        // sums of q over the groups, one MFMA per group: row = head, the 32 channels of the group against ones
-        constexpr uint32_t kOne = 0x3c003c00u;
-        floatx4 gsum[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const uint4 a = *reinterpret_cast<const uint4 *>(static_cast<const char *>(qf) + qf_chunk<KC>(r16 & 7, g * 4 + q4));
-            gsum[g] = mfma(as_half8(a.x, a.y, a.z, a.w), as_half8(kOne, kOne, kOne, kOne), floatx4{0.f, 0.f, 0.f, 0.f});
-        }
-        const float undo = ldexpf(1.0f, -E);
-        if (q4 < 2 && r16 == 0)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)   // [head][group]
-                *reinterpret_cast<float4 *>(lds.zl()[4 * q4 + i]) = make_float4(gsum[0][i] * undo, gsum[1][i] * undo, gsum[2][i] * undo, gsum[3][i] * undo);
+    for (int h = 0; h < 8; ++h) {
+        const float even = __uint_as_float(q2[h] << 16), odd = __uint_as_float(q2[h] & 0xffff0000u);
+        qf_store<KC>(qf, h, lane, pack_h2(even * two_e, odd * two_e));   // exact down to 2^-24: q has 8 significant bits
+        qsum[h] = row_sum(even + odd);
     }
+    if (r16 == 0)
+#pragma unroll
+        for (int h = 0; h < 8; ++h) lds.zl()[h][q4] = qsum[h];   // [head][group]
     lds_order();
     const int hcol = (r16 & 7) & (R - 1);   // head of this lane's column (columns beyond R repeat heads)
     half8 qz;
