@@ -366,14 +366,12 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
         const int64_t a2 = std::max<int64_t>(0, std::min(end, p2) - begin);
         return kCost2 * a2 + kCost4 * (end - begin - a2);
     };
-    std::vector<int32_t> n_parts(batch, 0);
+    auto parts_of = [&](int64_t p2, int64_t p4) { return std::min<int64_t>(p2 + p4, (kCost2 * p2 + kCost4 * p4 + per_item - 1) / per_item); };
     int64_t longest = 0, heaviest = 0, pages2 = 0, pages4 = 0;   // pages and cost of a part at most; pages of the batch
     for (int32_t b = 0; b < batch; ++b) {
         const int64_t p2 = ceil_div(n_tok_int2[b], kPageTokens), p4 = ceil_div(n_tok_int4[b], kPageTokens);
-        if (p2 + p4 == 0) continue;
-        n_parts[b] = (int32_t)std::min<int64_t>(p2 + p4, (kCost2 * p2 + kCost4 * p4 + per_item - 1) / per_item);
-        for (int64_t k = 0, begin = 0, end; k < n_parts[b]; ++k, begin = end) {
-            end = part_end(p2, p4, n_parts[b], k, begin);
+        for (int64_t k = 0, n = parts_of(p2, p4), begin = 0, end; k < n; ++k, begin = end) {
+            end = part_end(p2, p4, n, k, begin);
             longest = std::max(longest, end - begin);
             heaviest = std::max(heaviest, cost_of(p2, begin, end));
         }
@@ -414,12 +412,12 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
     for (int32_t b = 0; b < batch; ++b) {
         const int64_t p2 = ceil_div(n_tok_int2[b], kPageTokens), p4 = ceil_div(n_tok_int4[b], kPageTokens);
         int64_t begin = 0;
-        for (int64_t k = 0; full ? begin < p2 + p4 : k < n_parts[b]; ++k) {
+        for (int64_t k = 0, n = parts_of(p2, p4); full ? begin < p2 + p4 : k < n; ++k) {
             int64_t end;
             if (full) {
                 for (end = begin + 1; end < std::min(begin + longest, p2 + p4) && cost_of(p2, begin, end + 1) <= most; ) ++end;
             } else {
-                end = part_end(p2, p4, n_parts[b], k, begin);
+                end = part_end(p2, p4, n, k, begin);
             }
             if (n_items >= capacity) return TKV_ERR_CAPACITY;
             int32_t *it = items_out + 4 * (size_t)n_items;

@@ -1,4 +1,8 @@
 """The decode planner's two ways of cutting a sequence: equal parts, and items filled to the longest equal part.  Compared with equal parts (restated here) over small page tables of every mixture of widths."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -96,3 +100,28 @@ def test_plan_at_the_lines_of_the_rule(heads, p2, p4, axis):
     target = 3072 // heads
     items, sip = _plan(heads, p2, p4, target, axis=axis)
     _check(items, sip, heads, p2, p4, target, axis)
+
+
+_NO_MEMORY = """
+import ctypes as C, resource
+import numpy as np
+from paper_2605_17170_amd import tkv
+batch = 16 << 20
+zero, out, item = np.zeros(batch + 1, np.int32), np.ones(batch + 1, np.int32), np.empty(4, np.int32)
+L, desc = tkv.lib(), tkv.tkv_desc.make(1, 8, 8)
+def plan(n, indptr, n2, capacity):
+    p = lambda a: C.c_void_p(a.ctypes.data)
+    return L.tkv_plan_decode(C.byref(desc), n, p(indptr), p(n2), p(zero), 8, p(item), capacity, p(out))
+assert plan(2, zero, zero, 1) == 0
+size = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (size + (16 << 20), resource.RLIM_INFINITY))
+assert plan(batch, zero, zero, 1) == 0 and not out.any()
+print("planned")
+"""
+
+
+def test_plan_over_many_sequences_needs_no_memory():
+    """A C entry lets no exception out: what the cut into parts needs does not grow with the batch."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-c", _NO_MEMORY], cwd=root, capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0 and run.stdout.strip() == "planned", run.stderr[-500:]
