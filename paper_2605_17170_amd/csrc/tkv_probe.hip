@@ -74,24 +74,25 @@ __global__ __launch_bounds__(64) void tkv_probe_records_kernel(
         };
         int page = page_at(pb);
         read_record(page, kvh, r);
-        for (int pi = pb; pi < pe; ++pi) {
-            const int next = page_at(pi + 1 < pe ? pi + 1 : pi);
+        for (int pi = pb + 1; pi < pe; ++pi) {   // nothing is asked for behind the last page
+            const int next = page_at(pi);
             fold_record(page, r);
             read_record(next, kvh, r);
             page = next;
         }
+        fold_record(page, r);
     } else {
         const int n_rec = n_total * n_kv_heads;
         int k = blockIdx.x;
         if (k >= n_rec) return;
         read_record(k / n_kv_heads, k % n_kv_heads, r);
-        while (k < n_rec) {
-            const int kn = k + (int)gridDim.x < n_rec ? k + (int)gridDim.x : k;
+        while (n_rec - k > (int)gridDim.x) {
+            const int kn = k + (int)gridDim.x;
             fold_record(k / n_kv_heads, r);
             read_record(kn / n_kv_heads, kn % n_kv_heads, r);
-            if (kn == k) break;
             k = kn;
         }
+        fold_record(k / n_kv_heads, r);
     }
     if (acc == 0x5a17c0deu && sink) atomicOr(sink, 1u);
 }
