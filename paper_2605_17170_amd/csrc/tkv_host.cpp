@@ -324,8 +324,10 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
     if (batch < 0 || target_items < 1 || capacity < 0 || !page_indptr || !seq_item_indptr_out) return TKV_ERR_INVALID_ARG;
     if (batch > 0 && (!n_tok_int2 || !n_tok_int4)) return TKV_ERR_INVALID_ARG;
     if (capacity > 0 && !items_out) return TKV_ERR_INVALID_ARG;
-    // decode cost of a page: the kernel is bound by instruction issue, not bytes, and an INT4 page costs
-    // about 7/6 of an INT2 page (same MFMA count, a few more unpack operations, more bytes in flight)
+    // Decode cost of a page among pages of both widths: an INT4 page has the same MFMAs, a few more unpack operations and
+    // 5/3 of the bytes, but wavefronts over INT4 pages lean on memory, those over INT2 pages on their SIMD, and they share
+    // the compute unit: 6 : 6 to 6 : 10 end within 1.5 % of each other on 240 MB and on 805 MB.  (A cache of INT4 pages alone
+    // costs 8.5 a page.)
     constexpr int64_t kCost2 = 6, kCost4 = 7;
     int64_t total = 0;
     for (int32_t b = 0; b < batch; ++b) {
@@ -385,7 +387,7 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
     // than the heaviest equal part either.)
     // Time of full items over that of equal parts, ragged and even batches, 1, 2 and 8 kv heads, least / mean / worst:
     //   longest equal part   2 pages            3 pages            4                  5                  6 to 9             more
-    //   INT4 share to .4     .83 / .93 / 1.00   .88 / .97 / 1.01   .93 / .98 / 1.03   .93 / .99 / 1.05   .97 / .99 / 1.03   .98 / 1.00 / 1.02
+    //   INT4 share to .4     .83 / .93 / 1.00   .89 / .97 / 1.01   .93 / .98 / 1.03   .93 / .99 / 1.05   .97 / .99 / 1.03   .98 / 1.00 / 1.02
     //   .5 to .8             .83 / .86 / .89    .88 / .95 / 1.01   .97 / .99 / 1.03   .95 / .99 / 1.01   .97 / .99 / 1.03   .98 / 1.00 / 1.02
     //   INT4 only            .83 / .93 / 1.01   .96 / 1.00 / 1.02  1.01 / 1.02 / 1.04 1.01 / 1.03 / 1.05 .99 / 1.02 / 1.04  .99 / 1.01 / 1.02
     //   per-channel keys     .86 / .94 / 1.00   .92 / .98 / 1.05   .93 / .99 / 1.05   .92 / .99 / 1.05   .93 / .98 / 1.01   .94 / 1.00 / 1.04
@@ -395,7 +397,8 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
     // .01 faster, 4 slower.)  Longer items have enough pages to even out by themselves, and three full ones on a SIMD take
     // longer than a mixture, with the per-channel keys' dearer pages above all; INT4 pages wait for memory, and fewer items
     // are fewer requests under way.  Single pages cannot be cut differently, and more items than the 256 x 12 wavefronts
-    // that a whole MI355X holds at once were asked for as such: equal parts.
+    // that a whole MI355X holds at once were asked for as such: equal parts.  (A partition of the device holds fewer; the
+    // planner does not ask which it is.)
     constexpr int64_t kResident = 256 * 12;
     const bool per_token = desc->int2_key_axis == TKV_KEYS_PER_TOKEN;
     bool full = (longest == 2 || (longest == 3 && pages4 <= 4 * pages2) || (longest == 4 && per_token && 3 * pages4 <= 2 * pages2)) &&
@@ -426,13 +429,15 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
         }
         seq_item_indptr_out[b + 1] = n_items;
     }
-    // Launch order.  The kernel runs one wavefront per (item, kv head), all resident at once, three to a SIMD, and the
-    // hardware deals workgroups out in order: the items at places p, p + S and p + 2S of the list, S = target_items / 3,
-    // share SIMDs.  A wavefront over INT2 pages keeps its SIMD busier than one over INT4 pages (same arithmetic, 40 %
-    // fewer bytes to wait for), and three of them together run 3-12 % slower than in mixed company, which is what the
-    // launch then ends with.  Listing the items by falling share of INT2 pages puts the INT2-heaviest third at the
-    // places [0, S), the INT4-heaviest at [2S, 3S), one of each on every SIMD.  (Any order is correct: an item names
-    // its own partial slot.)
+    // Launch order.  The kernel runs one wavefront per (item, kv head), and the hardware deals workgroups out in order:
+    // with target_items chosen for three wavefronts per SIMD, the places p, p + S and p + 2S of the list, S =
+    // target_items / 3, share SIMDs.  A wavefront over INT2 pages keeps its SIMD busier than one over INT4 pages (same
+    // arithmetic, 40 % fewer bytes to wait for), and three of them together run 3-12 % slower than in mixed company, which
+    // is what the launch then ends with.  Listing the items by falling share of INT2 pages puts, where the places are all
+    // taken (equal parts), the INT2-heaviest third at [0, S), the INT4-heaviest at [2S, 3S), one of each on every SIMD: 805 MB
+    // 163.7 -> 160.2 us, 240 MB 57.1 -> 56.3.  Full items leave the last places empty, and a SIMD has one or two wavefronts or
+    // three by where the list ends; no other order was measured for those.  (Any order is correct: an item names its own
+    // partial slot.)
     if (n_items > 1) {
         std::vector<int32_t> order(n_items);
         std::vector<int64_t> key(n_items);
