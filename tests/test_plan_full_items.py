@@ -1,4 +1,5 @@
-"""The decode planner's two ways of cutting a sequence: equal parts, and items filled to the longest equal part.  Compared with equal parts (restated here) over small page tables of every mixture of widths."""
+"""The decode planner's two ways of cutting a sequence: equal parts, and items filled to the longest equal
+part.  Compared with equal parts (restated here) over small page tables of every mixture of widths."""
 import os
 import subprocess
 import sys
