@@ -25,21 +25,26 @@
 //         is one more MFMA per block whose A operand is the stored fp16 zero plane; the
 //         sums of q are fp32, in three fp16 pieces.
 //         (Per-channel INT2 keys use the columns differently, see compute_page.)
-//   PV    D[(head, half), channel] = sum_token a[head, token, g] * code[token, channel],
-//         a = W * scale[token, g], W the softmax weight: the V scale multiplies the
-//         weights, not the codes.  Rows 0..7 carry the weights of the heads for groups 0
-//         and 1, rows 8..15 for groups 2 and 3; the 16 columns of an MFMA are 8 channels
-//         of groups {0,1} and 8 channels of groups {2,3} (each lane loads its V words
-//         accordingly), so every (head, token, group) product is formed once per
-//         wavefront; the two cross quadrants of the result are never read.
+//   PV    D[(piece, head), channel] = sum_token a[piece, head, token, g] * code[token, channel],
+//         a = W * scale[token, g] in two pieces, W the softmax weight: the V scale multiplies the
+//         weights, not the codes.  Rows 0..7 carry the leading pieces of the heads, rows 8..15 the
+//         second pieces, and the two are added once, in the epilogue: every row and column
+//         of every MFMA counts.  (With rows 8..15 for other groups than rows 0..7 and an MFMA
+//         for each piece, half of every result was never read: 32 MFMAs a page instead of 16.
+//         MFMAs and other vector instructions of the three wavefronts of a SIMD hardly overlap:
+//         16 of these MFMAs alone take 85 ns, 64 FMAs 68 ns, both together 123 to 133 ns.
+//         With cache-resident pages an INT2 page takes 0.77 us of its SIMD instead of 0.84, an
+//         INT4 page 0.81 instead of 0.86.)
 //         The weights must be good to about 2^-17: a group with outlier channels has
 //         |code * scale| and |zero| of tens that cancel, and the tolerance near zero is
 //         2e-3.  W is therefore carried in two fp16 pieces (the leading 11 bits, then the
 //         next 11), and a in two pieces as well: a_hi = fp16(W_hi * s), a_lo = W_lo * s +
-//         the exact remainder of the hi product (packed fp16 FMAs); each V operand meets
-//         both pieces (two MFMAs into the same accumulator).  The zero-point term
+//         the exact remainder of the hi product (packed fp16 FMAs).  The zero-point term
 //         sum_t W * zero[t, g] and the softmax denominator sum_t W come from one more
-//         pair of MFMAs per 32 tokens against the stored zero plane and a column of ones.
+//         pair of MFMAs per 32 tokens against the stored zero plane and a column of ones.  (As
+//         one MFMA with the pieces in separate rows it would round less, but not as the code
+//         term does, which it cancels: error of 32 contexts of 4K to 128K 6.6e-6 -> 7.0e-6,
+//         as a pair 5.7e-6.)
 //
 // Every product the MFMAs see is exact; the roundings are fp32 accumulation (the sums of
 // q among it), the fp32 K-scale multiply, the 22-bit softmax weight (common to numerator and denominator) and
@@ -124,9 +129,38 @@ __device__ __forceinline__ float row_ror8(float v)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128 /* row_ror:8 */, 0xf, 0xf, true));
 }
+// The A operand of a PV MFMA from the two pieces (hi, lo) that every lane has made for its own four tokens (two fp16 pairs
+// each): row r < 8 is the leading piece of head r, row r + 8 the second, and the k-slot octet of both lists the four tokens
+// of the lanes of columns 0..7, then those of columns 8..15.  A lane keeps the piece its row wants and takes the other four
+// tokens from the lane eight columns on: one select with a DPP operand per register.  (DPP moves into a preset register
+// need a copy of one of the pieces as well, 25 moves a page.)  Two wait states are due between the write of a register
+// and its DPP read, and between the write and the read by an MFMA; the compiler does not see the instructions in here.
+__device__ __forceinline__ half8 piece_rows(const uint32_t (&hi)[2], const uint32_t (&lo)[2])
+{
+    uint32_t r0, r1, r2, r3;
+    asm("s_nop 0\n\t"
+        "s_mov_b64 vcc, %8\n\t"
+        "v_cndmask_b32_dpp %0, %6, %4, vcc row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %1, %7, %5, vcc row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "s_not_b64 vcc, vcc\n\t"
+        "v_cndmask_b32_dpp %2, %4, %6, vcc row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_cndmask_b32_dpp %3, %5, %7, vcc row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1"
+        : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
+        : "v"(hi[0]), "v"(hi[1]), "v"(lo[0]), "v"(lo[1]), "s"(0x00ff00ff00ff00ffull /* columns 0..7 */)
+        : "vcc", "scc");
+    return as_half8(r0, r1, r2, r3);
+}
 __device__ __forceinline__ uint32_t ror8_u32(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128 /* row_ror:8 */, 0xf, 0xf, true);
+}
+// x and y hold the sums of the two pieces of the weights in lanes 0..31 and 32..63: adds the pieces, x in lanes 0..31, y in
+// lanes 32..63.
+__device__ __forceinline__ float add_pieces(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, y), false, false);
+    return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 // The value of another lane of the same row of 16 lanes: CTRL is a DPP pattern under which every lane has a source.
 template <int CTRL> __device__ __forceinline__ int row_dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
@@ -165,11 +199,10 @@ __device__ __forceinline__ void lds_order()
 }
 
 struct WaveState {
-    // PV accumulators.  Lane (c = lane % 16, q4 = lane / 16) holds rows 4*q4 + i: head 4*(q4 & 1) + i of row half
-    // q4 >> 1; its column of acc[chunk][comp] is channel 64*(c >> 3) + 16*comp + (chunk ? c ^ 8 : c) % 16.
-    // Only the quadrants with q4 >> 1 == c >> 3 (row half = column half) are meaningful.
+    // PV accumulators.  Lane (c = lane % 16, q4 = lane / 16) holds rows 4*q4 + i: head 4*(q4 & 1) + i, leading piece of the
+    // weights (q4 < 2) or second piece; acc[half][comp] is channel 64*half + 16*comp + c.
     floatx4 acc[2][4];
-    floatx4 zp;         // sum_t W * zero[t, g] in columns 0..3 (groups), sum_t W in column 4
+    floatx4 zp;         // rows 0..7: sum_t W * zero[t, g] in columns 0..3 (groups), sum_t W in column 4
     uint32_t sat;       // non-zero once a staged scale was clamped (reported in the status word at the end)
     float m_ref;        // reference maximum of this lane's head column, log2 units, -inf before the first page
 };
@@ -284,7 +317,7 @@ __device__ __forceinline__ void build_q_operand(const void *qf /* the staged q (
 template <int BITS> struct PageRegs {
     uint4 kw[4];          // K codes, 16-byte chunks of four group words: [blk*2 + half group] of this lane's token (two token
                           // sets), or one per 16-token tile (per-channel INT2 keys)
-    uint4 vw[BITS];       // V codes: 16-byte chunks, one word per 16-channel tile; [blk*2 + chunk] (INT4), [chunk] (INT2)
+    uint4 vw[BITS];       // V codes: 16-byte chunks, one word per 16-channel tile; [blk*2 + channel half] (INT4), [channel half] (INT2)
     uint2 ksc, vsc, vzc;  // this lane's four entries of the K scale / V scale / V zero planes
     uint2 kzc;            // K zero of token `lane`, four groups
 };
@@ -324,11 +357,6 @@ template <int BITS, bool KC> constexpr int kcode_part(int i)
     if (KC && BITS == 2) return i * 32;   // tile i
     return BITS == 4 ? (i >> 1) * 128 + (i & 1) * 32 : (i >> 1) * 64 + (i & 1) * 16;
 }
-// Columns 0..7 of the PV MFMAs are channels of groups 0 and 1, columns 8..15 of groups 2 and 3: lane
-// (c, quad) reads the chunks of channel half c >> 3, at its own column (even i) and at column c ^ 8 (odd i);
-// INT4: i = blk*2 + chunk, INT2: i = chunk (a word holds both blocks)
-__device__ __forceinline__ int vcode_chunk(int lane) { return ((lane & 8) << 3) + (lane & 48) + (lane & 15); }
-
 // The loads of one record come in two parts, so that each can be issued as soon as the registers it lands in are
 // free: the metadata planes and the K codes, and the V codes.
 template <int BITS, bool KC> __device__ __forceinline__ void load_page_k(PageRegs<BITS> &pr, Record rec, int lane)
@@ -345,9 +373,8 @@ template <int BITS, bool KC> __device__ __forceinline__ void load_page_k(PageReg
 template <int BITS> __device__ __forceinline__ void load_page_v(PageRegs<BITS> &pr, Record rec, int lane)
 {
     using R = Rec<BITS>;
-    const int at = vcode_chunk(lane) * 16;
 #pragma unroll
-    for (int i = 0; i < BITS; ++i) pr.vw[i] = buffer_load16_once(rec, at ^ ((i & 1) << 7), R::kVCodes + (BITS == 4 ? (i >> 1) * 2048 : 0));
+    for (int i = 0; i < BITS; ++i) pr.vw[i] = buffer_load16_once(rec, lane * 16, R::kVCodes + 1024 * i);   // chunk 64 i + lane
 }
 // Lane constants of the page loop.
 struct LaneConst {
@@ -355,10 +382,7 @@ struct LaneConst {
     float kappa;          // sm_scale * log2(e)
     uint32_t vmul01, vmul23;   // fp16 pairs of the staging factor of the V scale, 2^(kVExp - pos)
     int zp_idx[2];        // chunk of Lds::pv with this lane's B operand of the zero-point MFMA, per 32-token block
-    int vs_idx;           // ... of the staged V scales of (block 0, this lane's quad, group 2*(c >> 3))
-    int vs_st;            // 8-byte slot of Lds::pv (behind kPvS) where this lane stages its four V scales
-    uint32_t vrot[2];     // INT4 V unpack: rotate amounts that bring registers 0, 1 / 2, 3 of the operand into place
-    uint32_t vmask[4];    // INT2 V unpack: field masks of operand registers 0..3
+    int vs_idx;           // 8-byte half chunk of Lds::pv with the staged V scales of (block 0, group 0) of this lane's four tokens
     int tok0;             // two token sets: first token of this lane's four within a 32-token block
     int qy_ent;           // ... entry of this lane in a q operand of the QK^T MFMAs (or one of the two zero entries)
     float zmul;           // per-channel INT2 keys: 2^-24 in head columns 0..7, 0 in columns 8..15
@@ -428,7 +452,7 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
             const uint32_t m01 = pk_mul(vsc.x, lc.vmul01), m23 = pk_mul(vsc.y, lc.vmul23);
             const uint32_t s01 = pk_min(m01, kVsClamp), s23 = pk_min(m23, kVsClamp);
             st.sat |= (s01 ^ m01) | (s23 ^ m23);
-            reinterpret_cast<uint2 *>(lds.pv)[2 * kPvS + lc.vs_st] = make_uint2(s01, s23);
+            reinterpret_cast<uint2 *>(lds.pv)[2 * kPvS + lane] = make_uint2(s01, s23);
             reinterpret_cast<uint2 *>(lds.pv)[2 * kPvZ + lane] = vzc;
         }
     }
@@ -555,6 +579,16 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
         asm volatile("" : "+v"(S[0]), "+v"(S[1]));   // the scaled sums are formed here, not sunk next to their first use
         __builtin_amdgcn_sched_barrier(0);
     }
+    // What the PV phase reads from LDS, requested ahead of the softmax: columns 0..3 of the zero-point MFMA are the V zeros of
+    // the groups, column 4 ones; the staged V scales of this lane's own tokens.
+    uint4 v_zero[2];
+    uint2 v_scale[2][4];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+        v_zero[blk] = lds.pv[lc.zp_idx[blk]];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) v_scale[blk][g] = reinterpret_cast<const uint2 *>(lds.pv)[lc.vs_idx + 32 * blk + 2 * g];
+    }
     after_qk();
     constexpr int kS = 2;   // logit registers of this lane: its eight tokens of the page
     if (partial) {
@@ -589,11 +623,9 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
         st.zp *= av;
     }
     const float nmref = (float)kPExp - (st.m_ref == -INFINITY ? 0.0f : st.m_ref);
-    // W = P * 2^kPExp in two fp16 pieces (leading 11 bits truncated, then the next 11): the eight tokens of this
-    // lane's k-slot octet per 32-token block.  With two token sets a lane forms the pieces of its own four tokens
-    // and takes the other four from the lane eight columns on: registers 0, 1 are its own, 2, 3 the other set's
-    // (the V operand of columns 8..15 lists its tokens in that order too).
-    uint32_t wh[2][4], wl[2][4];
+    // W = P * 2^kPExp in two fp16 pieces (leading 11 bits truncated, then the next 11), for this lane's own four tokens of
+    // each 32-token block (two token sets: tile 2*blk in columns 0..7, 2*blk + 1 in columns 8..15)
+    uint32_t wh[2][2], wl[2][2];
 #pragma unroll
     for (int e = 0; e < kS; ++e) {
         float pv[4];
@@ -601,69 +633,58 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
         for (int i = 0; i < 4; ++i) pv[i] = __builtin_amdgcn_exp2f(fmaf(S[e][i], lc.kappa, nmref));
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(pv[2 * k], pv[2 * k + 1]));
-            const uint32_t lo = __builtin_bit_cast(
-                uint32_t, __builtin_amdgcn_cvt_pkrtz(residual<0>(hi, -1.0f, pv[2 * k]), residual<1>(hi, -1.0f, pv[2 * k + 1])));
-            wh[e][k] = hi;
-            wl[e][k] = lo;
-            wh[e][2 + k] = ror8_u32(hi);
-            wl[e][2 + k] = ror8_u32(lo);
+            wh[e][k] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(pv[2 * k], pv[2 * k + 1]));
+            wl[e][k] = __builtin_bit_cast(
+                uint32_t, __builtin_amdgcn_cvt_pkrtz(residual<0>(wh[e][k], -1.0f, pv[2 * k]), residual<1>(wh[e][k], -1.0f, pv[2 * k + 1])));
         }
     }
 
     // ---- PV ------------------------------------------------------------------
+    auto weights = [&](int blk, int g) {
+        // a = W * scale in two fp16 pieces: hi = fp16(W_hi s), lo = W_lo s + the exact remainder of the hi product
+        const uint32_t vsr[2] = {v_scale[blk][g].x, v_scale[blk][g].y};
+        uint32_t ah[2], al[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) ah[k] = pk_mul(wh[blk][k], vsr[k]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) al[k] = pk_rem(wh[blk][k], vsr[k], ah[k]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) al[k] = pk_fma(wl[blk][k], vsr[k], al[k]);
+        return piece_rows(ah, al);
+    };
+    // Codes as fp16 subnormals, fields shifted towards the top of the mantissa (INT2: bits 4:3, 6:5, 8:7, 10:9 of each half;
+    // INT4: bits 6:3 and 10:7): the matrix core aligns the products of a lane's eight k-slots to the largest exponent
+    // *field* and drops what falls below a fixed window, so leading zeros of a subnormal cost precision.  Bit 10 is the
+    // lowest exponent bit: fp16 is linear through the first binade, so a field may reach it.  The slot's power of two is
+    // undone in the staged V scale.  Bits of the other half that a shift brings in fall outside the masks.
+    auto codes = [&](int blk, int half, int comp) {
+        const uint4 v = BITS == 4 ? pr.vw[blk * 2 + half] : pr.vw[half];
+        const uint32_t w = comp == 0 ? v.x : comp == 1 ? v.y : comp == 2 ? v.z : v.w;
+        if (BITS == 4) {
+            const uint32_t wa = w << 3, wb = w >> 5;
+            return as_half8(wa & 0x00780078u, wa & 0x07800780u, wb & 0x00780078u, wb & 0x07800780u);
+        } else {
+            const uint32_t ws = blk ? (w >> 5) : (w << 3);
+            return as_half8(ws & 0x00180018u, ws & 0x00600060u, ws & 0x01800180u, ws & 0x06000600u);
+        }
+    };
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
-        // zero-point term and denominator: columns 0..3 = V zero of the groups, column 4 = ones
-        {
-            const uint4 bz4 = lds.pv[lc.zp_idx[blk]];
-            const half8 bz = as_half8(bz4.x, bz4.y, bz4.z, bz4.w);
-            st.zp = mfma(as_half8(wh[blk][0], wh[blk][1], wh[blk][2], wh[blk][3]), bz, st.zp);
-            st.zp = mfma(as_half8(wl[blk][0], wl[blk][1], wl[blk][2], wl[blk][3]), bz, st.zp);
-        }
+        // zero-point term and denominator, both pieces into rows 0..7 (rows 8..15 are never read)
+        const half8 vz = as_half8(v_zero[blk].x, v_zero[blk].y, v_zero[blk].z, v_zero[blk].w);
+        st.zp = mfma(as_half8(wh[blk][0], wh[blk][1], ror8_u32(wh[blk][0]), ror8_u32(wh[blk][1])), vz, st.zp);
+        st.zp = mfma(as_half8(wl[blk][0], wl[blk][1], ror8_u32(wl[blk][0]), ror8_u32(wl[blk][1])), vz, st.zp);
+    }
+    // (block, group) by (block, group), the weights of the next one made ahead of the MFMAs of this one
+    half8 a = weights(0, 0);
 #pragma unroll
-        for (int gg = 0; gg < 2; ++gg) {
-            // a = W * scale for group 2*(c >> 3) + gg in two fp16 pieces: hi = fp16(W_hi s), lo = W_lo s + the exact
-            // remainder of the hi product
-            const uint4 vs = lds.pv[lc.vs_idx + 16 * blk + gg];
-            const uint32_t vsr[4] = {vs.x, vs.y, vs.z, vs.w};
-            uint32_t ah[4], al[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                ah[k] = pk_mul(wh[blk][k], vsr[k]);
-                al[k] = pk_fma(wl[blk][k], vsr[k], pk_rem(wh[blk][k], vsr[k], ah[k]));
-            }
-            const half8 a_hi = as_half8(ah[0], ah[1], ah[2], ah[3]), a_lo = as_half8(al[0], al[1], al[2], al[3]);
-            half8 b[2][2];
-#pragma unroll
-            for (int chunk = 0; chunk < 2; ++chunk)
-#pragma unroll
-                for (int cc = 0; cc < 2; ++cc) {
-                    const int comp = 2 * gg + cc;
-                    const uint4 v = BITS == 4 ? pr.vw[blk * 2 + chunk] : pr.vw[chunk];
-                    const uint32_t w = comp == 0 ? v.x : comp == 1 ? v.y : comp == 2 ? v.z : v.w;
-                    // Codes as fp16 subnormals, fields shifted towards the top of the mantissa (INT2: bits 4:3,
-                    // 6:5, 8:7, 10:9 of each half; INT4: bits 6:3 and 10:7): the matrix core aligns the products of
-                    // a lane's eight k-slots to the largest exponent *field* and drops what falls below a fixed
-                    // window, so leading zeros of a subnormal cost precision.  Bit 10 is the lowest exponent bit:
-                    // fp16 is linear through the first binade, so a field may reach it.  The slot's power of two
-                    // is undone in the staged V scale.
-                    // Registers 0, 1 take the tokens of this lane's own set, 2, 3 those of the other set (see the
-                    // weights): the rotate amounts (INT4) or the masks (INT2) differ between the column halves.
-                    if (BITS == 4) {
-                        const uint32_t wa = __builtin_amdgcn_alignbit(w, w, lc.vrot[0]), wb = __builtin_amdgcn_alignbit(w, w, lc.vrot[1]);
-                        b[chunk][cc] = as_half8(wa & 0x00780078u, wa & 0x07800780u, wb & 0x00780078u, wb & 0x07800780u);
-                    } else {
-                        const uint32_t ws = blk ? (w >> 5) : (w << 3);
-                        b[chunk][cc] = as_half8(ws & lc.vmask[0], ws & lc.vmask[1], ws & lc.vmask[2], ws & lc.vmask[3]);
-                    }
-                    st.acc[chunk][2 * gg + cc] = mfma(a_hi, b[chunk][cc], st.acc[chunk][2 * gg + cc]);
-                }
-#pragma unroll
-            for (int chunk = 0; chunk < 2; ++chunk)
-#pragma unroll
-                for (int cc = 0; cc < 2; ++cc) st.acc[chunk][2 * gg + cc] = mfma(a_lo, b[chunk][cc], st.acc[chunk][2 * gg + cc]);
-        }
+    for (int t = 0; t < 8; ++t) {
+        const int blk = t >> 2, g = t & 3, half = g >> 1, comp = 2 * (g & 1);
+        const half8 b0 = codes(blk, half, comp), b1 = codes(blk, half, comp + 1);
+        const half8 next = t < 7 ? weights((t + 1) >> 2, (t + 1) & 3) : a;
+        st.acc[half][comp] = mfma(a, b0, st.acc[half][comp]);
+        st.acc[half][comp + 1] = mfma(a, b1, st.acc[half][comp + 1]);
+        a = next;
     }
     after_pv();
 }
@@ -753,16 +774,6 @@ __device__ __forceinline__ void run_pages(const ItemCtx &cx, PageBatch &batch, i
         const uint32_t h01 = (uint32_t)(15 + kVExp - p01) << 10, h23 = (uint32_t)(15 + kVExp - p23) << 10;
         lc.vmul01 = h01 | (h01 << 16);
         lc.vmul23 = h23 | (h23 << 16);
-        // Order of the eight tokens of a k-slot octet in the PV operands: a lane lists its own token set first, which
-        // for columns 8..15 (the rows and columns of groups 2 and 3) is tile 2*blk + 1: those lanes swap the register
-        // pairs of the V operand, and the staged scales of groups 2 and 3 are stored with their 8-byte halves swapped.
-        const bool swap = lane & 8;
-        lc.vrot[0] = swap ? 5u : 29u;   // w >> 5 / w << 3 (stray bits fall outside the masks)
-        lc.vrot[1] = swap ? 29u : 5u;
-        const uint32_t m[4] = {0x00180018u, 0x00600060u, 0x01800180u, 0x06000600u};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) lc.vmask[k] = m[swap ? k ^ 2 : k];
-        lc.vs_st = (lane & 4) ? lane ^ 1 : lane;   // lane = ((blk*4 + quad)*4 + g)*2 + half
     }
     // One register set: every part of the next record is requested as soon as the registers it lands in
     // are dead, so about one page per wavefront is in flight while the current one is computed.
@@ -903,10 +914,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     lc.kappa = kappa;
     lc.vmul01 = lc.vmul23 = 0;
     lc.zmul = r16 >= 8 ? 0.0f : 0x1p-24f;
-    lc.vs_idx = kPvS + q4 * 4 + 2 * (r16 >> 3);
-    lc.vs_st = lane;
-    lc.vrot[0] = lc.vrot[1] = 0;
-    lc.vmask[0] = lc.vmask[1] = lc.vmask[2] = lc.vmask[3] = 0;
+    lc.vs_idx = 2 * (kPvS + q4 * 4) + (r16 >> 3);
     lc.tok0 = 16 * (r16 >> 3) + 4 * q4;
     static_assert(kQyZero0 == 24 && kQyZero1 == 16, "entry 24 - 8 * sub holds the zeros of the lanes of octet sub");
     const int other_set = -(int)((r16 >> 3) != (q4 >> 1));
@@ -1007,7 +1015,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     if (q4 == 0 && r16 < 8) lds.alpha[r16] = st.m_ref;
     lds_order();
     const float unscale = ldexpf(1.0f, 24 - kVExp);
-    const int hb = r16 >> 3;
     // The accumulators go through an LDS tile [head][channel] so that every lane stores 16 bytes and a store
     // instruction covers two whole heads (a lane holds single channels of four heads).  The tile takes the start of
     // the LDS, which holds nothing the epilogue needs (q staging, page staging); rows are 16 bytes longer than a
@@ -1016,23 +1023,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     static_assert(sizeof(LdsExtra<KC>) + sizeof(float) * kPageTokens * kGroups + sizeof(uint4) * kPvChunks >= 8 * kOutRow * sizeof(float),
                   "the output tile must fit in what precedes qo (= zl()) and alpha in Lds");
     float *tile = reinterpret_cast<float *>(&lds);
-    if ((q4 >> 1) == hb) {   // the quadrants whose rows and columns belong to the same pair of groups
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int head = 4 * (q4 & 1) + i;
+    for (int i = 0; i < 4; ++i) {
+        const int head = 4 * (q4 & 1) + i, half = q4 >> 1;   // lanes 0..31 go on with the lower channels, 32..63 with the upper
+        const float2 zsum = *reinterpret_cast<const float2 *>(&lds.zl()[head][2 * half]);
 #pragma unroll
-            for (int gg = 0; gg < 2; ++gg) {
-                const int g = 2 * hb + gg;
-                const float zsum = lds.zl()[head][g];
-#pragma unroll
-                for (int chunk = 0; chunk < 2; ++chunk)
-#pragma unroll
-                    for (int cc = 0; cc < 2; ++cc) {
-                        const int comp = 2 * gg + cc;
-                        tile[head * kOutRow + 64 * hb + 16 * comp + (chunk ? r16 ^ 8 : r16)] = st.acc[chunk][comp][i] * unscale + zsum;
-                    }
-            }
-        }
+        for (int comp = 0; comp < 4; ++comp)
+            tile[head * kOutRow + 64 * half + 16 * comp + r16] = fmaf(add_pieces(st.acc[0][comp][i], st.acc[1][comp][i]), unscale, comp < 2 ? zsum.x : zsum.y);
     }
     if (lane < 8 && lane < R) {
         const size_t ph = (size_t)slot * n_q_heads + kvh * R + lane;
