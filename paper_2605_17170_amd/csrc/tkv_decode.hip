@@ -165,15 +165,8 @@ __device__ __forceinline__ float add_pieces(float x, float y)
 // The value of another lane of the same row of 16 lanes: CTRL is a DPP pattern under which every lane has a source.
 template <int CTRL> __device__ __forceinline__ int row_dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
 template <int CTRL> __device__ __forceinline__ float row_dpp(float v) { return __builtin_bit_cast(float, row_dpp<CTRL>(__builtin_bit_cast(int, v))); }
-// Sum / maximum over a row of 16 lanes, in every lane of the row: neighbours, pairs, quads, halves
+// Maximum over a row of 16 lanes, in every lane of the row: neighbours, pairs, quads, halves
 // (quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror).
-__device__ __forceinline__ float row_sum(float v)
-{
-    v += row_dpp<0xB1>(v);
-    v += row_dpp<0x4E>(v);
-    v += row_dpp<0x141>(v);
-    return v + row_dpp<0x140>(v);
-}
 __device__ __forceinline__ int row_max(int v)
 {
     v = max(v, row_dpp<0xB1>(v));
@@ -214,13 +207,13 @@ struct WaveState {
 constexpr int kQyStride = 25, kQyZero0 = 24, kQyZero1 = 16;
 constexpr int kPvZ = 0, kPvS = 32, kPvZero = 64, kPvOne = 65, kPvChunks = 66;
 
-// What only one of the two kernels keeps in LDS: the staged q (per-token keys; the other kernel borrows the page
-// staging area for it), the second q operand (per-channel INT2 keys).
-template <bool KC> struct LdsExtra {
-    alignas(16) _Float16 qf[8][kHeadDim + 8];            // q * 2^E per head and channel (qf_chunk), kept for the whole item
-};
+// Entries of the q operand tables: 16 bytes for (group, half group, channel octet sub, head).  With per-channel INT2 keys
+// they lie densely; lane (r16, q4) of an MFMA reads entry (g, q4 >> 1, q4 & 1, r16 & 7).
+constexpr int kQcEntries = kGroups * 32;
+// What only the kernel for per-channel INT2 keys keeps in LDS: the second q operand.
+template <bool KC> struct LdsExtra {};
 template <> struct LdsExtra<true> {
-    alignas(16) uint4 qp[kGroups][64];                   // q * 2^E in the slot order of qo, without the slot factors
+    alignas(16) uint4 qp[kQcEntries];                    // q * 2^E in the slot order of qo, without the slot factors
 };
 template <bool KC> struct alignas(16) Lds : LdsExtra<KC> {
     // Per-channel INT2 keys reuse ks while INT2 pages run: the K scale plane (512 B) and the K zero plane (512 B) of
@@ -232,84 +225,76 @@ template <bool KC> struct alignas(16) Lds : LdsExtra<KC> {
     //   kPvS + (blk*4 + quad)*4 + g   V scale * 2^(kVExp - pos)
     //   kPvZero   zeros;   kPvOne   ones
     alignas(16) uint4 pv[kPvChunks];
-    // B operands of the QK^T MFMAs: per group and lane (per-channel INT2 keys), or 8 x (16 entries + zeros) (build_q_operand)
-    alignas(16) uint4 qo[KC ? kGroups : 2][KC ? 64 : 4 * kQyStride];
+    // B operands of the QK^T MFMAs (build_q_operand): 8 x (16 entries + zeros), or, per-channel INT2 keys, kQcEntries
+    alignas(16) uint4 qo[8 * kQyStride];
+    static_assert(8 * kQyStride >= kQcEntries, "either table");
+    // group sums of q (prologue: per head 12 fp16, the pieces of the four sums); zero-point sums of the groups and the
+    // denominator (epilogue: per head 5 floats)
+    alignas(16) float zl[8][8];
     alignas(16) float alpha[16];
-    // [head][8] floats of the prologue (group sums of q) and the epilogue (zero-point sums, denominator): the q
-    // operands are not live then
-    __device__ __forceinline__ float (*zl())[8] { return reinterpret_cast<float(*)[8]>(qo); }
     __device__ __forceinline__ uint4 *kc_scale() { return reinterpret_cast<uint4 *>(ks); }
     __device__ __forceinline__ uint4 *kc_zero() { return reinterpret_cast<uint4 *>(ks) + 32; }
 };
 
-// q * 2^E is staged in LDS as fp16 [head][128 channels].  The operand build reads the same channels of all eight
-// heads at once; with plain 256-byte rows those reads would all fall on the same banks.  The kernel for per-token
-// keys, which has the room, makes the rows 272 bytes long; the kernel for per-channel INT2 keys keeps 256-byte rows
-// (the staging area it borrows holds no more) and stores the 16-byte chunks of a row at chunk ^ head instead.
-// Byte offset of 16-byte chunk `chunk` (8 channels) of head `h`:
-template <bool KC> __device__ __forceinline__ int qf_chunk(int h, int chunk)
+// q of one work item: lane (head = lane / 8, c = lane % 8) holds channels 8 c .. 8 c + 7 and 64 + 8 c .. of its head, two
+// loads of whole lines.  Channel octet c of half j lies in group 2 j + c / 4, half group (c / 2) % 2, octet c % 2.
+// (Staged in LDS as rows and read back in operand order, q cost 24 LDS instructions more, a round trip and, with a row sum of
+// four DPP steps per head, four times the additions.)
+struct QRegs { uint4 x[2]; };
+__device__ __forceinline__ void load_q(QRegs &qr, const uint16_t *__restrict__ q_head /* this lane's head */, int lane)
 {
-    return KC ? h * 256 + ((chunk ^ h) << 4) : h * 272 + (chunk << 4);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) qr.x[j] = reinterpret_cast<const uint4 *>(q_head)[8 * j + (lane & 7)];
 }
-// lane l of a wavefront holds channels 2l, 2l+1 of a head as an fp16 pair
-template <bool KC> __device__ __forceinline__ void qf_store(void *qf, int h, int lane, uint32_t pair)
-{
-    *reinterpret_cast<uint32_t *>(static_cast<char *>(qf) + qf_chunk<KC>(h, lane >> 2) + ((lane & 3) << 2)) = pair;
-}
+__device__ __forceinline__ float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
 
-// B operand of the QK^T MFMAs for one width, kept in LDS: 4 registers of fp16 pairs holding
-// q' = q * 2^E * 2^-pos in the slot order the unpack produces.
-//  - per-channel INT2 keys: per group and lane (head columns 8..15 repeat heads 0..7), plus the copy without
-//    slot factors;
+// B operands of the QK^T MFMAs for one width, kept in LDS: entries of eight fp16 holding q' = q * 2^E * 2^-pos in the slot
+// order the unpack produces.  INT4 words list the eight channels of an octet, register k holds channels k and k + 4; INT2
+// words list the sixteen of a half group, an entry has channels 4 sub + k and 8 + 4 sub + k: the lanes of the two octets
+// trade four channels.
+//  - per-channel INT2 keys: dense entries, plus the copy without slot factors;
 //  - otherwise (two token sets, see compute_page): per (group, half group) one entry per (channel octet sub,
 //    head) and an entry of zeros, which the lanes whose k-slots belong to the other token set read.
 // The slot factors are powers of two and q * 2^E has 8 significant bits: the fp16 products are exact unless they
 // fall into the subnormals, where they round once.
 template <int BITS, bool KC>
-__device__ __forceinline__ void build_q_operand(const void *qf /* the staged q (qf_chunk) */, int h /* this lane's head */,
-                                               int q4, int lane, Lds<KC> &lds)
+__device__ __forceinline__ void build_q_operand(const QRegs &qr, float two_e, int lane, Lds<KC> &lds)
 {
-    const char *qb = static_cast<const char *>(qf);
-    // INT2 words: registers (crumb 4*sub+k, crumb 8+4*sub+k) * 2^-(2k+3), k = 0..3, of 16-channel word hg of a group
-    auto int2_pairs = [&](int g, int hg, int sub, uint32_t (&pr)[4]) {
-        const uint2 x = *reinterpret_cast<const uint2 *>(qb + qf_chunk<KC>(h, g * 4 + 2 * hg) + 8 * sub);       // channels 4*sub + 0..3
-        const uint2 y = *reinterpret_cast<const uint2 *>(qb + qf_chunk<KC>(h, g * 4 + 2 * hg + 1) + 8 * sub);   // channels 8 + 4*sub + 0..3
-        pr[0] = __builtin_amdgcn_perm(y.x, x.x, 0x05040100u);
-        pr[1] = __builtin_amdgcn_perm(y.x, x.x, 0x07060302u);
-        pr[2] = __builtin_amdgcn_perm(y.y, x.y, 0x05040100u);
-        pr[3] = __builtin_amdgcn_perm(y.y, x.y, 0x07060302u);
-    };
-    constexpr uint32_t kSlot2[4] = {0x30003000u, 0x28002800u, 0x20002000u, 0x18001800u};   // fp16 2^-3, 2^-5, 2^-7, 2^-9 twice
-    if constexpr (KC && BITS == 2) {
+    const int head = lane >> 3, sub = lane & 1, hg = (lane >> 1) & 1;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            uint32_t rp[4];
-            int2_pairs(g, q4 >> 1, q4 & 1, rp);   // the unpack leaves the field of slot k at bit 2k + 3 (see compute_page)
-            lds.qo[g][lane] = make_uint4(pk_mul(rp[0], kSlot2[0]), pk_mul(rp[1], kSlot2[1]), pk_mul(rp[2], kSlot2[2]), pk_mul(rp[3], kSlot2[3]));
-            lds.qp[g][lane] = make_uint4(rp[0], rp[1], rp[2], rp[3]);
-        }
-    } else {
-        // 8 x 16 entries, two per lane: lane (sub, head, g) makes those of the two halves of group g
-        uint4 *qy = reinterpret_cast<uint4 *>(lds.qo);
-        const int sub = (lane >> 3) & 1, g = q4;
+    for (int j = 0; j < 2; ++j) {
+        const int g = 2 * j + ((lane >> 2) & 1);
+        uint32_t x[2] = {qr.x[j].x, qr.x[j].y}, y[2] = {qr.x[j].z, qr.x[j].w};
+        if (BITS == 2) {
 #pragma unroll
-        for (int hg = 0; hg < 2; ++hg) {
-            uint32_t r[4];
-            if (BITS == 4) {
-                // registers: (n0,n4) (n1,n5)/16 (n2,n6) (n3,n7)/16 of the 8-channel word 2*hg + sub of the group
-                const uint4 c = *reinterpret_cast<const uint4 *>(qb + qf_chunk<KC>(h, g * 4 + 2 * hg + sub));   // channels (0,1) (2,3) (4,5) (6,7)
-                r[0] = __builtin_amdgcn_perm(c.z, c.x, 0x05040100u);
-                r[1] = pk_mul(__builtin_amdgcn_perm(c.z, c.x, 0x07060302u), 0x2c002c00u);
-                r[2] = __builtin_amdgcn_perm(c.w, c.y, 0x05040100u);
-                r[3] = pk_mul(__builtin_amdgcn_perm(c.w, c.y, 0x07060302u), 0x2c002c00u);
-            } else {
-                int2_pairs(g, hg, sub, r);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) r[k] = pk_mul(r[k], kSlot2[k]);
+            for (int i = 0; i < 2; ++i) {
+                const uint32_t other = (uint32_t)row_dpp<0xB1>((int)(sub ? x[i] : y[i]));
+                x[i] = sub ? other : x[i];
+                y[i] = sub ? y[i] : other;
             }
-            qy[(g * 2 + hg) * kQyStride + (lane & 15)] = make_uint4(r[0], r[1], r[2], r[3]);
         }
-        if (lane < 16) qy[(lane & 7) * kQyStride + (lane < 8 ? kQyZero0 : kQyZero1)] = make_uint4(0u, 0u, 0u, 0u);
+        auto pair = [&](int k, float f) {   // channels k of x and y, times f
+            return (k & 1) ? pack_h2(bf16_hi(x[k >> 1]) * f, bf16_hi(y[k >> 1]) * f) : pack_h2(bf16_lo(x[k >> 1]) * f, bf16_lo(y[k >> 1]) * f);
+        };
+        uint32_t r[4];
+        if constexpr (KC && BITS == 2) {
+            // the unpack leaves the field of slot k at bit 2k + 3 (see compute_page)
+            constexpr uint32_t kSlot2[4] = {0x30003000u, 0x28002800u, 0x20002000u, 0x18001800u};   // fp16 2^-3, 2^-5, 2^-7, 2^-9 twice
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[k] = pair(k, two_e);
+            const int e = g * 32 + hg * 16 + sub * 8 + head;
+            lds.qp[e] = make_uint4(r[0], r[1], r[2], r[3]);
+            lds.qo[e] = make_uint4(pk_mul(r[0], kSlot2[0]), pk_mul(r[1], kSlot2[1]), pk_mul(r[2], kSlot2[2]), pk_mul(r[3], kSlot2[3]));
+        } else {
+            // INT4: fields at bits 0 and 4 of a half, in turn; INT2: at bit 2k + 3
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r[k] = pair(k, two_e * (BITS == 4 ? ((k & 1) ? 0.0625f : 1.0f) : 0.125f / (float)(1 << (2 * k))));
+            lds.qo[(g * 2 + hg) * kQyStride + sub * 8 + head] = make_uint4(r[0], r[1], r[2], r[3]);
+        }
+    }
+    if constexpr (!(KC && BITS == 2)) {
+        if (lane < 16) lds.qo[(lane & 7) * kQyStride + (lane < 8 ? kQyZero0 : kQyZero1)] = make_uint4(0u, 0u, 0u, 0u);
     }
 }
 
@@ -385,6 +370,7 @@ struct LaneConst {
     int vs_idx;           // 8-byte half chunk of Lds::pv with the staged V scales of (block 0, group 0) of this lane's four tokens
     int tok0;             // two token sets: first token of this lane's four within a 32-token block
     int qy_ent;           // ... entry of this lane in a q operand of the QK^T MFMAs (or one of the two zero entries)
+    int qc_ent;           // per-channel INT2 keys: entry of this lane among those of a group
     float zmul;           // per-channel INT2 keys: 2^-24 in head columns 0..7, 0 in columns 8..15
 };
 
@@ -473,10 +459,10 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
         // (one per 16-token tile) and that of the zero term.
         struct Operands { uint4 qp, qo, zc, sc[2]; } op;
         auto fetch = [&](int g) {
-            op.qo = lds.qo[g][lane];
+            op.qo = lds.qo[g * 32 + lc.qc_ent];
             op.sc[0] = lds.kc_scale()[g * 4 + q4];
             op.sc[1] = lds.kc_scale()[(4 + g) * 4 + q4];
-            op.qp = lds.qp[g][lane];
+            op.qp = lds.qp[g * 32 + lc.qc_ent];
             op.zc = lds.kc_zero()[((r16 >> 3) * 4 + g) * 4 + q4];
         };
         floatx4 z = {0.f, 0.f, 0.f, 0.f};
@@ -532,7 +518,7 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
         // codes of the first token, 16..31 those of the second, and the B operand holds q in the matching half
         // of its k-slots and zeros in the other.  All that follows the MFMAs (K scale, exponentials, weight
         // pieces) is then done once per (token, head).
-        const uint4 *qy = reinterpret_cast<const uint4 *>(lds.qo);
+        const uint4 *qy = lds.qo;
         floatx4 s[2];
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
@@ -827,12 +813,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     )
 {
     __shared__ Lds<KC> lds;
-    // q * 2^E per head and channel (2 KiB of fp16), read while the MFMA operands are built.  With per-channel INT2
-    // keys it lives in the page staging area ks | pv, which is idle then, so that twelve wavefronts fit the LDS of a
-    // compute unit, and is written again before the INT4 operand is built; otherwise it has its own place.
-    void *qf;
-    if constexpr (KC) qf = lds.ks;
-    else qf = lds.qf;
     const int lane = threadIdx.x, r16 = lane & 15, q4 = lane >> 4;
     const int item = blockIdx.y + blockIdx.z * gridDim.y, kvh = blockIdx.x;
     if (item >= n_items) return;
@@ -884,123 +864,115 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     PageRegs<2> s2;
     PageRegs<4> s4;
 
-    // ---- q: load the R heads, common power-of-two normalisation, group sums ----
-    // lane l holds channels 2l, 2l+1 of every head
-    uint32_t q2[8];
-#pragma unroll
-    for (int h = 0; h < 8; ++h)   // (heads beyond R: head 0 again, not used)
-        q2[h] = reinterpret_cast<const uint32_t *>(q + ((size_t)seq * n_q_heads + kvh * R + (h < R ? h : 0)) * kHeadDim)[lane];
-    batch_check(cx, list, batch_ids(cx, list, pb));
-    // (The preparation of q is what a launch of one to three pages per wavefront consists of: no branches that depend on the
-    // lane, no 64-bit arithmetic.  16 contexts of 97 to 6011 tokens 15.4 -> 15.25 us, per-channel keys at 8 x 32768, which
-    // had the most registers to spill, 54.7 -> 53.0.)
-    // Largest exponent of the heads, from the bf16 bits: |x| as an integer, plus one in the exponent, which makes NaN and
-    // infinities negative: they do not count (a head that holds one must not spoil the others)
-    typedef short short2_t __attribute__((ext_vector_type(2)));
-    short2_t big = {0, 0};
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-        q2[h] = h < R ? q2[h] : 0;
-        big = __builtin_elementwise_max(big, __builtin_bit_cast(short2_t, ((q2[h] & 0x7fff7fffu) + 0x00800080u)));
-    }
-    const int top = wave_max(big[0] > big[1] ? big[0] : big[1]);   // 0x80 where all are zero
-    // 2^E with max|q| * 2^E in [2^14, 2^15); E clamped so every factor stays a normal fp32
-    int E = (KC ? kKcQExp : 15) - ((top >> 7) - 127);   // max|q| = m * 2^(exponent - 126), m in [0.5, 1)
-    E = E > 100 ? 100 : (E < -100 ? -100 : E);
-    if (top <= 0x80) E = 0;
-    const float two_e = ldexpf(1.0f, E);
+    // What a wavefront of few pages does is a chain of loads (arguments -> item -> counts -> page ids and q -> record) and the
+    // preparation of q.  The first record is requested when the exponents and sums of q are known, ahead of the operand
+    // tables: asked for any earlier, the records of the wavefronts that came first stand in front of the q and the page ids
+    // of the others of the compute unit (16 contexts of 97 to 6011 tokens 15.4 us asked with the page ids there, 14.7 here,
+    // 14.9 behind the tables; four-layer step 84.1, 81.8, 83.8).
+    const int first_ids = batch_ids(cx, list, pb);
+    const uint16_t *q_head = q + ((size_t)seq * n_q_heads + kvh * R + ((lane >> 3) & (R - 1))) * kHeadDim;   // columns beyond R repeat heads
+    QRegs qr;
+    load_q(qr, q_head, lane);
+    batch_check(cx, list, first_ids);
+
+    float two_e;
     LaneConst lc;
-    lc.F = ldexpf(1.0f, 24 - E);
-    lc.kappa = kappa;
-    lc.vmul01 = lc.vmul23 = 0;
-    lc.zmul = r16 >= 8 ? 0.0f : 0x1p-24f;
-    lc.vs_idx = 2 * (kPvS + q4 * 4) + (r16 >> 3);
-    lc.tok0 = 16 * (r16 >> 3) + 4 * q4;
-    static_assert(kQyZero0 == 24 && kQyZero1 == 16, "entry 24 - 8 * sub holds the zeros of the lanes of octet sub");
-    const int other_set = -(int)((r16 >> 3) != (q4 >> 1));
-    lc.qy_ent = (((q4 & 1) * 8 + (r16 & 7)) & ~other_set) | ((kQyZero0 - 8 * (q4 & 1)) & other_set);
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-        lc.zp_idx[blk] = r16 < 4 ? kPvZ + (blk * 4 + q4) * 4 + r16 : (r16 == 4 ? kPvOne : kPvZero);
-    }
-    if (lane < 2) {
-        const uint32_t c = lane == 1 ? 0x3c003c00u : 0u;
-        lds.pv[kPvZero + lane] = make_uint4(c, c, c, c);
-    }
-    // q * 2^E to LDS; sums of q over the groups, lanes 16 g .. 16 g + 15 hold group g.  The sums are of q itself, in 32 bits:
-    // they meet zero-points of tens.  (From the staged q on the matrix core, numbers far below the largest of their group
-    // or of the heads lose bits, and it is no faster: 16 contexts of 97 to 6011 tokens 15.4 us either way.)
-    float qsum[8];
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-        const float even = __uint_as_float(q2[h] << 16), odd = __uint_as_float(q2[h] & 0xffff0000u);
-        qf_store<KC>(qf, h, lane, pack_h2(even * two_e, odd * two_e));   // exact down to 2^-24: q has 8 significant bits
-        qsum[h] = row_sum(even + odd);
-    }
-    if (r16 == 0)
-#pragma unroll
-        for (int h = 0; h < 8; ++h) lds.zl()[h][q4] = qsum[h];   // [head][group]
-    lds_order();
-    const int hcol = (r16 & 7) & (R - 1);   // head of this lane's column (columns beyond R repeat heads)
     half8 qz;
-    {
+    WaveState st;
+    // ---- q: common power-of-two normalisation, group sums (no branches that depend on the lane, no 64-bit arithmetic) ----
+    // (Called in the branch of the item's first width: in front of the branches, its registers live through both page loops
+    // and are spilled, 16 short contexts 14.7 -> 15.2 us.)
+    auto prepare_q = [&]() {
+        const uint32_t d[8] = {qr.x[0].x, qr.x[0].y, qr.x[0].z, qr.x[0].w, qr.x[1].x, qr.x[1].y, qr.x[1].z, qr.x[1].w};
+        // Largest exponent of the heads, from the bf16 bits: |x| as an integer, plus one in the exponent, which makes NaN and
+        // infinities negative: they do not count (a head that holds one must not spoil the others)
+        typedef short short2_t __attribute__((ext_vector_type(2)));
+        short2_t big = {0, 0};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) big = __builtin_elementwise_max(big, __builtin_bit_cast(short2_t, ((d[i] & 0x7fff7fffu) + 0x00800080u)));
+        const int top = wave_max(big[0] > big[1] ? big[0] : big[1]);   // 0x80 where all are zero
+        // 2^E with max|q| * 2^E in [2^14, 2^15); E clamped so every factor stays a normal fp32
+        int E = (KC ? kKcQExp : 15) - ((top >> 7) - 127);   // max|q| = m * 2^(exponent - 126), m in [0.5, 1)
+        E = E > 100 ? 100 : (E < -100 ? -100 : E);
+        if (top <= 0x80) E = 0;
+        two_e = ldexpf(1.0f, E);
+        lc.F = ldexpf(1.0f, 24 - E);
+        lc.kappa = kappa;
+        lc.vmul01 = lc.vmul23 = 0;
+        lc.zmul = r16 >= 8 ? 0.0f : 0x1p-24f;
+        lc.vs_idx = 2 * (kPvS + q4 * 4) + (r16 >> 3);
+        lc.tok0 = 16 * (r16 >> 3) + 4 * q4;
+        static_assert(kQyZero0 == 24 && kQyZero1 == 16, "entry 24 - 8 * sub holds the zeros of the lanes of octet sub");
+        const int other_set = -(int)((r16 >> 3) != (q4 >> 1));
+        lc.qy_ent = (((q4 & 1) * 8 + (r16 & 7)) & ~other_set) | ((kQyZero0 - 8 * (q4 & 1)) & other_set);
+        lc.qc_ent = q4 * 8 + (r16 & 7);
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+            lc.zp_idx[blk] = r16 < 4 ? kPvZ + (blk * 4 + q4) * 4 + r16 : (r16 == 4 ? kPvOne : kPvZero);
+        }
+        if (lane < 2) {
+            const uint32_t c = lane == 1 ? 0x3c003c00u : 0u;
+            lds.pv[kPvZero + lane] = make_uint4(c, c, c, c);
+        }
+        // The sums of q over this lane's two groups, in 32 bits: they meet zero-points of tens.  (From the staged q on the
+        // matrix core, numbers far below the largest of their group or of the heads lose bits, and it is no faster.)  As
+        // three fp16 pieces to LDS, [head][hi of the four groups, mid, lo], one by each of three lanes of a quad.
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float sum = ((bf16_lo(d[4 * j]) + bf16_hi(d[4 * j])) + (bf16_lo(d[4 * j + 1]) + bf16_hi(d[4 * j + 1]))) +
+                        ((bf16_lo(d[4 * j + 2]) + bf16_hi(d[4 * j + 2])) + (bf16_lo(d[4 * j + 3]) + bf16_hi(d[4 * j + 3])));
+            sum += row_dpp<0xB1>(sum);
+            sum += row_dpp<0x4E>(sum);
+            const _Float16 hi = (_Float16)sum;
+            const float r1 = sum - (float)hi;
+            const _Float16 mid = (_Float16)r1, lo = (_Float16)(r1 - (float)mid);
+            const int piece = lane & 3;
+            if (piece < 3) reinterpret_cast<_Float16 *>(lds.zl[lane >> 3])[4 * piece + 2 * j + ((lane >> 2) & 1)] = piece == 0 ? hi : (piece == 1 ? mid : lo);
+        }
+        lds_order();
         // Z-term B operand (two token sets: the k-slots of a column's own set carry the pieces, the others zeros):
         // slots 0..3 / 4..7 of the first octet = hi / mid pieces of the four group sums, slots 0..3 of the second
-        // octet = lo pieces
-        const float4 gs = reinterpret_cast<const float4 *>(lds.zl()[hcol])[0];
-        const float sums[4] = {gs.x, gs.y, gs.z, gs.w};
-        _Float16 hi[4], mid[4], lo[4];
+        // octet = lo pieces.  Masks and no branches.
+        const uint4 z4 = reinterpret_cast<const uint4 *>(lds.zl[r16 & 7])[q4 & 1];
+        const uint32_t own = (r16 >> 3) == (q4 >> 1) ? 0xffffffffu : 0u, first = (q4 & 1) ? 0u : own;
+        qz = as_half8(z4.x & own, z4.y & own, z4.z & first, z4.w & first);
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            hi[g] = (_Float16)sums[g];
-            const float r1 = sums[g] - (float)hi[g];
-            mid[g] = (_Float16)r1;
-            lo[g] = (_Float16)(r1 - (float)mid[g]);
-        }
-        auto pair = [](_Float16 a, _Float16 b) { const half2_t v = {a, b}; return __builtin_bit_cast(uint32_t, v); };
-        const uint32_t own = (r16 >> 3) == (q4 >> 1) ? 0xffffffffu : 0u;                    // masks and no branches
-        const uint32_t first = (q4 & 1) ? 0u : own, second = (q4 & 1) ? own : 0u;
-        qz = as_half8((pair(hi[0], hi[1]) & first) | (pair(lo[0], lo[1]) & second), (pair(hi[2], hi[3]) & first) | (pair(lo[2], lo[3]) & second),
-                      pair(mid[0], mid[1]) & first, pair(mid[2], mid[3]) & first);
-    }
+        for (int j = 0; j < 8; ++j) st.acc[j >> 2][j & 3] = floatx4{0.f, 0.f, 0.f, 0.f};
+        st.zp = floatx4{0.f, 0.f, 0.f, 0.f};
+        st.m_ref = -INFINITY;
+        st.sat = 0;
+    };
 
-    WaveState st;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) st.acc[j >> 2][j & 3] = floatx4{0.f, 0.f, 0.f, 0.f};
-    st.zp = floatx4{0.f, 0.f, 0.f, 0.f};
-    st.m_ref = -INFINITY;
-    st.sat = 0;
-
-    batch_finish(cx, list);
     if (has2) {
-        build_q_operand<2, KC>(qf, hcol, q4, lane, lds);
+        prepare_q();
+        __builtin_amdgcn_sched_barrier(0);
+        const Record rec = batch_record<2>(cx, list, pb, true);
+        load_page_k<2, KC>(s2, rec, lane);
+        load_page_v<2>(s2, rec, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        build_q_operand<2, KC>(qr, two_e, lane, lds);
+        batch_finish(cx, list);
         LaneConst lc2 = lc;
         if constexpr (KC) {
             lc2.kappa = lc.kappa * lc.F;   // the power of two that the K scale carries otherwise
         }
-        const Record rec = batch_record<2>(cx, list, pb, true);
-        load_page_k<2, KC>(s2, rec, lane);
-        load_page_v<2>(s2, rec, lane);
         lds_order();
         run_pages<2, KC>(cx, list, pb, e2, s2, qz, lc2, st, lds);
     }
     if (has4) {
-        batch_seek(cx, list, b4);
+        if (has2) {
+            batch_seek(cx, list, b4);
+            load_q(qr, q_head, lane);   // (not kept through the INT2 pages)
+        } else {
+            prepare_q();
+            batch_finish(cx, list);
+        }
+        __builtin_amdgcn_sched_barrier(0);
         const Record rec = batch_record<4>(cx, list, b4, true);
         load_page_k<4, KC>(s4, rec, lane);
         load_page_v<4>(s4, rec, lane);
-        if (KC && has2) {   // the INT2 pages have used that memory since
-            lds_order();
-#pragma unroll
-            for (int h = 0; h < 8; ++h) {
-                uint32_t two = 0;
-                if (h < R) two = reinterpret_cast<const uint32_t *>(q + ((size_t)seq * n_q_heads + kvh * R + h) * kHeadDim)[lane];
-                const float q0 = __uint_as_float(two << 16) * two_e, q1 = __uint_as_float(two & 0xffff0000u) * two_e;
-                qf_store<KC>(qf, h, lane, pack_h2(q0, q1));
-            }
-            lds_order();
-        }
-        build_q_operand<4, KC>(qf, hcol, q4, lane, lds);
+        __builtin_amdgcn_sched_barrier(0);
+        build_q_operand<4, KC>(qr, two_e, lane, lds);
         lds_order();
         run_pages<4, KC>(cx, list, b4, pe, s4, qz, lc, st, lds);
     }
@@ -1011,29 +983,28 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     lds_order();
     if (q4 < 2 && r16 < 5)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lds.zl()[4 * q4 + i][r16] = st.zp[i];
+        for (int i = 0; i < 4; ++i) lds.zl[4 * q4 + i][r16] = st.zp[i];
     if (q4 == 0 && r16 < 8) lds.alpha[r16] = st.m_ref;
     lds_order();
     const float unscale = ldexpf(1.0f, 24 - kVExp);
     // The accumulators go through an LDS tile [head][channel] so that every lane stores 16 bytes and a store
     // instruction covers two whole heads (a lane holds single channels of four heads).  The tile takes the start of
-    // the LDS, which holds nothing the epilogue needs (q staging, page staging); rows are 16 bytes longer than a
+    // the LDS, which holds nothing the epilogue needs (page staging, q operands); rows are 16 bytes longer than a
     // head so that heads h and h + 4, written by the same instruction, fall on different banks.
     constexpr int kOutRow = kHeadDim + 4;
-    static_assert(sizeof(LdsExtra<KC>) + sizeof(float) * kPageTokens * kGroups + sizeof(uint4) * kPvChunks >= 8 * kOutRow * sizeof(float),
-                  "the output tile must fit in what precedes qo (= zl()) and alpha in Lds");
+    static_assert(sizeof(lds.ks) + sizeof(lds.pv) + sizeof(lds.qo) >= 8 * kOutRow * sizeof(float), "the output tile must fit in what precedes zl and alpha in Lds");
     float *tile = reinterpret_cast<float *>(&lds);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int head = 4 * (q4 & 1) + i, half = q4 >> 1;   // lanes 0..31 go on with the lower channels, 32..63 with the upper
-        const float2 zsum = *reinterpret_cast<const float2 *>(&lds.zl()[head][2 * half]);
+        const float2 zsum = *reinterpret_cast<const float2 *>(&lds.zl[head][2 * half]);
 #pragma unroll
         for (int comp = 0; comp < 4; ++comp)
             tile[head * kOutRow + 64 * half + 16 * comp + r16] = fmaf(add_pieces(st.acc[0][comp][i], st.acc[1][comp][i]), unscale, comp < 2 ? zsum.x : zsum.y);
     }
     if (lane < 8 && lane < R) {
         const size_t ph = (size_t)slot * n_q_heads + kvh * R + lane;
-        reinterpret_cast<float2 *>(ml_ws)[ph] = make_float2(lds.alpha[lane], lds.zl()[lane][4]);
+        reinterpret_cast<float2 *>(ml_ws)[ph] = make_float2(lds.alpha[lane], lds.zl[lane][4]);
     }
     lds_order();
 #pragma unroll
