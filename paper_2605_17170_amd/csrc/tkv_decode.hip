@@ -5,7 +5,7 @@
 // One wavefront owns one (work item, kv head): a contiguous range of one
 // sequence's page list.  All query heads that share the kv head (up to 8)
 // are processed together so the packed KV bytes are read from HBM once; the
-// partials (m, l, acc) of the items are merged by tkv_reduce_rows_kernel.
+// partials (m, l, acc) of the items are merged by tkv_merge_kernel or tkv_reduce_rows_kernel.
 //
 // Matrix cores do both contractions (v_mfma_f32_16x16x32_f16), fp32 accumulate,
 // and the packed codes are never expanded by arithmetic: a masked 16-bit field
@@ -323,6 +323,14 @@ __device__ __forceinline__ uint2 buffer_load8(Record r, int lane_offset, int pla
     const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, lane_offset, plane, 0);
     return make_uint2(v.x, v.y);
 }
+// (whole offsets in the vector register: with part of it in a scalar one the range check is not of the sum)
+__device__ __forceinline__ uint2 buffer_load8_once(Record r, uint32_t offset)
+{
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)offset, 0, 2 /* nt */);
+    return make_uint2(v.x, v.y);
+}
+__device__ __forceinline__ uint32_t buffer_load4_once(Record r, uint32_t offset) { return __builtin_amdgcn_raw_buffer_load_b32(r, (int)offset, 0, 2 /* nt */); }
 __device__ __forceinline__ uint4 buffer_load16_once(Record r, int lane_offset, int plane)   // non-temporal, as load_once
 {
     const uint4v v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_offset, plane, 2 /* nt */);
@@ -1019,13 +1027,142 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 
 // D7: out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i over the items of a sequence (Sec. 3.2.3: the
 // splits are merged by online log-sum-exp).
-// One workgroup of TH threads per (sequence, query head, one of SL channel slices).  32 / SL lanes own an item at a
-// time: their 16-byte loads are the item's accumulators of the slice, so every partial is read once with 128-bit
-// loads and TH * SL / 32 items are in flight per workgroup round.  Each such lane group keeps a running (M, l, acc);
-// the groups are merged through LDS by the first wavefront.  SL = 1, TH = 256 when a sequence has tens of items;
-// SL = 4, TH = 512 (four workgroups per head, 64 item slots each) when it has hundreds, as a single long sequence
-// with one kv head does.
-template <int SL, int TH>
+// Two kernels: this one for sequences of up to a few hundred items, the next for more.
+//
+// A workgroup of four wavefronts per (sequence, query head, 2 / VEC halves of the channels), a lane owns VEC channels.  Each
+// wavefront takes a quarter of the items; lane l weighs item l, and an item's accumulators are one load of whole lines.
+// What bounds it is latency (bytes alone would take 1 to 2 us): the chain is item list -> (m, l) pairs and accumulators of 32
+// items at once -> weights -> sum -> one exchange through LDS, which a sequence of few items does without.
+// Against the kernel below with 8 items in flight per workgroup and a running maximum per item, us alone, 64 heads, sequences x
+// items each: 8 x 4 2.6 -> 2.25, 32 x 12 4.6 -> 4.4, 8 x 24 4.4 -> 3.4, 8 x 48 5.1 -> 4.6, 4 x 96 4.9 -> 4.2, 4 x 192 8.8 -> 6.8;
+// behind the split kernel, 16 short contexts 14.7 -> 14.3, four-layer step 82.7 -> 79.2.
+constexpr int kMergeWaves = 4, kMergeBatch = 32;
+constexpr int kMergeAlone = 24;   // up to that many items the first wavefront does the work alone
+__device__ __forceinline__ float wave_sum(float v)   // four DPP steps in the rows of 16 lanes, then the four rows
+{
+    v += row_dpp<0xB1>(v);
+    v += row_dpp<0x4E>(v);
+    v += row_dpp<0x141>(v);
+    v += row_dpp<0x140>(v);
+    const int i = __float_as_int(v);
+    return (__int_as_float(__builtin_amdgcn_readlane(i, 0)) + __int_as_float(__builtin_amdgcn_readlane(i, 16))) +
+           (__int_as_float(__builtin_amdgcn_readlane(i, 32)) + __int_as_float(__builtin_amdgcn_readlane(i, 48)));
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = fmaxf(v, row_dpp<0xB1>(v));
+    v = fmaxf(v, row_dpp<0x4E>(v));
+    v = fmaxf(v, row_dpp<0x141>(v));
+    v = fmaxf(v, row_dpp<0x140>(v));
+    const int i = __float_as_int(v);
+    return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(i, 0)), __int_as_float(__builtin_amdgcn_readlane(i, 16))),
+                 fmaxf(__int_as_float(__builtin_amdgcn_readlane(i, 32)), __int_as_float(__builtin_amdgcn_readlane(i, 48))));
+}
+// 2^(m - M), and 0 for m = -inf: an item without tokens has m = -inf, l = 0 and weighs nothing
+__device__ __forceinline__ float merge_weight(float m, float M) { return m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M); }
+
+template <int VEC>
+__global__ __launch_bounds__(64 * kMergeWaves) void tkv_merge_kernel(
+    const float *__restrict__ acc_ws, const float *__restrict__ ml_ws, const int32_t *__restrict__ seq_item_indptr,
+    int batch, int n_q_heads, float *__restrict__ out)
+{
+    constexpr int kParts = 2 / VEC;
+    __shared__ float num_s[kMergeWaves][64 * VEC];
+    __shared__ float2 ml_s[kMergeWaves];
+    const int b = blockIdx.y + blockIdx.z * gridDim.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (b >= batch) return;
+    const int h = blockIdx.x / kParts, c0 = (blockIdx.x % kParts) * 64 + lane * VEC;   // this lane's first channel
+    int i0 = seq_item_indptr[b], i1 = seq_item_indptr[b + 1];
+    const bool alone = i1 - i0 <= kMergeAlone;
+    if (!alone) {
+        const int per = (i1 - i0 + kMergeWaves - 1) / kMergeWaves;
+        i0 += wave * per;
+        i1 = i0 + per < i1 ? i0 + per : i1;
+    } else if (wave > 0) {
+        return;
+    }
+    const uint32_t stride = (uint32_t)n_q_heads * (kHeadDim * 4);
+    float M = -INFINITY, den = 0.0f;
+    float num[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) num[v] = 0.0f;
+    for (int i = i0; i < i1; i += kMergeBatch) {
+        const int n = i1 - i < kMergeBatch ? i1 - i : kMergeBatch;
+        // item i + k of the head at k * stride; those behind the last one lie outside the buffer: zeros, no memory access
+        const float *base = acc_ws + ((size_t)i * n_q_heads + h) * kHeadDim;
+        const Record rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, (uint32_t)(n - 1) * stride + kHeadDim * 4, 0x00027000);
+        float2 ml = make_float2(-INFINITY, 0.0f);
+        if (lane < n) ml = reinterpret_cast<const float2 *>(ml_ws)[(size_t)(i + lane) * n_q_heads + h];
+        float a[kMergeBatch][VEC];
+#pragma unroll
+        for (int g = 0; g < kMergeBatch; g += 8) {
+            if (g > 0 && n <= g) break;
+#pragma unroll
+            for (int k = g; k < g + 8; ++k) {
+                if constexpr (VEC == 2) {
+                    const uint2 t = buffer_load8_once(rows, (uint32_t)(c0 * 4) + k * stride);
+                    a[k][0] = __uint_as_float(t.x);
+                    a[k][VEC - 1] = __uint_as_float(t.y);
+                } else {
+                    a[k][0] = __uint_as_float(buffer_load4_once(rows, (uint32_t)(c0 * 4) + k * stride));
+                }
+            }
+        }
+        const float Mn = fmaxf(M, wave_max(ml.x));
+        const float so = merge_weight(M, Mn), w = merge_weight(ml.x, Mn);
+        den = den * so + wave_sum(w * ml.y);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) num[v] *= so;
+#pragma unroll
+        for (int g = 0; g < kMergeBatch; g += 8) {
+            if (g > 0 && n <= g) break;
+#pragma unroll
+            for (int k = g; k < g + 8; ++k) {
+                const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k));
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) num[v] = fmaf(wk, a[k][v], num[v]);
+            }
+        }
+        M = Mn;
+    }
+    if (!alone) {
+        if (wave > 0) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) num_s[wave][lane * VEC + v] = num[v];
+            if (lane == 0) ml_s[wave] = make_float2(M, den);
+        }
+        __syncthreads();
+        if (wave > 0) return;
+        float2 o[kMergeWaves];
+        float Mg = M;
+#pragma unroll
+        for (int k = 1; k < kMergeWaves; ++k) {
+            o[k] = ml_s[k];
+            Mg = fmaxf(Mg, o[k].x);
+        }
+        const float w0 = merge_weight(M, Mg);
+        den *= w0;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) num[v] *= w0;
+#pragma unroll
+        for (int k = 1; k < kMergeWaves; ++k) {
+            const float wk = merge_weight(o[k].x, Mg);
+            den += wk * o[k].y;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) num[v] += wk * num_s[k][lane * VEC + v];
+        }
+    }
+    const float r = den > 0.0f ? 1.0f / den : 0.0f;
+    float *dst = out + ((size_t)b * n_q_heads + h) * kHeadDim + c0;
+    if constexpr (VEC == 2) *reinterpret_cast<float2 *>(dst) = make_float2(num[0] * r, num[VEC - 1] * r);
+    else dst[0] = num[0] * r;
+}
+
+// Sequences of hundreds of items, as a single long sequence with one kv head has them.  One workgroup of TH threads per
+// (sequence, query head, one of SL channel slices).  32 / SL lanes own an item at a time: their 16-byte loads are the item's
+// accumulators of the slice, so every partial is read once with 128-bit loads and TH * SL / 32 items are in flight per
+// workgroup round.  Each such lane group keeps a running (M, l, acc); the groups are merged through LDS by the first wavefront.
+constexpr int SL = 4, TH = 512;   // four workgroups per head, 64 item slots each
 __global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(
     const float *__restrict__ acc_ws, const float *__restrict__ ml_ws, const int32_t *__restrict__ seq_item_indptr,
     int n_q_heads, float *__restrict__ out)
@@ -1125,13 +1262,21 @@ int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indpt
     (void)desc;
     const float *acc_ws = (const float *)workspace;
     const float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
-    // the item counts are on the device; the average per sequence picks the shape of the reduction
-    if ((int64_t)n_items <= 128 * (int64_t)batch)
-        hipLaunchKernelGGL((tkv_reduce_rows_kernel<1, 256>), dim3((unsigned)(batch * n_q_heads)), dim3(256), 0,
-                           (hipStream_t)stream, acc_ws, ml_ws, seq_item_indptr, n_q_heads, out);
-    else
-        hipLaunchKernelGGL((tkv_reduce_rows_kernel<4, 512>), dim3((unsigned)(batch * n_q_heads * 4)), dim3(512), 0,
-                           (hipStream_t)stream, acc_ws, ml_ws, seq_item_indptr, n_q_heads, out);
+    // The item counts are on the device; the average per sequence picks the kernel.  us alone, 64-slot kernel / merge kernel with 2
+    // channels a lane / with 1: 64 heads, 4 x 192 items 8.8 / 6.8 / 7.5, 4 x 256 10.1 / 8.3 / 9.5, 2 x 384 8.3 / 8.3 / 7.7; 8 heads,
+    // 4 x 192 4.8 / 5.3 / 4.4, 4 x 384 5.1 / 7.0 / 5.8, 1 x 384 3.7 / 5.4 / 4.4.  Two channels a lane where that gives 256 workgroups:
+    // 64 heads, 8 x 48 4.6 against 4.9, 4 x 96 4.2 against 4.6; 8 heads, 4 x 96 3.0 against 2.8.  (32 items of one head are
+    // addressed in 32 bits.)
+    if ((int64_t)n_items <= 256 * (int64_t)batch && n_q_heads <= 1 << 17) {
+        const bool two = (int64_t)batch * n_q_heads >= 256;
+        constexpr int kMaxY = 65535;
+        const dim3 grid((unsigned)n_q_heads * (two ? 1 : 2), (unsigned)(batch < kMaxY ? batch : kMaxY), (unsigned)((batch + kMaxY - 1) / kMaxY));
+        hipLaunchKernelGGL(two ? tkv_merge_kernel<2> : tkv_merge_kernel<1>, grid, dim3(64 * kMergeWaves), 0, (hipStream_t)stream, acc_ws, ml_ws,
+                           seq_item_indptr, batch, n_q_heads, out);
+    } else {
+        hipLaunchKernelGGL(tkv_reduce_rows_kernel, dim3((unsigned)(batch * n_q_heads * SL)), dim3(TH), 0, (hipStream_t)stream, acc_ws, ml_ws,
+                           seq_item_indptr, n_q_heads, out);
+    }
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
 
