@@ -13,8 +13,9 @@
 //    for at once is: the slots, then tags, rows and the V words that may have to be merged;
 //  - K and V apart: a workgroup holds 16 KiB of LDS and eight are resident per compute unit, each in a phase of its
 //    own.  65 536 tokens x 8 heads, inputs not in any cache: 67.2 us with both in one workgroup and 64-byte runs per thread
-//    through registers, 63.1 with rows through LDS (32 KiB, five resident), 59.1 apart (with ordinary stores 60.7);
-//    per-channel keys 69.4 -> 60.1; one token for each of 32 sequences 6.0 -> 4.4.  The launcher says which loads and
+//    through registers, 63.1 with rows through LDS (32 KiB, five resident), 59.1 apart (with ordinary stores 60.7), 58.4 with
+//    one wait per level of the chain;
+//    per-channel keys 69.4 -> 59.1; one token for each of 32 sequences 6.0 -> 4.2.  The launcher says which loads and
 //    which order of the workgroups are taken.
 //
 // K words go straight to HBM (a wavefront's stores for one word index are 256 contiguous bytes, written with
@@ -28,6 +29,8 @@
 //   code = clamp(rint((x - zero) * (1 / scale)), 0, 2^b - 1), 0 if scale == 0.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
+
+#include <type_traits>
 
 #include "tkv_internal.h"
 #include "tkv_layout.h"
@@ -305,17 +308,21 @@ __global__ __launch_bounds__(256) void tkv_append_kernel(
     __shared__ uint4 rows[kPageTokens * kRowPieces];
     const int w = blockIdx.z * 8 + blockIdx.x, head = first_head + (blockIdx.y >> 1);   // grid (8, 2 * heads, blocks of eight pages): see the launcher
     const bool is_v = blockIdx.y & 1;
+    // A launch of a few tokens is a chain of loads: arguments -> page and slots -> tags, rows and words to merge.  All of
+    // a level at once: an argument fetched where it is first used, a wait for the tag ahead of the rows, or for a slot between
+    // two rows, is a round trip more.  (12288 tokens x 8 heads 12.9 -> 12.1 us, 65536 59.8 -> 58.4, per-channel keys 62.0 -> 59.1,
+    // six ragged chunks 10.9 -> 10.2, four-layer step 78.1 -> 76.8.)
+    asm volatile("" :: "s"(pool), "s"(bit_map), "s"(K), "s"(V), "s"(tag_bits), "s"(n_tokens), "s"(work_pages), "s"(work_src), "s"(n_work),
+                 "s"(n_kv_heads), "s"(n_pages_int2), "s"(n_pages_int4), "s"(status));
     if (w >= n_work) return;
-    // All arguments at once: a launch of a few tokens is a chain of dependent loads, and each argument fetched where it
-    // is first used would be one more.
-    asm volatile("" :: "s"(pool), "s"(bit_map), "s"(K), "s"(V), "s"(tag_bits), "s"(status));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t *__restrict__ srcs = work_src + (size_t)w * kPageTokens;
-    const int page = work_pages[w];
     const int src = srcs[lane];   // every wavefront looks at all 64 slots
     int row_src[4];               // and fetches pieces of four rows per lane
 #pragma unroll
     for (int i = 0; i < 4; ++i) row_src[i] = srcs[16 * wave + 4 * i + (lane >> 4)];
+    const int page = ((const __attribute__((address_space(4))) int32_t *)work_pages)[w];
+    asm volatile("" :: "s"(page), "v"(src), "v"(row_src[0]), "v"(row_src[1]), "v"(row_src[2]), "v"(row_src[3]));
     if (page < 0 || page >= n_pages_int2 + n_pages_int4) {
         if (status && tid == 0) atomicOr(status, TKV_STATUS_PAGE_RANGE);
         return;
@@ -323,17 +330,18 @@ __global__ __launch_bounds__(256) void tkv_append_kernel(
     const int bits = page < n_pages_int2 ? 2 : 4;
     uint8_t *rec = pool + record_offset(page, head, n_kv_heads, n_pages_int2);
     const bool in = src >= 0 && src < n_tokens;
-    uint8_t tag = 0;
-    if (in) tag = tag_bits[src];
+    // the tag of this lane's slot; slots without a source lie outside the buffer and read 0
+    const uint8_t tag = __builtin_amdgcn_raw_buffer_load_b8(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(tag_bits), 0, n_tokens, 0x00027000), src, 0, 0);
     const size_t stride = (size_t)n_kv_heads * kHeadDim;
     const uint16_t *from = (is_v ? V : K) + head * kHeadDim;
+    auto fetch_rows = [&](auto once) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (row_src[i] >= 0 && row_src[i] < n_tokens) {
-            const uint16_t *row = from + (size_t)row_src[i] * stride;
-            if (K_ONCE && !is_v) fetch_row_pieces<true>(rows + 16 * wave * kRowPieces, i, row, lane);
-            else fetch_row_pieces<false>(rows + 16 * wave * kRowPieces, i, row, lane);
-        }
+        for (int i = 0; i < 4; ++i)
+            if (row_src[i] >= 0 && row_src[i] < n_tokens)
+                fetch_row_pieces<decltype(once)::value>(rows + 16 * wave * kRowPieces, i, from + (size_t)row_src[i] * stride, lane);
+    };
+    if (K_ONCE && !is_v) fetch_rows(std::true_type());
+    else fetch_rows(std::false_type());
     // the V words of a page that does not arrive whole, in case they change
     uint32_t old[4] = {0, 0, 0, 0};
     auto fetch_old = [&]() {
@@ -383,9 +391,14 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
     // How much of the input leaves the 256 MiB Infinity Cache alone.  Up to 64 MiB of rows are still there from whoever
     // computed them, and ordinary loads find them; larger inputs push each other out, and with the K rows read past the
     // cache the V rows stay in it.  us per call, ordinary / K past the cache / both, same rows again and again | rows not read
-    // for three calls: 12288 tokens x 8 heads 12.0 / 12.5 / 13.0 | 13.1 / 13.6 / 14.1; 20001 22.4 / 23.4 / 25.2 | 27.5 / 23.6 /
-    // 26.1; 65536 47.5 / 49.3 / 56.8 | 61.5 / 59.7 / 57.8; 131072 118 / 94 / 112 | 119 / 116 / 114.
-    const bool k_once = (int64_t)n_tokens * desc->n_kv_heads * (2 * kRowBytes) > (64 << 20);
+    // for three calls: 12288 tokens x 8 heads 11.7 / 11.5 / - | 12.1 / 12.3 / -; 20001 16.6 / 16.5 / 17.7 | 19.1 / 17.3 / 19.3;
+    // 65536 45.6 / 46.9 / 55.9 | 61.0 / 58.4 / 57.9; 131072 120 / 89 / 113 | 121 / 116 / 115.
+    const int64_t row_bytes = (int64_t)n_tokens * desc->n_kv_heads * (2 * kRowBytes);
+    const bool k_once = row_bytes > (64 << 20);
+    // Eight workgroups of 16 KiB are resident per compute unit.  From 768 MiB of rows on, more than any cache keeps, six (by
+    // idle LDS) ask for no more than the memory takes in: 262144 tokens x 8 heads 235 -> 229 us; 131072 116 -> 115, but 89 -> 94
+    // where the cache still holds rows.
+    const unsigned idle_lds = row_bytes > ((int64_t)768 << 20) ? 10200 : 0;
     auto kernel = kc ? (k_once ? tkv_append_kernel<true, true> : tkv_append_kernel<true, false>)
                      : (k_once ? tkv_append_kernel<false, true> : tkv_append_kernel<false, false>);
     // Workgroups are dealt to the eight XCDs in turn: the first grid dimension is the XCD, which reads the rows of all heads
@@ -397,7 +410,7 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
         for (int head = 0; head < desc->n_kv_heads; head += kMaxHeads) {
             const int n = n_work - page < kMaxPages ? n_work - page : kMaxPages;
             const int h = desc->n_kv_heads - head < kMaxHeads ? desc->n_kv_heads - head : kMaxHeads;
-            hipLaunchKernelGGL(kernel, dim3(8, 2 * (unsigned)h, (unsigned)((n + 7) / 8)), dim3(256), 0, (hipStream_t)stream,
+            hipLaunchKernelGGL(kernel, dim3(8, 2 * (unsigned)h, (unsigned)((n + 7) / 8)), dim3(256), idle_lds, (hipStream_t)stream,
                                (uint8_t *)pool, bit_map, (const uint16_t *)K, (const uint16_t *)V, tag_bits, n_tokens, work_pages + page,
                                work_src + (size_t)page * kPageTokens, n, head, desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4,
                                status);
