@@ -990,6 +990,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
         } else {
             prepare_q();
             batch_finish(cx, list);
+            batch_seek(cx, list, b4);   // INT2 positions lie ahead where the table counts INT2 tokens and the pool has no INT2 pages
         }
         __builtin_amdgcn_sched_barrier(0);
         const Record rec = batch_record<4>(cx, list, b4, true);
