@@ -1044,14 +1044,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 
 // D7: out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i over the items of a sequence (Sec. 3.2.3: the
 // splits are merged by online log-sum-exp).
-// Two kernels: this one for sequences of up to a few hundred items, the next for more.
+// Two kernels: this one for batches of up to 128 items per sequence on average, the next for more.
 //
 // A workgroup of four wavefronts per (sequence, query head, 2 / VEC halves of the channels), a lane owns VEC channels.  Each
 // wavefront takes a quarter of the items; lane l weighs item l, and an item's accumulators are one load of whole lines.
 // What bounds it is latency (bytes alone would take 1 to 2 us): the chain is item list -> (m, l) pairs and accumulators of 32
 // items at once -> weights -> sum -> one exchange through LDS, which a sequence of few items does without.
 // Against the kernel below with 8 items in flight per workgroup and a running maximum per item, us alone, 64 heads, sequences x
-// items each: 8 x 4 2.6 -> 2.25, 32 x 12 4.6 -> 4.4, 8 x 24 4.4 -> 3.4, 8 x 48 5.1 -> 4.6, 4 x 96 4.9 -> 4.2, 4 x 192 8.8 -> 6.8;
+// items each: 8 x 4 2.6 -> 2.25, 32 x 12 4.6 -> 4.4, 8 x 24 4.4 -> 3.4, 8 x 48 5.1 -> 4.6, 4 x 96 4.9 -> 4.2;
 // behind the split kernel, 16 short contexts 14.7 -> 14.3, four-layer step 82.7 -> 79.2.
 constexpr int kMergeWaves = 4, kMergeBatch = 32;
 constexpr int kMergeAlone = 24;   // up to that many items the first wavefront does the work alone
@@ -1282,12 +1282,16 @@ int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indpt
     (void)desc;
     const float *acc_ws = (const float *)workspace;
     const float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
-    // The item counts are on the device; the average per sequence picks the kernel.  us alone, 64-slot kernel / merge kernel with 2
-    // channels a lane / with 1: 64 heads, 4 x 192 items 8.8 / 6.8 / 7.5, 4 x 256 10.1 / 8.3 / 9.5, 2 x 384 8.3 / 8.3 / 7.7; 8 heads,
-    // 4 x 192 4.8 / 5.3 / 4.4, 4 x 384 5.1 / 7.0 / 5.8, 1 x 384 3.7 / 5.4 / 4.4.  Two channels a lane where that gives 256 workgroups:
+    // The item counts are on the device; the average per sequence picks the kernel.  The longest sequence decides how long
+    // either takes, and it may hold nearly all items.  Up to 128 on average the merge kernel is the faster one for equal
+    // counts and for every skew (against a 64-slot kernel with 8 slots, which it has replaced; us alone, 64 heads: [250, 45, 45, 44] 8.8 ->
+    // 6.6, [300, 7 x 12] 9.5 -> 7.6, [200, 56] 7.3 -> 5.0; 8 heads: 24 x 128 6.2 -> 4.9, [2049, 31 x 33] 45 -> 27).  Above, it
+    // gains on equal counts and loses on skewed ones (64 slots / merge kernel, 64 heads: 16 x 161 21.5 / 16.6, 2 x 192 5.9 / 5.1,
+    // [380, 4] 6.1 / 6.6, [700, 1, 1, 1] 8.4 / 12.5; 8 heads: 16 x 161 5.4 / 4.8, 4 x 256 4.6 / 4.9, 16 between 30 and 409 6.2 / 7.9,
+    // [2049, 11 x 32] 11.3 / 18.7), and the host cannot tell them apart.  Two channels a lane where that gives 256 workgroups:
     // 64 heads, 8 x 48 4.6 against 4.9, 4 x 96 4.2 against 4.6; 8 heads, 4 x 96 3.0 against 2.8.  (32 items of one head are
     // addressed in 32 bits.)
-    if ((int64_t)n_items <= 256 * (int64_t)batch && n_q_heads <= 1 << 17) {
+    if ((int64_t)n_items <= 128 * (int64_t)batch && n_q_heads <= 1 << 17) {
         const bool two = (int64_t)batch * n_q_heads >= 256;
         constexpr int kMaxY = 65535;
         const dim3 grid((unsigned)n_q_heads * (two ? 1 : 2), (unsigned)(batch < kMaxY ? batch : kMaxY), (unsigned)((batch + kMaxY - 1) / kMaxY));

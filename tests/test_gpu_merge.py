@@ -1,5 +1,6 @@
 """tkv_decode_reduce on made-up partials: item counts at the edges of the two kernels (alone / shared between wavefronts, batches
-of 32, the switch at 256 items per sequence on average), both lane widths, skewed and empty sequences, empty items."""
+of 32, the switch at 128 items per sequence on average, by equal and by skewed counts), both lane widths, skewed and empty sequences,
+empty items."""
 import numpy as np
 import pytest
 import torch
@@ -53,7 +54,8 @@ def _run(acc, m, l, counts, hq, tail=0):
     return out.cpu().numpy()
 
 
-COUNTS = [[1], [24], [25], [26, 0, 3], [31, 32, 33], [96, 97], [128], [129, 1, 0], [4 * 32 + 1], [255], [256], [257], [1, 1, 1, 700], [0, 0], [600, 40]]
+COUNTS = [[1], [24], [25], [26, 0, 3], [31, 32, 33], [96, 97], [128], [129, 1, 0], [4 * 32 + 1], [255], [256], [257], [1, 1, 1, 700], [0, 0], [600, 40],
+          [200, 56], [200, 57], [1, 509, 1, 1], [1, 510, 1, 1]]
 
 
 @pytest.mark.parametrize("counts, hq", [(c, h) for c in COUNTS for h in (1, 8, 64, 256) if sum(c) * h <= 80000],   # (host memory)
