@@ -395,10 +395,14 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
     // 65536 45.6 / 46.9 / 55.9 | 61.0 / 58.4 / 57.9; 131072 120 / 89 / 113 | 121 / 116 / 115.
     const int64_t row_bytes = (int64_t)n_tokens * desc->n_kv_heads * (2 * kRowBytes);
     const bool k_once = row_bytes > (64 << 20);
-    // Eight workgroups of 16 KiB are resident per compute unit.  From 768 MiB of rows on, more than any cache keeps, six (by
-    // idle LDS) ask for no more than the memory takes in: 262144 tokens x 8 heads 235 -> 229 us; 131072 116 -> 115, but 89 -> 94
-    // where the cache still holds rows.
-    const unsigned idle_lds = row_bytes > ((int64_t)768 << 20) ? 10200 : 0;
+    // Eight workgroups of 16 KiB are resident per compute unit.  From 320 MiB of rows on six (by idle LDS): eight ask for more
+    // at once than the memory takes in.  us, eight / six, rows not read for three calls | same rows again and again, 8 heads:
+    // 65536 tokens 59.2 / 58.0 | 46.3 / 48.3; 81920 73.9 / 72.4 | 56.5 / 58.7; 98304 88.7 / 86.3 | 66.5 / 69.4; 131072 117.5 /
+    // 113.8 | 87 / 91; 163840 146 / 142 | 147 / 140; 262144 235 / 229.  Where a tag held up the rows (one wait more in the
+    // chain of loads), eight took 74.0 | 59.8 at 81920, 87.7 | 70.3 at 98304, 115 | 92 at 131072, 171.5 (196608; six 170.4, eight
+    // 176.3), 229: the line lies where eight become slower than that on rows that no cache holds.  (1 and 2 heads, and per-channel
+    // keys: six are nowhere slower than that either.)
+    const unsigned idle_lds = row_bytes > ((int64_t)320 << 20) ? 10200 : 0;
     auto kernel = kc ? (k_once ? tkv_append_kernel<true, true> : tkv_append_kernel<true, false>)
                      : (k_once ? tkv_append_kernel<false, true> : tkv_append_kernel<false, false>);
     // Workgroups are dealt to the eight XCDs in turn: the first grid dimension is the XCD, which reads the rows of all heads

@@ -46,7 +46,7 @@ def test_slots_without_a_source_change_nothing(n_tokens):
 
 
 @pytest.mark.parametrize("keys", [tkv.TKV_KEYS_PER_TOKEN, tkv.TKV_KEYS_PER_CHANNEL])
-@pytest.mark.parametrize("mib", [64, 768])
+@pytest.mark.parametrize("mib", [64, 320, 768])
 def test_large_inputs_give_the_bytes_of_small_ones(mib, keys):
     """The rows of a few pages, out of an input just at and just above the size where the launcher changes over."""
     at = (mib << 20) // 512
