@@ -13,8 +13,8 @@
 // unpacking is one AND per two codes, for K and for V.
 //
 //   QK^T  D[token, head] = sum_c code[token, c] * q[head, c].  q is converted to fp16
-//         once, scaled by a power of two common to the heads (exact down to 2^-31 of the
-//         largest |q|, 2^-25 with per-channel keys) and by 2^-pos per slot; the K scale
+//         once, scaled by a power of two common to the heads and by 2^-pos per slot
+//         (exact above the subnormals of fp16, see build_q_operand); the K scale
 //         (fp32, times the compensating power of two) multiplies the MFMA result.  The
 //         eight heads fill half of the 16 columns, so the columns carry two token sets:
 //         row r of a 32-token block is token r in columns 0..7 and token 16 + r in
@@ -47,8 +47,8 @@
 //         as a pair 5.7e-6.)
 //
 // Every product the MFMAs see is exact; the roundings are fp32 accumulation (the sums of
-// q among it), the fp32 K-scale multiply, the 22-bit softmax weight (common to numerator and denominator) and
-// the two-piece a.
+// q among it), the fp32 K-scale multiply, the 22-bit softmax weight (common to numerator and denominator),
+// the two-piece a, and those of channels of q far below the largest of the kv head's heads (build_q_operand).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -261,7 +261,11 @@ __device__ __forceinline__ float bf16_hi(uint32_t v) { return __uint_as_float(v 
 //  - otherwise (two token sets, see compute_page): per (group, half group) one entry per (channel octet sub,
 //    head) and an entry of zeros, which the lanes whose k-slots belong to the other token set read.
 // The slot factors are powers of two and q * 2^E has 8 significant bits: the fp16 products are exact unless they
-// fall into the subnormals, where they round once.
+// fall below the grid of the subnormals, 2^-24.  With a slot factor of 2^-p that spares every q down to 2^(p-31) of the largest
+// |q| of the heads, 2^(p-25) in the kernel for per-channel INT2 keys, whose q * 2^E stays below 2^kKcQExp: INT2 (p up to 9)
+// down to 2^-22 and 2^-16, INT4 (p = 0 or 4) down to 2^-27 and 2^-21, the copy without slot factors down to 2^-25.  What is
+// smaller rounds once, by at most 2^(p-39) of the largest |q| (2^(p-33)); for per-channel INT2 keys twice, first by 2^-33
+// on the way to the copy.
 template <int BITS, bool KC>
 __device__ __forceinline__ void build_q_operand(const QRegs &qr, float two_e, int lane, Lds<KC> &lds)
 {
@@ -461,7 +465,7 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
     floatx4 S[4];
     if constexpr (kPerChannel) {
         // score = sum_c (q_c s_c) code + sum_c q_c z_c with s, z of the token's block.  q s is formed per block
-        // in two fp16 pieces, exactly (q has 8 significant bits, s 11): head columns 0..7 take
+        // in two fp16 pieces, exactly (q has 8 significant bits, s 11) above the subnormals' grid: head columns 0..7 take
         // fp16(q s), columns 8..15 the remainder q s - fp16(q s); the columns of a head are added after the
         // MFMAs.  What is subtracted is formed from a q that is zero in the hi columns.
         const uint32_t lo_cols = r16 >= 8 ? 0xffffffffu : 0u;
@@ -915,7 +919,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 #pragma unroll
         for (int i = 0; i < 8; ++i) big = __builtin_elementwise_max(big, __builtin_bit_cast(short2_t, ((d[i] & 0x7fff7fffu) + 0x00800080u)));
         const int top = wave_max(big[0] > big[1] ? big[0] : big[1]);   // 0x80 where all are zero
-        // 2^E with max|q| * 2^E in [2^14, 2^15); E clamped so every factor stays a normal fp32
+        // 2^E with max|q| * 2^E in [2^14, 2^15) ([2^8, 2^9) with per-channel INT2 keys); E clamped so every factor stays a normal fp32
         int E = (KC ? kKcQExp : 15) - ((top >> 7) - 127);   // max|q| = m * 2^(exponent - 126), m in [0.5, 1)
         E = E > 100 ? 100 : (E < -100 ? -100 : E);
         if (top <= 0x80) E = 0;
