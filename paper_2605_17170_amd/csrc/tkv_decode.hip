@@ -878,17 +878,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     bool has2 = pb < e2, has4 = b4 < pe;
     // tokens of a width whose pool has no pages at all: nothing to read
     if ((has2 && n_pages_int2 == 0) || (has4 && n_pages_int4 == 0)) {
-        if (status && lane == 0) atomicOr(status, TKV_STATUS_PAGE_RANGE);
+        int bits = TKV_STATUS_PAGE_RANGE;
+        // (pages of the other pool among the first 64 are flagged as such, as they are where the pool has pages)
+        if (has4 && n_pages_int4 > 0 && pb + lane < b4 && (uint32_t)pages[pb + lane] < (uint32_t)n_pages_total) bits |= TKV_STATUS_BITMAP_MISMATCH;
+        if (status) atomicOr(status, bits);
         has2 = has2 && n_pages_int2 > 0;
         has4 = has4 && n_pages_int4 > 0;
     }
+    const int first = has2 ? pb : b4;   // the first list position that is read: more than pb where there is no INT2 pool
     if (!(has2 || has4)) {   // an item without pages
         write_empty();
         return;
     }
     const ItemCtx cx = {pool, bit_map, pages, pb, pe, np2, np4, n2 - (np2 - 1) * kPageTokens, n4 - (np4 - 1) * kPageTokens,
                         kvh, n_kv_heads, n_pages_int2, n_pages_total, lane, status};
-    PageBatch list = {pb, 0, 0, 0};
+    PageBatch list = {first, 0, 0, 0};
     PageRegs<2> s2;
     PageRegs<4> s4;
 
@@ -897,7 +901,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     // tables: asked for any earlier, the records of the wavefronts that came first stand in front of the q and the page ids
     // of the others of the compute unit (16 contexts of 97 to 6011 tokens 15.4 us asked with the page ids there, 14.7 here,
     // 14.9 behind the tables; four-layer step 84.1, 81.8, 83.8).
-    const int first_ids = batch_ids(cx, list, pb);
+    const int first_ids = batch_ids(cx, list, first);
     const uint16_t *q_head = q + ((size_t)seq * n_q_heads + kvh * R + ((lane >> 3) & (R - 1))) * kHeadDim;   // columns beyond R repeat heads
     QRegs qr;
     load_q(qr, q_head, lane);
@@ -994,7 +998,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
         } else {
             prepare_q();
             batch_finish(cx, list);
-            batch_seek(cx, list, b4);   // INT2 positions lie ahead where the table counts INT2 tokens and the pool has no INT2 pages
         }
         __builtin_amdgcn_sched_barrier(0);
         const Record rec = batch_record<4>(cx, list, b4, true);

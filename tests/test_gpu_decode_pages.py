@@ -95,7 +95,8 @@ def test_one_odd_head_leaves_the_others_alone(G, bits, axis):
 
 @pytest.mark.parametrize("axis", [tkv.TKV_KEYS_PER_TOKEN, tkv.TKV_KEYS_PER_CHANNEL])
 @pytest.mark.parametrize("claimed,first", [(1, 0), (63, 0), (64, 0), (65, 0), (70, 0), (128, 0), (130, 5), (200, 136), (200, 137), (70, 70)])
-def test_int2_tokens_without_an_int2_pool_take_nothing_from_the_int4_pages(G, claimed, first, axis):
+@pytest.mark.parametrize("named", [-1, 0], ids=["nothing", "an-int4-page"])
+def test_int2_tokens_without_an_int2_pool_take_nothing_from_the_int4_pages(G, named, claimed, first, axis):
     """The table counts `claimed` INT2 pages, the pool has none: they are flagged, and the item attends over all its INT4
     pages, however many list positions lie between its first one and the first INT4 page."""
     q, K, V, seq_bits = _case(G, 107, 0, 6, 17, 8, 2)
@@ -104,7 +105,7 @@ def test_int2_tokens_without_an_int2_pool_take_nothing_from_the_int4_pages(G, cl
         assert cache.P2 == 1   # an unused page in front of the INT4 pages: the same memory without it is a pool of INT4 pages only
         desc = tkv.tkv_desc.make(2, 0, cache.P4, int2_key_axis=axis)
         pool, bit_map = cache.pool[tkv.tkv_pool_bytes(cache.desc) - tkv.tkv_pool_bytes(desc):], cache.bit_map[1:]
-        ids = np.concatenate([np.full(claimed, -1), cache.page_ids - 1])
+        ids = np.concatenate([np.full(claimed, named), cache.page_ids - 1])
         dev = lambda *v: torch.tensor(v, dtype=torch.int32, device=G.DEV)
         items = torch.tensor([[0, first, ids.size, 0]], dtype=torch.int32, device=G.DEV)
         out = torch.empty((1, 8, 128), device=G.DEV)
@@ -112,7 +113,8 @@ def test_int2_tokens_without_an_int2_pool_take_nothing_from_the_int4_pages(G, cl
         tkv.tkv_decode_attention(desc, pool, bit_map, harness.bf16_tensor(q, G.DEV), dev(0, ids.size), dev(*ids.tolist()), dev(64 * claimed),
                                  dev(seq_bits[0].size), items, dev(0, 1), G.SM, out, workspace, cache.status)
         torch.cuda.synchronize()
-        assert int(cache.status.item()) == (tkv.TKV_STATUS_PAGE_RANGE if first < claimed else 0)
+        flags = tkv.TKV_STATUS_PAGE_RANGE | (tkv.TKV_STATUS_BITMAP_MISMATCH if named == 0 else 0)
+        assert int(cache.status.item()) == (flags if first < claimed else 0)
         G.assert_close(out.cpu().numpy(), G.decode_ref(q, Kq, Vq, [seq_bits[0].size]), "behind %d INT2 pages" % (claimed - first))
     finally:
         cache.close()
