@@ -13,9 +13,9 @@
 //    for at once is: the slots, then tags, rows and the V words that may have to be merged;
 //  - K and V apart: a workgroup holds 16 KiB of LDS and eight are resident per compute unit, each in a phase of its
 //    own.  65 536 tokens x 8 heads, inputs not in any cache: 67.2 us with both in one workgroup and 64-byte runs per thread
-//    through registers, 63.1 with rows through LDS (32 KiB, five resident), 59.1 apart (with ordinary stores 60.7), 58.4 with
-//    one wait per level of the chain;
-//    per-channel keys 69.4 -> 59.1; one token for each of 32 sequences 6.0 -> 4.2.  The launcher says which loads and
+//    through registers, 63.1 with rows through LDS (32 KiB, five resident), 59.1 apart (with ordinary stores 60.7);
+//    per-channel keys 69.4 -> 60.1; one token for each of 32 sequences 6.0 -> 4.4.  What one wait per level of the chain of
+//    loads adds to that stands where it is made (tkv_append_kernel).  The launcher says which loads and
 //    which order of the workgroups are taken.
 //
 // K words go straight to HBM (a wavefront's stores for one word index are 256 contiguous bytes, written with
@@ -310,8 +310,8 @@ __global__ __launch_bounds__(256) void tkv_append_kernel(
     const bool is_v = blockIdx.y & 1;
     // A launch of a few tokens is a chain of loads: arguments -> page and slots -> tags, rows and words to merge.  All of
     // a level at once: an argument fetched where it is first used, a wait for the tag ahead of the rows, or for a slot between
-    // two rows, is a round trip more.  (12288 tokens x 8 heads 12.9 -> 12.1 us, 65536 59.8 -> 58.4, per-channel keys 62.0 -> 59.1,
-    // six ragged chunks 10.9 -> 10.2, four-layer step 78.1 -> 76.8.)
+    // two rows, is a round trip more.  (12288 tokens x 8 heads 13.4 -> 12.7 us, 65536 59.6 -> 58.7, per-channel keys 61.6 -> 59.2,
+    // six ragged chunks 10.85 -> 10.15, four-layer step 78.1 -> 76.8.)
     asm volatile("" :: "s"(pool), "s"(bit_map), "s"(K), "s"(V), "s"(tag_bits), "s"(n_tokens), "s"(work_pages), "s"(work_src), "s"(n_work),
                  "s"(n_kv_heads), "s"(n_pages_int2), "s"(n_pages_int4), "s"(status));
     if (w >= n_work) return;
@@ -392,7 +392,7 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
     // computed them, and ordinary loads find them; larger inputs push each other out, and with the K rows read past the
     // cache the V rows stay in it.  us per call, ordinary / K past the cache / both, same rows again and again | rows not read
     // for three calls: 12288 tokens x 8 heads 11.7 / 11.5 / - | 12.1 / 12.3 / -; 20001 16.6 / 16.5 / 17.7 | 19.1 / 17.3 / 19.3;
-    // 65536 45.6 / 46.9 / 55.9 | 61.0 / 58.4 / 57.9; 131072 120 / 89 / 113 | 121 / 116 / 115.
+    // 65536 45.6 / 46.9 / 55.9 | 61.0 / 58.4 / 57.9; 131072 (eight workgroups per CU) 120 / 89 / 113 | 121 / 116 / 115.
     const int64_t row_bytes = (int64_t)n_tokens * desc->n_kv_heads * (2 * kRowBytes);
     const bool k_once = row_bytes > (64 << 20);
     // Eight workgroups of 16 KiB are resident per compute unit.  From 320 MiB of rows on six (by idle LDS): eight ask for more

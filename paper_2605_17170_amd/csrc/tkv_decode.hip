@@ -611,8 +611,8 @@ __device__ __forceinline__ void compute_page(const PageRegs<BITS> &pr, int n_val
     for (int e = 1; e < kS; ++e) mx = fmaxf(fmaxf(mx, S[e][0]), fmaxf(fmaxf(S[e][1], S[e][2]), S[e][3]));
     if (__any(mx * lc.kappa > st.m_ref + kTau)) {
         // the other token set of the head, then the other rows of 16 lanes (every item comes here on its first page; through
-        // LDS, two round trips and 14 instructions more, 16 contexts of 97 to 6011 tokens took 14.1 us, now 13.8, 8 contexts of
-        // 2000 to 16000 19.3, now 19.0)
+        // LDS, two round trips and 14 instructions more, 16 contexts of 97 to 6011 tokens took 14.1 us, now 13.85, 8 contexts of
+        // 2000 to 16000 19.2, now 18.75)
         mx = fmaxf(mx, row_ror8(mx));
         mx = swap_max(__builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false));
         mx = swap_max(__builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false));
@@ -834,8 +834,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     __shared__ Lds<KC> lds;
     const int lane = threadIdx.x, r16 = lane & 15, q4 = lane >> 4;
     // Everything of a level of the chain arguments -> item -> counts -> page ids at once: fetched where each is first used,
-    // the arguments and counts alone are six round trips in a row.  (16 contexts of 97 to 6011 tokens 14.45 -> 14.2 us, 4 x
-    // 102400 on one head 18.4 -> 18.15, four-layer step 79.0 -> 78.1.)
+    // the arguments and counts alone are six round trips in a row.  (16 contexts of 97 to 6011 tokens 14.45 -> 14.1 us, 4 x
+    // 102400 on one head 18.5 -> 18.2, 8 contexts of 2000 to 16000 20.1 -> 19.3, four-layer step 79.5 -> 78.1.)
     asm volatile("" :: "s"(pool), "s"(bit_map), "s"(q), "s"(page_indptr), "s"(page_ids), "s"(n_tok_int2), "s"(n_tok_int4), "s"(items),
                  "s"(n_items), "s"(batch), "s"(n_kv_heads), "s"(log2_r), "s"(n_pages_int2), "s"(n_pages_int4), "s"(acc_ws), "s"(ml_ws), "s"(status),
                  "s"(gridDim.y));
@@ -1059,7 +1059,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 // items at once -> weights -> sum -> one exchange through LDS, which a sequence of few items does without.
 // Against the kernel below with 8 items in flight per workgroup and a running maximum per item, us alone, 64 heads, sequences x
 // items each: 8 x 4 2.6 -> 2.25, 32 x 12 4.6 -> 4.4, 8 x 24 4.4 -> 3.4, 8 x 48 5.1 -> 4.6, 4 x 96 4.9 -> 4.2;
-// behind the split kernel, 16 short contexts 14.7 -> 14.3, four-layer step 82.7 -> 79.2.
+// behind the split kernel, 16 short contexts 14.7 -> 14.45, four-layer step 83.4 -> 79.5.
 constexpr int kMergeWaves = 4, kMergeBatch = 32;
 constexpr int kMergeAlone = 24;   // up to that many items the first wavefront does the work alone
 __device__ __forceinline__ float wave_sum(float v)   // four DPP steps in the rows of 16 lanes, then the four rows
@@ -1291,7 +1291,7 @@ int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indpt
     const float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
     // The item counts are on the device; the average per sequence picks the kernel.  The longest sequence decides how long
     // either takes, and it may hold nearly all items.  Up to 128 on average the merge kernel is the faster one for equal
-    // counts and for every skew (against a 64-slot kernel with 8 slots, which it has replaced; us alone, 64 heads: [250, 45, 45, 44] 8.8 ->
+    // counts and for every skew (against a kernel of 8 item slots, which it has replaced; us alone, 64 heads: [250, 45, 45, 44] 8.8 ->
     // 6.6, [300, 7 x 12] 9.5 -> 7.6, [200, 56] 7.3 -> 5.0; 8 heads: 24 x 128 6.2 -> 4.9, [2049, 31 x 33] 45 -> 27).  Above, it
     // gains on equal counts and loses on skewed ones (64 slots / merge kernel, 64 heads: 16 x 161 21.5 / 16.6, 2 x 192 5.9 / 5.1,
     // [380, 4] 6.1 / 6.6, [700, 1, 1, 1] 8.4 / 12.5; 8 heads: 16 x 161 5.4 / 4.8, 4 x 256 4.6 / 4.9, 16 between 30 and 409 6.2 / 7.9,

@@ -387,14 +387,15 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
     // than the heaviest equal part either.)
     // Time of full items over that of equal parts, ragged and even batches, 1, 2 and 8 kv heads, least / mean / worst:
     //   longest equal part   2 pages            3 pages            4                  5                  6 to 9             more
-    //   INT4 share to .4     .83 / .93 / 1.00   .89 / .97 / 1.01   .93 / .98 / 1.03   .93 / .99 / 1.05   .97 / .99 / 1.03   .98 / 1.00 / 1.02
-    //   .5 to .8             .83 / .86 / .89    .88 / .95 / 1.01   .97 / .99 / 1.03   .95 / .99 / 1.01   .97 / .99 / 1.03   .98 / 1.00 / 1.02
-    //   INT4 only            .83 / .93 / 1.01   .96 / 1.00 / 1.02  1.01 / 1.02 / 1.04 1.01 / 1.03 / 1.05 .99 / 1.02 / 1.04  .99 / 1.01 / 1.02
-    //   per-channel keys     .86 / .94 / 1.00   .92 / .98 / 1.05   .93 / .99 / 1.05   .92 / .99 / 1.05   .93 / .98 / 1.01   .94 / 1.00 / 1.04
-    //   ... up to 4/5 of target_items            .92 / .96 / 1.03
-    //   ... more                                 .96 / .99 / 1.05
-    // (10 to 200 batches in a field; repetitions of one plan differ by .01; four pages to .4: 105 of 186 batches more than
-    // .01 faster, 4 slower.)  Longer items have enough pages to even out by themselves, and three full ones on a SIMD take
+    //   INT4 share to .4     .77 / .90 / 1.00   .85 / .96 / 1.00   .93 / .97 / 1.01   .89 / .97 / 1.02   .94 / .99 / 1.03   .97 / 1.00 / 1.03
+    //   .5 to .8             .80 / .88 / 1.01   .84 / .95 / 1.03   .94 / 1.01 / 1.05  .94 / 1.00 / 1.05  .91 / .97 / 1.04   .94 / .98 / 1.03
+    //   INT4 only            .80 / .91 / 1.00   .98 / 1.00 / 1.01  1.00 / 1.02 / 1.04 1.01 / 1.04 / 1.06 1.00 / 1.02 / 1.05 1.00 / 1.01 / 1.02
+    //   per-channel keys     .80 / .90 / 1.00   .87 / .96 / 1.00   .94 / .97 / 1.00   .96 / .98 / 1.02   .97 / .99 / 1.03   .98 / 1.01 / 1.06
+    //   ... up to 4/5 of target_items            .87 / .94 / .97
+    //   ... more                                 .95 / .97 / 1.00
+    // (7 to 88 batches in a field, items counted in pages in all of them; nine in ten repetitions of one plan are within .01.  The
+    // lines were drawn with an earlier kernel, whose pages cost more beside what an item costs by itself: channel keys of
+    // three pages above 4/5 of target_items .96 / .99 / 1.05, four .93 / .99 / 1.05.)  Longer items have enough pages to even out by themselves, and three full ones on a SIMD take
     // longer than a mixture, with the per-channel keys' dearer pages above all; INT4 pages wait for memory, and fewer items
     // are fewer requests under way.  Single pages cannot be cut differently, and more items than the 256 x 12 wavefronts
     // that a whole MI355X holds at once were asked for as such: equal parts.  (A partition of the device holds fewer; the
