@@ -1190,16 +1190,18 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tkv_merge_kernel(
 // accumulators of the slice, so every partial is read once with 128-bit loads and TH * SL / 32 items are in flight per
 // workgroup round.  Each such lane group keeps a running (M, l, acc); the groups are merged through LDS by the first wavefront.
 constexpr int SL = 4, TH = 512;   // four workgroups per head, 64 item slots each
+constexpr uint32_t kRowsGridX = 1u << 22;   // workgroups are folded there: a grid dimension ends at 2^32 threads
 __global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(
     const float *__restrict__ acc_ws, const float *__restrict__ ml_ws, const int32_t *__restrict__ seq_item_indptr,
-    int n_q_heads, float *__restrict__ out)
+    int n_rows /* sequences x query heads */, int n_q_heads, float *__restrict__ out)
 {
     constexpr int kLanes = 32 / SL;       // lanes per item: 16 bytes each
     constexpr int kSlots = TH / kLanes;   // items in flight
     constexpr int kSubsets = 64 / kLanes; // the first wavefront merges the slots in this many interleaved subsets
     __shared__ float4 num_s[kSlots][kLanes];
     __shared__ float2 ml_s[kSlots];
-    const int bh = blockIdx.x / SL, slice = blockIdx.x % SL;
+    const int bh = blockIdx.y * (kRowsGridX / SL) + blockIdx.x / SL, slice = blockIdx.x % SL;
+    if (bh >= n_rows) return;
     const int b = bh / n_q_heads, h = bh % n_q_heads, tid = threadIdx.x;
     const int slot = tid / kLanes, ln = tid % kLanes, cq = slice * kLanes + ln;   // cq: which float4 of the 32 of a row
     const int i0 = seq_item_indptr[b], i1 = seq_item_indptr[b + 1];
@@ -1305,8 +1307,10 @@ int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indpt
         hipLaunchKernelGGL(two ? tkv_merge_kernel<2> : tkv_merge_kernel<1>, grid, dim3(64 * kMergeWaves), 0, (hipStream_t)stream, acc_ws, ml_ws,
                            seq_item_indptr, batch, n_q_heads, out);
     } else {
-        hipLaunchKernelGGL(tkv_reduce_rows_kernel, dim3((unsigned)(batch * n_q_heads * SL)), dim3(TH), 0, (hipStream_t)stream, acc_ws, ml_ws,
-                           seq_item_indptr, n_q_heads, out);
+        const uint64_t blocks = (uint64_t)batch * n_q_heads * SL;
+        const dim3 grid((unsigned)(blocks < kRowsGridX ? blocks : kRowsGridX), (unsigned)((blocks + kRowsGridX - 1) / kRowsGridX));
+        hipLaunchKernelGGL(tkv_reduce_rows_kernel, grid, dim3(TH), 0, (hipStream_t)stream, acc_ws, ml_ws, seq_item_indptr,
+                           batch * n_q_heads, n_q_heads, out);
     }
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }

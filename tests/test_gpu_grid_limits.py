@@ -1,5 +1,5 @@
 """A launch is cut where the grid ends: append at 524 280 pages and 32 767 kv heads, gather at 262 136 pages and 65 535 kv
-heads, and the decode kernel folds its items at 65 535.  Lists just above those limits, little of them in use: what lies
+heads, the decode kernel folds its items at 65 535 and the merge of hundreds of items its workgroups at 2^22.  Lists just above those limits, little of them in use: what lies
 around each cut is where it belongs, and nothing else is touched."""
 import numpy as np
 import pytest
@@ -119,3 +119,33 @@ def test_decode_beyond_65535_items(G):
         G.assert_close(out.cpu().numpy(), ref.cpu().numpy(), "%d items" % batch)
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("heads", [131072, 131080])   # up to 2^17 the merge kernel of few items, above it the one of hundreds
+def test_merge_beyond_the_workgroups_of_a_launch(heads):
+    """Four workgroups of 512 threads for each of 16 x 131080 heads are more than 2^32 threads."""
+    counts = [1, 3] + [0] * 13 + [2]
+    n = sum(counts)
+    desc = tkv.tkv_desc.make(heads // 8, 1, 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(304)
+    ws = torch.empty(tkv.tkv_decode_workspace_bytes(desc, n, heads) // 4, device="cuda")
+    acc, ml = ws[:n * heads * 128].view(n, heads, 128), ws[n * heads * 128:].view(n, heads, 2)
+    acc.normal_(generator=g)
+    ml[..., 0].normal_(generator=g)
+    ml[..., 1].uniform_(1, 300, generator=g)
+    out = torch.full((len(counts), heads, 128), float("nan"), device="cuda")
+    indptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    tkv.tkv_decode_reduce(desc, torch.from_numpy(indptr).cuda(), n, out, ws.view(torch.uint8))
+    torch.cuda.synchronize()
+    for b, (i0, i1) in enumerate(zip(indptr, indptr[1:])):
+        if i0 == i1:
+            assert int(torch.count_nonzero(out[b])) == 0
+            continue
+        m, l = ml[i0:i1, :, 0].double(), ml[i0:i1, :, 1].double()
+        w = torch.exp2(m - m.max(0).values)
+        num = (w[..., None] * acc[i0:i1].double()).sum(0)
+        mag = (w[..., None] * acc[i0:i1].double().abs()).sum(0)
+        den = (w * l).sum(0)[:, None]
+        # a weight is good to 2^-22, sums of three terms and the division to a few ulps of the magnitudes added
+        assert bool(((out[b].double() - num / den).abs() <= 2.0 ** -20 * mag / den).all()), "sequence %d" % b
