@@ -1057,9 +1057,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 // wavefront takes a quarter of the items; lane l weighs item l, and an item's accumulators are one load of whole lines.
 // What bounds it is latency (bytes alone would take 1 to 2 us): the chain is item list -> (m, l) pairs and accumulators of 32
 // items at once -> weights -> sum -> one exchange through LDS, which a sequence of few items does without.
-// Against the kernel below with 8 items in flight per workgroup and a running maximum per item, us alone, 64 heads, sequences x
-// items each: 8 x 4 2.6 -> 2.25, 32 x 12 4.6 -> 4.4, 8 x 24 4.4 -> 3.4, 8 x 48 5.1 -> 4.6, 4 x 96 4.9 -> 4.2;
-// behind the split kernel, 16 short contexts 14.7 -> 14.45, four-layer step 83.4 -> 79.5.
+// Against a kernel of the next one's kind that it replaced (a running maximum per item, 8 items in flight per workgroup), us
+// alone, 64 heads, sequences x items each: 8 x 4 2.6 -> 2.25, 32 x 12 4.6 -> 4.4, 8 x 24 4.4 -> 3.4, 8 x 48 5.1 -> 4.6, 4 x 96
+// 4.9 -> 4.2; behind the split kernel, 16 short contexts 14.7 -> 14.45, four-layer step 83.4 -> 79.5.
 constexpr int kMergeWaves = 4, kMergeBatch = 32;
 constexpr int kMergeAlone = 24;   // up to that many items the first wavefront does the work alone
 __device__ __forceinline__ float wave_sum(float v)   // four DPP steps in the rows of 16 lanes, then the four rows
