@@ -306,7 +306,9 @@ int tkv_gather_dequant(const tkv_desc *desc, const void *pool, const uint8_t *bi
  * pages in five) and target_items times the kv heads fit the 3072 wavefronts
  * that a whole MI355X holds at once, every item gets as many pages as that part
  * instead: fewer items, none with more pages than the longest equal part and,
- * at four pages, none of a greater cost than the heaviest.
+ * at four pages, none of a greater cost than the heaviest.  Under the same
+ * condition, where every part is a single page and the pages times the kv heads
+ * are more than 2048 (and at most 3072), an item gets two.
  * A plan depends only on the page COUNTS of the sequences: it stays valid while
  * tokens are appended to open pages (the kernel reads the token counts from the
  * device arrays and masks by them) and must be made again when a sequence gains

@@ -397,7 +397,7 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
     // lines were drawn with an earlier kernel, whose pages cost more beside what an item costs by itself: channel keys of
     // three pages above 4/5 of target_items .96 / .99 / 1.05, four .93 / .99 / 1.05.)  Longer items have enough pages to even out by themselves, and three full ones on a SIMD take
     // longer than a mixture, with the per-channel keys' dearer pages above all; INT4 pages wait for memory, and fewer items
-    // are fewer requests under way.  Single pages cannot be cut differently, and more items than the 256 x 12 wavefronts
+    // are fewer requests under way.  More items than the 256 x 12 wavefronts
     // that a whole MI355X holds at once were asked for as such: equal parts.  (A partition of the device holds fewer; the
     // planner does not ask which it is.)
     constexpr int64_t kResident = 256 * 12;
@@ -409,6 +409,17 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
         for (int32_t b = 0; b < batch; ++b)
             n_full += ceil_div(ceil_div(n_tok_int2[b], kPageTokens) + ceil_div(n_tok_int4[b], kPageTokens), (int32_t)longest);
         full = 5 * n_full <= 4 * (int64_t)target_items;
+    }
+    // Single pages on more than two wavefronts per SIMD go in pairs: half the wavefronts, each with one more page, prepare q and
+    // leave a partial half as often, ask for half the first records at once, and the merge has half the rows.  Time of pairs
+    // over that of single pages, 1 to 8 kv heads, 1 to 8 query heads each, ragged and even, least / mean / worst: 950 to 1150
+    // (page, kv head) records .89 / 1.02 / 1.14, to 1536 .87 / 1.02 / 1.11, to 1792 .88 / .99 / 1.10, to 2048 .84 / .95 / 1.05,
+    // to 2300 .82 / .91 / .98, to 3072 .77 / .87 / .94 (16 contexts of 97 to 6011 tokens 13.9 us, now 12.2).  Three pages are
+    // within .05 of two either way up to 3072.
+    const int64_t n_records = (pages2 + pages4) * desc->n_kv_heads;
+    if (longest == 1 && n_records > kResident / 3 * 2 && n_records <= kResident && (int64_t)target_items * desc->n_kv_heads <= kResident) {
+        longest = 2;
+        full = true;
     }
     const int64_t most = longest <= 3 ? longest * kCost4 : heaviest;
     int32_t n_items = 0;
