@@ -966,10 +966,13 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3)
     PageRegs<4> s4;
 
     // What a wavefront of few pages does is a chain of loads (arguments -> item -> counts -> page ids and q -> record) and the
-    // preparation of q.  The first record is requested when the exponents and sums of q are known, ahead of the operand
-    // tables: asked for any earlier, the records of the wavefronts that came first stand in front of the q and the page ids
-    // of the others of the compute unit (16 contexts of 97 to 6011 tokens 15.4 us asked with the page ids there, 14.7 here,
-    // 14.9 behind the tables; four-layer step 84.1, 81.8, 83.8).
+    // preparation of q.  The vector loads of a compute unit return in the order in which they were asked for: records that the
+    // first wavefronts ask for early stand in front of the q and the page ids of the others.  So the first record is requested
+    // when the exponents and sums of q are known, ahead of the operand tables (16 contexts of 97 to 6011 tokens, one page to a
+    // wavefront, 15.4 us asked with the page ids, 14.7 here, 14.9 behind the tables; four-layer step 84.1, 81.8, 83.8), and its V
+    // codes, which are needed last, behind them (step 75.8 -> 75.2, 4 x 102400 on one head 18.5 -> 18.3, 20 shapes of 1500 to
+    // 9000 records .94 to 1.00, mean .985; with the first K metadata 76.3 and 18.5).  The tables for per-channel keys take longer
+    // (.98 to 1.04): K and V together there.
     const int first_ids = batch_ids(cx, list, first);
     const uint16_t *q_head = q + ((size_t)seq * n_q_heads + kvh * R + ((lane >> 3) & (R - 1))) * kHeadDim;   // columns beyond R repeat heads
     QRegs qr;
@@ -1049,9 +1052,14 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3)
         __builtin_amdgcn_sched_barrier(0);
         const Record rec = batch_record<2>(cx, list, pb, true);
         load_page_k<2, KC>(s2, rec, lane);
-        load_page_v<2>(s2, rec, lane);
+        if constexpr (KC) load_page_v<2>(s2, rec, lane);
         __builtin_amdgcn_sched_barrier(0);
         build_q_operand<2, KC>(qr, two_e, lane, lds);
+        if constexpr (!KC) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_page_v<2>(s2, rec, lane);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         batch_finish(cx, list);
         LaneConst lc2 = lc;
         if constexpr (KC) {
@@ -1071,9 +1079,14 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3)
         __builtin_amdgcn_sched_barrier(0);
         const Record rec = batch_record<4>(cx, list, b4, true);
         load_page_k<4, KC>(s4, rec, lane);
-        load_page_v<4>(s4, rec, lane);
+        if constexpr (KC) load_page_v<4>(s4, rec, lane);
         __builtin_amdgcn_sched_barrier(0);
         build_q_operand<4, KC>(qr, two_e, lane, lds);
+        if constexpr (!KC) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_page_v<4>(s4, rec, lane);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         lds_order();
         run_pages<4, KC>(cx, list, b4, pe, s4, qz, lc, st, lds);
     }
