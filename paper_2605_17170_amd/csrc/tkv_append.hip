@@ -297,14 +297,43 @@ __device__ __forceinline__ void append_v(uint8_t *rec, uint64_t mask, const uint
     }
 }
 
+// One argument instead of fourteen: the runtime looks every pointer argument up on the way to a launch (one token for each of 32
+// sequences, where the launch is what a call waits for, 4.04 -> 3.76 us; chunks of a few hundred tokens 7.9 -> 7.7).
+struct AppendArgs {
+    uint8_t *pool;
+    uint8_t *bit_map;
+    const uint16_t *K;
+    const uint16_t *V;
+    const uint8_t *tag_bits;
+    int n_tokens;
+    const int32_t *work_pages;
+    const int32_t *work_src;
+    int n_work;
+    int first_head;
+    int n_kv_heads;
+    int n_pages_int2;
+    int n_pages_int4;
+    int32_t *status;
+};
 // K_ONCE: the K rows are read with non-temporal loads (see the launcher).
 template <bool KC, bool K_ONCE>
-__global__ __launch_bounds__(256) void tkv_append_kernel(
-    uint8_t *__restrict__ pool, uint8_t *__restrict__ bit_map, const uint16_t *__restrict__ K,
-    const uint16_t *__restrict__ V, const uint8_t *__restrict__ tag_bits, int n_tokens,
-    const int32_t *__restrict__ work_pages, const int32_t *__restrict__ work_src, int n_work, int first_head, int n_kv_heads,
-    int n_pages_int2, int n_pages_int4, int32_t *status)
+__global__ __launch_bounds__(256) void tkv_append_kernel(AppendArgs args)
 {
+    uint8_t *__restrict__ pool = args.pool;
+    uint8_t *__restrict__ bit_map = args.bit_map;
+    const uint16_t *__restrict__ K = args.K;
+    const uint16_t *__restrict__ V = args.V;
+    const uint8_t *__restrict__ tag_bits = args.tag_bits;
+    const int n_tokens = args.n_tokens;
+    const int32_t *__restrict__ work_pages = args.work_pages;
+    const int32_t *__restrict__ work_src = args.work_src;
+    const int n_work = args.n_work;
+    const int first_head = args.first_head;
+    const int n_kv_heads = args.n_kv_heads;
+    const int n_pages_int2 = args.n_pages_int2;
+    const int n_pages_int4 = args.n_pages_int4;
+    int32_t *status = args.status;
+
     __shared__ uint4 rows[kPageTokens * kRowPieces];
     const int w = blockIdx.z * 8 + blockIdx.x, head = first_head + (blockIdx.y >> 1);   // grid (8, 2 * heads, blocks of eight pages): see the launcher
     const bool is_v = blockIdx.y & 1;
@@ -414,10 +443,10 @@ int tkv_launch_append(const tkv_desc *desc, void *pool, uint8_t *bit_map, const 
         for (int head = 0; head < desc->n_kv_heads; head += kMaxHeads) {
             const int n = n_work - page < kMaxPages ? n_work - page : kMaxPages;
             const int h = desc->n_kv_heads - head < kMaxHeads ? desc->n_kv_heads - head : kMaxHeads;
-            hipLaunchKernelGGL(kernel, dim3(8, 2 * (unsigned)h, (unsigned)((n + 7) / 8)), dim3(256), idle_lds, (hipStream_t)stream,
-                               (uint8_t *)pool, bit_map, (const uint16_t *)K, (const uint16_t *)V, tag_bits, n_tokens, work_pages + page,
-                               work_src + (size_t)page * kPageTokens, n, head, desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4,
-                               status);
+            const AppendArgs args = {(uint8_t *)pool, bit_map, (const uint16_t *)K, (const uint16_t *)V, tag_bits, n_tokens, work_pages + page,
+                                     work_src + (size_t)page * kPageTokens, n, head, desc->n_kv_heads, desc->n_pages_int2, desc->n_pages_int4,
+                                     status};
+            hipLaunchKernelGGL(kernel, dim3(8, 2 * (unsigned)h, (unsigned)((n + 7) / 8)), dim3(256), idle_lds, (hipStream_t)stream, args);
         }
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
