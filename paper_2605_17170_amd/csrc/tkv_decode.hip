@@ -880,19 +880,42 @@ __device__ __forceinline__ void join_team(TeamLds<KC, kTeam> &team, float *__res
     }
 }
 
+// The kernels take their arguments as one struct: the runtime looks every pointer argument up on the way to a launch, and small calls
+// wait for their two launches (eighteen arguments 2.7 us, a struct of them 2.4, on a slower host 3.8 and 3.3; step of five layers over
+// 19 pages 64 -> 57 us, tiny calls 1 to 7 %).  The bodies are functions with parameters of their own, which the compiler then
+// knows apart: with the members read where they are used two registers were spilled (four-layer step 75.2 -> 76.2).
+struct DecodeArgs {
+    const uint8_t *pool;
+    const uint8_t *bit_map;
+    const uint16_t *q;
+    const int32_t *page_indptr;
+    const int32_t *page_ids;
+    const int32_t *n_tok_int2;
+    const int32_t *n_tok_int4;
+    const int32_t *items;
+    int n_items;
+    int batch;
+    int n_kv_heads;
+    int log2_r;
+    int n_pages_int2;
+    int n_pages_int4;
+    float kappa;
+    float *acc_ws;
+    float *ml_ws;
+    int32_t *status;
+};
 // KC: the INT2 keys of the pool are quantised per channel over 32-token blocks (Sec. 3.2.1).
 // TEAM wavefronts, one work item each, form a workgroup: with one of them every item leaves a partial in its slot, with kTeam
 // the items of a sequence share one (join_team).
 // The grid is (kv heads, groups of TEAM items): the workgroups of an item are launched one behind the other, without a division to
 // find the item.
 template <bool KC, int TEAM>
-__global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3))) void tkv_decode_kernel(
+__device__ __forceinline__ void decode_items(
     const uint8_t *__restrict__ pool, const uint8_t *__restrict__ bit_map, const uint16_t *__restrict__ q,
     const int32_t *__restrict__ page_indptr, const int32_t *__restrict__ page_ids,
     const int32_t *__restrict__ n_tok_int2, const int32_t *__restrict__ n_tok_int4,
     const int32_t *__restrict__ items, int n_items, int batch, int n_kv_heads, int log2_r, int n_pages_int2, int n_pages_int4,
-    float kappa, float *__restrict__ acc_ws, float *__restrict__ ml_ws, int32_t *status
-    )
+    float kappa, float *__restrict__ acc_ws, float *__restrict__ ml_ws, int32_t *status)
 {
     __shared__ TeamLds<KC, TEAM> team;
     const int wave = TEAM == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1135,6 +1158,12 @@ __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3)
     } while (false);
     if constexpr (TEAM > 1) join_team<KC>(team, acc_ws, ml_ws, n_kv_heads << log2_r, blockIdx.x, 1 << log2_r);
 }
+template <bool KC, int TEAM>
+__global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3))) void tkv_decode_kernel(DecodeArgs a)
+{
+    decode_items<KC, TEAM>(a.pool, a.bit_map, a.q, a.page_indptr, a.page_ids, a.n_tok_int2, a.n_tok_int4, a.items, a.n_items, a.batch,
+                           a.n_kv_heads, a.log2_r, a.n_pages_int2, a.n_pages_int4, a.kappa, a.acc_ws, a.ml_ws, a.status);
+}
 
 // D7: out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i over the items of a sequence (Sec. 3.2.3: the
 // splits are merged by online log-sum-exp).
@@ -1188,8 +1217,16 @@ __device__ __forceinline__ float half_sum(float v)
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+struct MergeArgs {
+    const float *acc_ws;
+    const float *ml_ws;
+    const int32_t *seq_item_indptr;
+    int batch;
+    int n_q_heads;
+    float *out;
+};
 template <int VEC>
-__global__ __launch_bounds__(64 * kMergeWaves) void tkv_merge_kernel(
+__device__ __forceinline__ void merge_sequence(
     const float *__restrict__ acc_ws, const float *__restrict__ ml_ws, const int32_t *__restrict__ seq_item_indptr,
     int batch, int n_q_heads, float *__restrict__ out)
 {
@@ -1287,6 +1324,11 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tkv_merge_kernel(
     if constexpr (VEC == 2) *reinterpret_cast<float2 *>(dst) = make_float2(num[0] * r, num[VEC - 1] * r);
     else dst[0] = num[0] * r;
 }
+template <int VEC>
+__global__ __launch_bounds__(64 * kMergeWaves) void tkv_merge_kernel(MergeArgs a)
+{
+    merge_sequence<VEC>(a.acc_ws, a.ml_ws, a.seq_item_indptr, a.batch, a.n_q_heads, a.out);
+}
 
 // The merge behind workgroups of several items, which leave one partial for up to kTeam slots and m = -inf in the others.
 // A wavefront has two neighbouring heads, 32 lanes each, 16 bytes a lane: it lists the slots that hold something (128 at a
@@ -1297,7 +1339,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tkv_merge_kernel(
 constexpr int kTeamRows = 16, kTeamSlots = 128, kTeamMergeWaves = 8;
 constexpr uint32_t kNoRow = 0x7fff0000u;   // outside the buffer: zeros, no memory access
 template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void tkv_merge_teams_kernel(
+__device__ __forceinline__ void merge_teams(
     const float *__restrict__ acc_ws, const float *__restrict__ ml_ws, const int32_t *__restrict__ seq_item_indptr,
     int batch, int n_q_heads, float *__restrict__ out)
 {
@@ -1399,6 +1441,11 @@ __global__ __launch_bounds__(64 * WAVES) void tkv_merge_teams_kernel(
     const float r = den > 0.0f ? 1.0f / den : 0.0f;
     if (h < n_q_heads) reinterpret_cast<float4 *>(out + ((size_t)b * n_q_heads + h) * kHeadDim)[c4] = make_float4(num.x * r, num.y * r, num.z * r, num.w * r);
 }
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void tkv_merge_teams_kernel(MergeArgs a)
+{
+    merge_teams<WAVES>(a.acc_ws, a.ml_ws, a.seq_item_indptr, a.batch, a.n_q_heads, a.out);
+}
 
 // Sequences of hundreds of items, as a single long sequence with one kv head has them.  One workgroup of TH threads per
 // (sequence, query head, one of SL channel slices).  32 / SL lanes own an item at a time: their 16-byte loads are the item's
@@ -1406,7 +1453,7 @@ __global__ __launch_bounds__(64 * WAVES) void tkv_merge_teams_kernel(
 // workgroup round.  Each such lane group keeps a running (M, l, acc); the groups are merged through LDS by the first wavefront.
 constexpr int SL = 4, TH = 512;   // four workgroups per head, 64 item slots each
 constexpr uint32_t kRowsGridX = 1u << 22;   // workgroups are folded there: a grid dimension ends at 2^32 threads
-__global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(
+__device__ __forceinline__ void reduce_rows(
     const float *__restrict__ acc_ws, const float *__restrict__ ml_ws, const int32_t *__restrict__ seq_item_indptr,
     int n_rows /* sequences x query heads */, int n_q_heads, float *__restrict__ out)
 {
@@ -1477,6 +1524,10 @@ __global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(
             reinterpret_cast<float4 *>(out + ((size_t)b * n_q_heads + h) * kHeadDim)[cq] = make_float4(n.x * r, n.y * r, n.z * r, n.w * r);
     }
 }
+__global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(MergeArgs a)
+{
+    reduce_rows(a.acc_ws, a.ml_ws, a.seq_item_indptr, a.batch * a.n_q_heads, a.n_q_heads, a.out);
+}
 
 // Whether the split kernel joins the partials of neighbouring items: where they are more than 17408 rows (9 MB) of at most
 // 3072 wavefronts, which takes eight query heads per kv head and 2176 wavefronts.  Time over that of single items, 64 shapes of 1 to 8 kv
@@ -1508,9 +1559,9 @@ int tkv_launch_decode_split(const tkv_desc *desc, const void *pool, const uint8_
     while ((desc->n_kv_heads << log2_r) < n_q_heads) ++log2_r;
     constexpr int kMaxY = 65535;
     const dim3 grid((unsigned)desc->n_kv_heads, (unsigned)(n_groups < kMaxY ? n_groups : kMaxY), (unsigned)((n_groups + kMaxY - 1) / kMaxY));
-    hipLaunchKernelGGL(kernel, grid, dim3(teams ? 64 * kTeam : 64), 0, (hipStream_t)stream, (const uint8_t *)pool, bit_map, (const uint16_t *)q, page_indptr,
-                       page_ids, n_tok_int2, n_tok_int4, items, n_items, batch, desc->n_kv_heads, log2_r,
-                       desc->n_pages_int2, desc->n_pages_int4, kappa, acc_ws, ml_ws, status);
+    const DecodeArgs args = {(const uint8_t *)pool, bit_map, (const uint16_t *)q, page_indptr, page_ids, n_tok_int2, n_tok_int4, items, n_items, batch,
+                             desc->n_kv_heads, log2_r, desc->n_pages_int2, desc->n_pages_int4, kappa, acc_ws, ml_ws, status};
+    hipLaunchKernelGGL(kernel, grid, dim3(teams ? 64 * kTeam : 64), 0, (hipStream_t)stream, args);
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
 
@@ -1519,6 +1570,7 @@ int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indpt
 {
     const float *acc_ws = (const float *)workspace;
     const float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
+    const MergeArgs args = {acc_ws, ml_ws, seq_item_indptr, batch, n_q_heads, out};
     // The item counts are on the device; the average per sequence picks the kernel.  The longest sequence decides how long
     // either takes, and it may hold nearly all items.  Up to 128 on average the merge kernel is the faster one for equal
     // counts and for every skew (against a kernel of 8 item slots, which it has replaced; us alone, 64 heads: [250, 45, 45, 44] 8.8 ->
@@ -1532,19 +1584,17 @@ int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indpt
         const bool one = (int64_t)n_items <= 64 * (int64_t)batch;
         constexpr int kMaxY = 65535;
         const dim3 grid((unsigned)(n_q_heads + 1) / 2, (unsigned)(batch < kMaxY ? batch : kMaxY), (unsigned)((batch + kMaxY - 1) / kMaxY));
-        hipLaunchKernelGGL(one ? tkv_merge_teams_kernel<1> : tkv_merge_teams_kernel<kTeamMergeWaves>, grid, dim3(one ? 64 : 64 * kTeamMergeWaves), 0, (hipStream_t)stream, acc_ws, ml_ws,
-                           seq_item_indptr, batch, n_q_heads, out);
+        hipLaunchKernelGGL(one ? tkv_merge_teams_kernel<1> : tkv_merge_teams_kernel<kTeamMergeWaves>, grid, dim3(one ? 64 : 64 * kTeamMergeWaves), 0,
+                           (hipStream_t)stream, args);
     } else if ((int64_t)n_items <= 128 * (int64_t)batch && n_q_heads <= 1 << 17) {
         const bool two = (int64_t)batch * n_q_heads >= 256;
         constexpr int kMaxY = 65535;
         const dim3 grid((unsigned)n_q_heads * (two ? 1 : 2), (unsigned)(batch < kMaxY ? batch : kMaxY), (unsigned)((batch + kMaxY - 1) / kMaxY));
-        hipLaunchKernelGGL(two ? tkv_merge_kernel<2> : tkv_merge_kernel<1>, grid, dim3(64 * kMergeWaves), 0, (hipStream_t)stream, acc_ws, ml_ws,
-                           seq_item_indptr, batch, n_q_heads, out);
+        hipLaunchKernelGGL(two ? tkv_merge_kernel<2> : tkv_merge_kernel<1>, grid, dim3(64 * kMergeWaves), 0, (hipStream_t)stream, args);
     } else {
         const uint64_t blocks = (uint64_t)batch * n_q_heads * SL;
         const dim3 grid((unsigned)(blocks < kRowsGridX ? blocks : kRowsGridX), (unsigned)((blocks + kRowsGridX - 1) / kRowsGridX));
-        hipLaunchKernelGGL(tkv_reduce_rows_kernel, grid, dim3(TH), 0, (hipStream_t)stream, acc_ws, ml_ws, seq_item_indptr,
-                           batch * n_q_heads, n_q_heads, out);
+        hipLaunchKernelGGL(tkv_reduce_rows_kernel, grid, dim3(TH), 0, (hipStream_t)stream, args);
     }
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
