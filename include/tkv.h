@@ -307,8 +307,9 @@ int tkv_gather_dequant(const tkv_desc *desc, const void *pool, const uint8_t *bi
  * that a whole MI355X holds at once, every item gets as many pages as that part
  * instead: fewer items, none with more pages than the longest equal part and,
  * at four pages, none of a greater cost than the heaviest.  Under the same
- * condition, where every part is a single page and the pages times the kv heads
- * are more than 2048 (and at most 3072), an item gets two.
+ * condition, where the longest part has one page (two pages) and the pages times
+ * the kv heads are more than 2048 (4096) and at most 3072 (6144), an item gets a
+ * page more than that.
  * A plan depends only on the page COUNTS of the sequences: it stays valid while
  * tokens are appended to open pages (the kernel reads the token counts from the
  * device arrays and masks by them) and must be made again when a sequence gains

@@ -410,15 +410,17 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
             n_full += ceil_div(ceil_div(n_tok_int2[b], kPageTokens) + ceil_div(n_tok_int4[b], kPageTokens), (int32_t)longest);
         full = 5 * n_full <= 4 * (int64_t)target_items;
     }
-    // Single pages on more than two wavefronts per SIMD go in pairs: half the wavefronts, each with one more page, prepare q and
-    // leave a partial half as often, ask for half the first records at once, and the merge has half the rows.  Time of pairs
-    // over that of single pages, 1 to 8 kv heads, 1 to 8 query heads each, ragged and even, least / mean / worst: 950 to 1150
-    // (page, kv head) records .89 / 1.02 / 1.14, to 1536 .87 / 1.02 / 1.11, to 1792 .88 / .99 / 1.10, to 2048 .84 / .95 / 1.05,
-    // to 2300 .82 / .91 / .98, to 3072 .77 / .87 / .94 (16 contexts of 97 to 6011 tokens 13.9 us, now 12.2).  Three pages are
-    // within .05 of two either way up to 3072.
+    // Parts of one or two pages on more than two wavefronts per SIMD get a page more: fewer wavefronts, which prepare q and
+    // leave a partial less often, ask for fewer first records at once, and leave the merge fewer rows.  Time over that of one page
+    // less, 1 to 8 kv heads, 1 to 8 query heads each, ragged and even, least / mean / worst.  Pairs instead of single pages: 950 to
+    // 1150 (page, kv head) records .89 / 1.02 / 1.14, to 1536 .87 / 1.02 / 1.11, to 1792 .88 / .99 / 1.10, to 2048 .84 / .95 / 1.05, to 2300
+    // .82 / .91 / .98, to 3072 .77 / .87 / .94 (16 contexts of 97 to 6011 tokens 13.9 us, now 12.2).  Three instead of two:
+    // 3072 to 4096 records .94 / 1.01 / 1.07, to 6144 .87 / .93 / .98.  Three instead of one are within .05 of two up to 3072.  (From
+    // three to four it would be .86 / .93 / .99 below 8500 records; those items are as long as the longest equal part, above.)
     const int64_t n_records = (pages2 + pages4) * desc->n_kv_heads;
-    if (longest == 1 && n_records > kResident / 3 * 2 && n_records <= kResident && (int64_t)target_items * desc->n_kv_heads <= kResident) {
-        longest = 2;
+    if (longest <= 2 && n_records > kResident / 3 * 2 * longest && n_records <= kResident * longest &&
+        (int64_t)target_items * desc->n_kv_heads <= kResident) {
+        ++longest;
         full = true;
     }
     const int64_t most = longest <= 3 ? longest * kCost4 : heaviest;

@@ -1,5 +1,5 @@
-"""The decode planner's rule for single pages: in pairs above 2048 (page, kv head) records, up to the 3072 wavefronts that the
-device holds at once."""
+"""The decode planner's rule for parts of one or two pages: a page more above 2048 (page, kv head) records per page, up to the 3072
+wavefronts that the device holds at once."""
 import numpy as np
 import pytest
 
@@ -19,12 +19,14 @@ CASES = [
     (4, [3] * 90 + [0], [4] * 90 + [1], 768, 2),                                          # an odd page at every end, pairs of both widths
     (3, [1] * 900, [0] * 900, 1024, 1),                                                   # a page each: nothing to pair
     (8, [300], [0], 385, 1), (8, [300], [0], 1000, 1),                                    # more items asked for than run at once
+    (8, [512], [0], 384, 2), (8, [513], [0], 384, 3), (8, [400], [368], 384, 3),          # 4096, 4104, 6144 records
+    (1, [1000, 1097], [1000, 1000], 3072, 3), (2, [1, 2, 500], [700, 1, 900], 1536, 3),   # odd ends
 ]
 
 
 @pytest.mark.parametrize("axis", [tkv.TKV_KEYS_PER_TOKEN, tkv.TKV_KEYS_PER_CHANNEL])
 @pytest.mark.parametrize("heads,p2,p4,target,size", CASES)
-def test_single_pages_go_in_pairs(heads, p2, p4, target, size, axis):
+def test_short_parts_get_a_page_more(heads, p2, p4, target, size, axis):
     items, sip = _plan(heads, p2, p4, target, axis)
     want = [(b, a, min(a + size, x + y)) for b, (x, y) in enumerate(zip(p2, p4)) for a in range(0, x + y, size)]
     assert [tuple(i[:3]) for i in items[np.argsort(items[:, 3])].tolist()] == want
