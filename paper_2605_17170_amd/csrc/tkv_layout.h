@@ -76,6 +76,14 @@ __device__ __forceinline__ void store_once(uint4 *p, uint4 v)
 __device__ __forceinline__ void store_once(uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void store_once(uint16_t *p, uint16_t v) { __builtin_nontemporal_store(v, p); }
 
+// A store_once that the L2 passes on to memory at once, as store_through below.  (No builtin for global memory has both; the wait
+// state is what a store of more than 64 bits needs before its registers are written again.)
+__device__ __forceinline__ void store_once_through(uint4 *p, uint4 v)
+{
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    const u32x4_t t = {v.x, v.y, v.z, v.w};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" :: "v"(p), "v"(t) : "memory");
+}
 // A store that the L2 of the XCD passes on to memory at once (device scope), for what the next launch reads: a launch ends with the
 // write-back of the lines that are still dirty in the eight L2s, and the next one begins behind it.  Only where one store instruction
 // fills whole 128-byte lines and the launch is short: parts of lines, and streams that fill the memory's write path, are slower
