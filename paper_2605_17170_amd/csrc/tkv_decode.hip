@@ -836,24 +836,22 @@ struct PartialRows {
 };
 // ---- workgroups of several wavefronts: one partial for the items of a sequence -----------------------------------------
 // With as many wavefronts as the device holds and eight query heads each, the partials of single items are 12.8 MB, written
-// at the end of the launch and read at once by the merge, which takes as long for them as for the way from launch to launch.
-// Four wavefronts that are neighbours in the launch order, one on each SIMD of a compute unit, mostly have the same sequence
-// (the order is stable): their partials are joined in LDS, a quarter of the rows is left.  From the last store of the split to
-// the last of the merge 5.8 -> 3.9 us (8 x 32768), 5.9 -> 5.0 (32 contexts of 4K to 128K); in_teams says where.
+// at the end of the launch and read at once by the merge.  Four wavefronts that are neighbours in the launch order, one on each
+// SIMD of a compute unit, mostly have the same sequence (the order is stable): their partials are joined in LDS, a quarter of the
+// rows is left, and ordinary stores do best for those.  in_teams says where.
 constexpr int kTeam = 4;                   // wavefronts of a workgroup, one per SIMD
 constexpr int kOutRow = kHeadDim + 4;      // floats of a head's row in a wavefront's output tile
 struct Member { int seq, slot; };          // of a wavefront: its sequence (-1: it has nothing to add), the slot of its item
 template <bool KC, int TEAM> struct TeamLds { Lds<KC> wave[TEAM]; };
-template <bool KC> struct TeamLds<KC, kTeam> {
-    Lds<KC> wave[kTeam];
+template <> struct TeamLds<false, kTeam> {   // (per-token keys, see in_teams)
+    Lds<false> wave[kTeam];
     Member member[kTeam];
 };
 // 2^(m - M), and 0 for m = -inf: an item without tokens has m = -inf, l = 0 and weighs nothing
 __device__ __forceinline__ float merge_weight(float m, float M) { return m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M); }
 // Joins the tiles [head][channel] and (m, l) pairs that the wavefronts hold in LDS, by sequence: the joined partial goes to the
 // slot of the sequence's first wavefront here, the slots of the others get m = -inf.
-template <bool KC>
-__device__ __forceinline__ void join_team(TeamLds<KC, kTeam> &team, float *__restrict__ acc_ws, float *__restrict__ ml_ws, int n_q_heads, int kvh, int R)
+__device__ __forceinline__ void join_team(TeamLds<false, kTeam> &team, float *__restrict__ acc_ws, float *__restrict__ ml_ws, int n_q_heads, int kvh, int R)
 {
     __syncthreads();
     const int head = threadIdx.x >> 5, c4 = threadIdx.x & 31;
@@ -888,14 +886,9 @@ __device__ __forceinline__ void join_team(TeamLds<KC, kTeam> &team, float *__res
             num.z = fmaf(wt, a.z, num.z);
             num.w = fmaf(wt, a.w, num.w);
         }
-        const int slot = __builtin_amdgcn_readfirstlane(team.member[lead].slot);
-        PartialRows(acc_ws, ml_ws, slot, n_q_heads, kvh * R, R).put(head, c4, num);
-#pragma unroll
-        for (int w = 0; w < kTeam; ++w) {
-            if (!((mine >> w) & 1)) continue;
-            const int own_slot = __builtin_amdgcn_readfirstlane(team.member[w].slot);
-            if (c4 == 0) PartialRows(acc_ws, ml_ws, own_slot, n_q_heads, kvh * R, R).put(head, w == lead ? make_float2(M, den) : make_float2(-INFINITY, 0.0f));
-        }
+        reinterpret_cast<float4 *>(acc_ws + ((size_t)team.member[lead].slot * n_q_heads + h) * kHeadDim)[c4] = num;
+        if (c4 < kTeam && ((mine >> c4) & 1))
+            reinterpret_cast<float2 *>(ml_ws)[(size_t)team.member[c4].slot * n_q_heads + h] = c4 == lead ? make_float2(M, den) : make_float2(-INFINITY, 0.0f);
         todo &= ~mine;
     }
 }
@@ -1171,7 +1164,7 @@ __device__ __forceinline__ void decode_items(
     }
     }
     } while (false);
-    if constexpr (TEAM > 1) join_team<KC>(team, acc_ws, ml_ws, n_kv_heads << log2_r, blockIdx.x, 1 << log2_r);
+    if constexpr (TEAM > 1) join_team(team, acc_ws, ml_ws, n_kv_heads << log2_r, blockIdx.x, 1 << log2_r);
 }
 template <bool KC, int TEAM>
 __global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3))) void tkv_decode_kernel(DecodeArgs a)
@@ -1545,14 +1538,15 @@ __global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(MergeArgs a)
 }
 
 // Whether the split kernel joins the partials of neighbouring items: where they are more than 17408 rows (9 MB) of at most
-// 3072 wavefronts, which takes eight query heads per kv head and 2176 wavefronts.  Time over that of single items, 64 shapes of 1 to 8 kv
-// heads, least / mean / worst: above the line .92 / .97 / 1.02 (8 x 32768 47.7 -> 45.9 us, with per-channel keys 52.9 -> 51.8, 32
-// contexts of 4K to 128K 164.8 -> 162.6); 14000 to 17408 rows .90 / .97 / 1.03, 12000 to 14000 .92 / .99 / 1.03, below .94 / 1.04 /
-// 1.19: the barrier and the way through LDS cost what fewer rows save.  More wavefronts than run at once wait for whole
-// workgroups to end; they are single sequences mostly.  (It goes by what both launches are given: split and merge agree.)
+// 3072 wavefronts, which takes eight query heads per kv head and 2176 wavefronts, and the keys are per token.  Joined and left in
+// the L2 against single and written through, us: 32 contexts of 4K to 128K 161.0 | 163.4 (another box 161.4 | 164.5), 8 x 32768
+// 45.1 | 45.7 (46.3 | 46.2), 3 x 128000 63.8 | 63.1; joined and written through 162.9, 45.5; with per-channel keys 51.6 |
+// 51.0.  With fewer rows the barrier and the way through LDS cost more than the rows (four-layer step 75.5 | 67.9, 4 x 102400 on
+// one head 19.7 | 17.5).  More wavefronts than run at once wait for whole workgroups to end; they are single sequences
+// mostly.  (It goes by what both launches are given: split and merge agree.)
 bool in_teams(const tkv_desc *desc, int32_t n_items, int32_t n_q_heads)
 {
-    return (int64_t)n_items * n_q_heads > 17408 && (int64_t)n_items * desc->n_kv_heads <= 3072;
+    return desc->int2_key_axis == TKV_KEYS_PER_TOKEN && (int64_t)n_items * n_q_heads > 17408 && (int64_t)n_items * desc->n_kv_heads <= 3072;
 }
 
 } // namespace
@@ -1567,7 +1561,7 @@ int tkv_launch_decode_split(const tkv_desc *desc, const void *pool, const uint8_
     float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
     const float kappa = sm_scale * 1.44269504088896340736f;
     const bool teams = in_teams(desc, n_items, n_q_heads);
-    auto kernel = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL ? (teams ? tkv_decode_kernel<true, kTeam> : tkv_decode_kernel<true, 1>)
+    auto kernel = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL ? tkv_decode_kernel<true, 1>
                                                               : (teams ? tkv_decode_kernel<false, kTeam> : tkv_decode_kernel<false, 1>);
     const int n_groups = teams ? (n_items + kTeam - 1) / kTeam : n_items;
     int log2_r = 0;   // 1, 2, 4 or 8 query heads per kv head
