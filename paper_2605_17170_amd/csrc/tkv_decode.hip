@@ -6,6 +6,8 @@
 // sequence's page list.  All query heads that share the kv head (up to 8)
 // are processed together so the packed KV bytes are read from HBM once; the
 // partials (m, l, acc) of the items are merged by tkv_merge_kernel or tkv_reduce_rows_kernel.
+// In the largest launches four wavefronts form a workgroup and join the partials of a
+// sequence's items in LDS (in_teams); tkv_merge_teams_kernel merges those.
 //
 // Matrix cores do both contractions (v_mfma_f32_16x16x32_f16), fp32 accumulate,
 // and the packed codes are never expanded by arithmetic: a masked 16-bit field

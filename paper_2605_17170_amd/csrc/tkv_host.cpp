@@ -415,7 +415,8 @@ int32_t tkv_plan_decode(const tkv_desc *desc, int32_t batch, const int32_t *page
     // less, 1 to 8 kv heads, 1 to 8 query heads each, ragged and even, least / mean / worst.  Pairs instead of single pages: 950 to
     // 1150 (page, kv head) records .89 / 1.02 / 1.14, to 1536 .87 / 1.02 / 1.11, to 1792 .88 / .99 / 1.10, to 2048 .84 / .95 / 1.05, to 2300
     // .82 / .91 / .98, to 3072 .77 / .87 / .94 (16 contexts of 97 to 6011 tokens 13.9 us, now 12.2).  Three instead of two:
-    // 3072 to 4096 records .94 / 1.01 / 1.07, to 6144 .87 / .93 / .98.  Three instead of one are within .05 of two up to 3072.  (From
+    // 3072 to 4096 records .94 / 1.01 / 1.07, to 6144 .87 / .93 / .98.  (Again with the partials written through: pairs from 2049 to
+    // 3072 .80 / .90 / .99, three from 4097 to 6144 .86 / .93 / .99.)  Three instead of one are within .05 of two up to 3072.  (From
     // three to four it would be .86 / .93 / .99 below 8500 records; those items are as long as the longest equal part, above.)
     const int64_t n_records = (pages2 + pages4) * desc->n_kv_heads;
     if (longest <= 2 && n_records > kResident / 3 * 2 * longest && n_records <= kResident * longest &&
