@@ -1541,7 +1541,7 @@ __global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(MergeArgs a)
 
 // Whether the split kernel joins the partials of neighbouring items: where they are more than 17408 rows (9 MB) of at most
 // 3072 wavefronts, which takes eight query heads per kv head and 2176 wavefronts, and the keys are per token.  Joined and left in
-// the L2 against single and written through, us: 32 contexts of 4K to 128K 161.0 | 163.4 (another box 161.4 | 164.5), 8 x 32768
+// the L2 against single and written through, us: 32 contexts of 4K to 128K 161.0 | 163.4 (on another device 161.4 | 164.5), 8 x 32768
 // 45.1 | 45.7 (46.3 | 46.2), 3 x 128000 63.8 | 63.1; joined and written through 162.9, 45.5; with per-channel keys 51.6 |
 // 51.0.  With fewer rows the barrier and the way through LDS cost more than the rows (four-layer step 75.5 | 67.9, 4 x 102400 on
 // one head 19.7 | 17.5).  More wavefronts than run at once wait for whole workgroups to end; they are single sequences
