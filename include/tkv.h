@@ -392,15 +392,10 @@ int tkv_decode_attention(const tkv_desc *desc, const void *pool, const uint8_t *
 
 /*
  * The two launches of tkv_decode_attention as separate calls, same arguments
- * and the same checks: D2-D6, the split kernel, which leaves a partial
+ * and the same checks: D2-D6, the split kernel, which leaves one partial
  * (m, l, acc) per work item and query head in `workspace`; and D7, the
  * cross-split merge by log-sum-exp (Sec. 3.2.3), which reads the partials
  * and writes `out`.  tkv_decode_attention is exactly one call of each.
- * With per-token keys and more than 17408 items times query heads, of at most
- * 3072 items times kv heads, up to four items of a sequence share one partial: it
- * lies in the slot of one of them, the others' slots have m = -inf and an acc that
- * is not written.
- * Both calls go by n_items, n_q_heads and the descriptor, which must be the same.
  */
 int tkv_decode_split(const tkv_desc *desc, const void *pool, const uint8_t *bit_map,
                      const void *q, const int32_t *page_indptr, const int32_t *page_ids,

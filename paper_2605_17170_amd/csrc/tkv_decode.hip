@@ -6,8 +6,6 @@
 // sequence's page list.  All query heads that share the kv head (up to 8)
 // are processed together so the packed KV bytes are read from HBM once; the
 // partials (m, l, acc) of the items are merged by tkv_merge_kernel or tkv_reduce_rows_kernel.
-// In the largest launches four wavefronts form a workgroup and join the partials of a
-// sequence's items in LDS (in_teams); tkv_merge_teams_kernel merges those.
 //
 // Matrix cores do both contractions (v_mfma_f32_16x16x32_f16), fp32 accumulate,
 // and the packed codes are never expanded by arithmetic: a masked 16-bit field
@@ -836,65 +834,6 @@ struct PartialRows {
     __device__ __forceinline__ void put(int head, int c4, float4 v) const { store_through(acc, head * (kHeadDim * 4) + c4 * 16, v); }
     __device__ __forceinline__ void put(int head, float2 v) const { store_through(ml, head * 8, v); }
 };
-// ---- workgroups of several wavefronts: one partial for the items of a sequence -----------------------------------------
-// With as many wavefronts as the device holds and eight query heads each, the partials of single items are 12.8 MB, written
-// at the end of the launch and read at once by the merge.  Four wavefronts that are neighbours in the launch order, one on each
-// SIMD of a compute unit, mostly have the same sequence (the order is stable): their partials are joined in LDS, a quarter of the
-// rows is left, and ordinary stores do best for those.  in_teams says where.
-constexpr int kTeam = 4;                   // wavefronts of a workgroup, one per SIMD
-constexpr int kOutRow = kHeadDim + 4;      // floats of a head's row in a wavefront's output tile
-struct Member { int seq, slot; };          // of a wavefront: its sequence (-1: it has nothing to add), the slot of its item
-template <bool KC, int TEAM> struct TeamLds { Lds<KC> wave[TEAM]; };
-template <> struct TeamLds<false, kTeam> {   // (per-token keys, see in_teams)
-    Lds<false> wave[kTeam];
-    Member member[kTeam];
-};
-// 2^(m - M), and 0 for m = -inf: an item without tokens has m = -inf, l = 0 and weighs nothing
-__device__ __forceinline__ float merge_weight(float m, float M) { return m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M); }
-// Joins the tiles [head][channel] and (m, l) pairs that the wavefronts hold in LDS, by sequence: the joined partial goes to the
-// slot of the sequence's first wavefront here, the slots of the others get m = -inf.
-__device__ __forceinline__ void join_team(TeamLds<false, kTeam> &team, float *__restrict__ acc_ws, float *__restrict__ ml_ws, int n_q_heads, int kvh, int R)
-{
-    __syncthreads();
-    const int head = threadIdx.x >> 5, c4 = threadIdx.x & 31;
-    if (head >= R) return;
-    const int h = kvh * R + head;
-    int seq[kTeam];
-#pragma unroll
-    for (int w = 0; w < kTeam; ++w) seq[w] = __builtin_amdgcn_readfirstlane(team.member[w].seq);
-    int todo = 0;   // the wavefronts that have something to add and are in no joined partial yet
-#pragma unroll
-    for (int w = 0; w < kTeam; ++w) todo |= seq[w] >= 0 ? 1 << w : 0;
-#pragma unroll 1
-    while (todo) {
-        const int lead = __builtin_ctz(todo), own = __builtin_amdgcn_readfirstlane(team.member[lead].seq);
-        float m[kTeam], M = -INFINITY, den = 0.0f;
-        float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-        int mine = 0;
-#pragma unroll
-        for (int w = 0; w < kTeam; ++w) {
-            mine |= seq[w] == own ? 1 << w : 0;
-            m[w] = seq[w] == own ? team.wave[w].alpha[head] : -INFINITY;
-            M = fmaxf(M, m[w]);
-        }
-#pragma unroll
-        for (int w = 0; w < kTeam; ++w) {
-            if (!((mine >> w) & 1)) continue;
-            const float wt = merge_weight(m[w], M);
-            const float4 a = reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(&team.wave[w]) + head * kOutRow)[c4];
-            den = fmaf(wt, team.wave[w].zl[head][4], den);
-            num.x = fmaf(wt, a.x, num.x);
-            num.y = fmaf(wt, a.y, num.y);
-            num.z = fmaf(wt, a.z, num.z);
-            num.w = fmaf(wt, a.w, num.w);
-        }
-        reinterpret_cast<float4 *>(acc_ws + ((size_t)team.member[lead].slot * n_q_heads + h) * kHeadDim)[c4] = num;
-        if (c4 < kTeam && ((mine >> c4) & 1))
-            reinterpret_cast<float2 *>(ml_ws)[(size_t)team.member[c4].slot * n_q_heads + h] = c4 == lead ? make_float2(M, den) : make_float2(-INFINITY, 0.0f);
-        todo &= ~mine;
-    }
-}
-
 // The kernels take their arguments as one struct: the runtime looks every pointer argument up on the way to a launch, and small calls
 // wait for their two launches (eighteen arguments 2.7 us, a struct of them 2.4, on a slower host 3.8 and 3.3; step of five layers over
 // 19 pages 64 -> 57 us, tiny calls 1 to 7 %).  The bodies are functions with parameters of their own, which the compiler then
@@ -920,34 +859,26 @@ struct DecodeArgs {
     int32_t *status;
 };
 // KC: the INT2 keys of the pool are quantised per channel over 32-token blocks (Sec. 3.2.1).
-// TEAM wavefronts, one work item each, form a workgroup: with one of them every item leaves a partial in its slot, with kTeam
-// the items of a sequence share one (join_team).
-// The grid is (kv heads, groups of TEAM items): the workgroups of an item are launched one behind the other, without a division to
+// The grid is (kv heads, items): the workgroups of an item are launched one behind the other, without a division to
 // find the item.
-template <bool KC, int TEAM>
-__device__ __forceinline__ void decode_items(
+template <bool KC>
+__device__ __forceinline__ void decode_item(
     const uint8_t *__restrict__ pool, const uint8_t *__restrict__ bit_map, const uint16_t *__restrict__ q,
     const int32_t *__restrict__ page_indptr, const int32_t *__restrict__ page_ids,
     const int32_t *__restrict__ n_tok_int2, const int32_t *__restrict__ n_tok_int4,
     const int32_t *__restrict__ items, int n_items, int batch, int n_kv_heads, int log2_r, int n_pages_int2, int n_pages_int4,
     float kappa, float *__restrict__ acc_ws, float *__restrict__ ml_ws, int32_t *status)
 {
-    __shared__ TeamLds<KC, TEAM> team;
-    const int wave = TEAM == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    Lds<KC> &lds = team.wave[wave];
-    const int lane = TEAM == 1 ? threadIdx.x : threadIdx.x & 63, r16 = lane & 15, q4 = lane >> 4;
-    if constexpr (TEAM > 1) {
-        if (lane == 0) team.member[wave] = Member{-1, 0};   // nothing to add so far
-    }
-    do {   // (a wavefront without an item, or with one that adds nothing, leaves by `break`: in a team it takes part in the joining)
+    __shared__ Lds<KC> lds;
+    const int lane = threadIdx.x, r16 = lane & 15, q4 = lane >> 4;
     // Everything of a level of the chain arguments -> item -> counts -> page ids at once: fetched where each is first used,
     // the arguments and counts alone are six round trips in a row.  (16 contexts of 97 to 6011 tokens 14.45 -> 14.1 us, 4 x
     // 102400 on one head 18.5 -> 18.2, 8 contexts of 2000 to 16000 20.1 -> 19.3, four-layer step 79.5 -> 78.1.)
     asm volatile("" :: "s"(pool), "s"(bit_map), "s"(q), "s"(page_indptr), "s"(page_ids), "s"(n_tok_int2), "s"(n_tok_int4), "s"(items),
                  "s"(n_items), "s"(batch), "s"(n_kv_heads), "s"(log2_r), "s"(n_pages_int2), "s"(n_pages_int4), "s"(acc_ws), "s"(ml_ws), "s"(status),
                  "s"(gridDim.y));
-    const int item = (int)(blockIdx.y + blockIdx.z * gridDim.y) * TEAM + wave, kvh = blockIdx.x;
-    if (item >= n_items) break;
+    const int item = blockIdx.y + blockIdx.z * gridDim.y, kvh = blockIdx.x;
+    if (item >= n_items) return;
     const int R = 1 << log2_r, n_q_heads = n_kv_heads << log2_r;
     // The partial of this item goes to slot items[4*item + 3] of the workspace: items are listed in launch order,
     // the slots of a sequence are contiguous (the merge reads them by sequence).
@@ -971,7 +902,7 @@ __device__ __forceinline__ void decode_items(
         // the workspace held before
         if (slot_ok) write_empty();
         if (status && lane == 0) atomicOr(status, TKV_STATUS_BAD_ITEM);
-        break;
+        return;
     }
     const int np2 = (n2 + kPageTokens - 1) / kPageTokens, np4 = (n4 + kPageTokens - 1) / kPageTokens;
     const int seq_pages = list1 - list0;
@@ -995,7 +926,7 @@ __device__ __forceinline__ void decode_items(
     const int first = has2 ? pb : b4;   // the first list position that is read: more than pb where there is no INT2 pool
     if (!(has2 || has4)) {   // an item without pages
         write_empty();
-        break;
+        return;
     }
     const ItemCtx cx = {pool, bit_map, pages, pb, pe, np2, np4, n2 - (np2 - 1) * kPageTokens, n4 - (np4 - 1) * kPageTokens,
                         kvh, n_kv_heads, n_pages_int2, n_pages_total, lane, status};
@@ -1143,6 +1074,7 @@ __device__ __forceinline__ void decode_items(
     // instruction covers two whole heads (a lane holds single channels of four heads).  The tile takes the start of
     // the LDS, which holds nothing the epilogue needs (page staging, q operands); rows are 16 bytes longer than a
     // head so that heads h and h + 4, written by the same instruction, fall on different banks.
+    constexpr int kOutRow = kHeadDim + 4;
     static_assert(sizeof(lds.ks) + sizeof(lds.pv) + sizeof(lds.qo) >= 8 * kOutRow * sizeof(float), "the output tile must fit in what precedes zl and alpha in Lds");
     float *tile = reinterpret_cast<float *>(&lds);
 #pragma unroll
@@ -1153,9 +1085,6 @@ __device__ __forceinline__ void decode_items(
         for (int comp = 0; comp < 4; ++comp)
             tile[head * kOutRow + 64 * half + 16 * comp + r16] = fmaf(add_pieces(st.acc[0][comp][i], st.acc[1][comp][i]), unscale, comp < 2 ? zsum.x : zsum.y);
     }
-    if constexpr (TEAM > 1) {
-        if (lane == 0) team.member[wave] = Member{seq, slot};
-    } else {
     const PartialRows partial(acc_ws, ml_ws, slot, n_q_heads, kvh * R, R);
     if (lane < 8) partial.put(lane, make_float2(lds.alpha[lane], lds.zl[lane][4]));
     lds_order();
@@ -1164,15 +1093,12 @@ __device__ __forceinline__ void decode_items(
         const int head = 2 * k + (lane >> 5), c4 = lane & 31;
         partial.put(head, c4, reinterpret_cast<const float4 *>(tile + head * kOutRow)[c4]);
     }
-    }
-    } while (false);
-    if constexpr (TEAM > 1) join_team(team, acc_ws, ml_ws, n_kv_heads << log2_r, blockIdx.x, 1 << log2_r);
 }
-template <bool KC, int TEAM>
-__global__ __launch_bounds__(64 * TEAM) __attribute__((amdgpu_waves_per_eu(3, 3))) void tkv_decode_kernel(DecodeArgs a)
+template <bool KC>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void tkv_decode_kernel(DecodeArgs a)
 {
-    decode_items<KC, TEAM>(a.pool, a.bit_map, a.q, a.page_indptr, a.page_ids, a.n_tok_int2, a.n_tok_int4, a.items, a.n_items, a.batch,
-                           a.n_kv_heads, a.log2_r, a.n_pages_int2, a.n_pages_int4, a.kappa, a.acc_ws, a.ml_ws, a.status);
+    decode_item<KC>(a.pool, a.bit_map, a.q, a.page_indptr, a.page_ids, a.n_tok_int2, a.n_tok_int4, a.items, a.n_items, a.batch,
+                    a.n_kv_heads, a.log2_r, a.n_pages_int2, a.n_pages_int4, a.kappa, a.acc_ws, a.ml_ws, a.status);
 }
 
 // D7: out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i over the items of a sequence (Sec. 3.2.3: the
@@ -1208,25 +1134,9 @@ __device__ __forceinline__ float wave_max(float v)
     return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(i, 0)), __int_as_float(__builtin_amdgcn_readlane(i, 16))),
                  fmaxf(__int_as_float(__builtin_amdgcn_readlane(i, 32)), __int_as_float(__builtin_amdgcn_readlane(i, 48))));
 }
+// 2^(m - M), and 0 for m = -inf: an item without tokens has m = -inf, l = 0 and weighs nothing
+__device__ __forceinline__ float merge_weight(float m, float M) { return m == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m - M); }
 
-// max / sum over the 32 lanes of a half wavefront, in every lane of it
-__device__ __forceinline__ float half_max(float v)
-{
-    v = fmaxf(v, row_dpp<0xB1>(v));
-    v = fmaxf(v, row_dpp<0x4E>(v));
-    v = fmaxf(v, row_dpp<0x141>(v));
-    v = fmaxf(v, row_dpp<0x140>(v));
-    return swap_max(__builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
-}
-__device__ __forceinline__ float half_sum(float v)
-{
-    v += row_dpp<0xB1>(v);
-    v += row_dpp<0x4E>(v);
-    v += row_dpp<0x141>(v);
-    v += row_dpp<0x140>(v);
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 struct MergeArgs {
     const float *acc_ws;
     const float *ml_ws;
@@ -1340,123 +1250,6 @@ __global__ __launch_bounds__(64 * kMergeWaves) void tkv_merge_kernel(MergeArgs a
     merge_sequence<VEC>(a.acc_ws, a.ml_ws, a.seq_item_indptr, a.batch, a.n_q_heads, a.out);
 }
 
-// The merge behind workgroups of several items, which leave one partial for up to kTeam slots and m = -inf in the others.
-// A wavefront has two neighbouring heads, 32 lanes each, 16 bytes a lane: it lists the slots that hold something (128 at a
-// time, through LDS) and reads those, 16 rows at once.  What bounds it is latency: item list -> (m, l) pairs -> rows.  One wavefront
-// does for 64 slots per sequence on average (it goes on for longer ones), eight share them above that.  64 heads, sequences x slots with
-// every fourth in use, us alone, against tkv_merge_kernel over as many rows as slots: 8 x 48 2.45 (3.9), 32 x 12 2.8 (4.05), 32
-// between 2 and 33 2.8 (4.7).
-constexpr int kTeamRows = 16, kTeamSlots = 128, kTeamMergeWaves = 8;
-constexpr uint32_t kNoRow = 0x7fff0000u;   // outside the buffer: zeros, no memory access
-template <int WAVES>
-__device__ __forceinline__ void merge_teams(
-    const float *__restrict__ acc_ws, const float *__restrict__ ml_ws, const int32_t *__restrict__ seq_item_indptr,
-    int batch, int n_q_heads, float *__restrict__ out)
-{
-    __shared__ uint2 list_s[WAVES][2][kTeamSlots + kTeamRows];   // per head: where the row starts, its weight
-    __shared__ float4 num_s[WAVES][64];
-    __shared__ float2 ml_s[WAVES][2];
-    asm volatile("" :: "s"(acc_ws), "s"(ml_ws), "s"(seq_item_indptr), "s"(batch), "s"(n_q_heads), "s"(out), "s"(gridDim.y));   // all arguments at once
-    const int b = blockIdx.y + blockIdx.z * gridDim.y, lane = threadIdx.x & 63, wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (b >= batch) return;
-    const int half = lane >> 5, c4 = lane & 31, h = 2 * blockIdx.x + half, head = h < n_q_heads ? h : n_q_heads - 1;
-    int i0 = ((ConstWords)seq_item_indptr)[b], i1 = ((ConstWords)seq_item_indptr)[b + 1];
-    if constexpr (WAVES > 1) {
-        const int per = (i1 - i0 + WAVES - 1) / WAVES;
-        i0 += wave * per;
-        i1 = i0 + per < i1 ? i0 + per : i1;
-    }
-    const uint32_t stride = (uint32_t)n_q_heads * (kHeadDim * 4);
-    float M = -INFINITY, den = 0.0f;
-    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i = i0; i < i1; i += kTeamSlots) {
-        const int n = i1 - i < kTeamSlots ? i1 - i : kTeamSlots;
-        const Record rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(acc_ws + (size_t)i * n_q_heads * kHeadDim), 0, (uint32_t)n * stride, 0x00027000);
-        const Record mls = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(ml_ws + (size_t)i * n_q_heads * 2), 0, (uint32_t)(n * n_q_heads) * 8u, 0x00027000);
-        float2 ml[kTeamSlots / 32];
-        float Mn = M;
-#pragma unroll
-        for (int c = 0; c < kTeamSlots / 32; ++c) {
-            const uint2 t = buffer_load8(mls, (int)(((uint32_t)(32 * c + c4) * (uint32_t)n_q_heads + (uint32_t)head) * 8u), 0);
-            ml[c] = 32 * c + c4 < n ? make_float2(__uint_as_float(t.x), __uint_as_float(t.y)) : make_float2(-INFINITY, 0.0f);
-        }
-#pragma unroll
-        for (int c = 0; c < kTeamSlots / 32; ++c) Mn = fmaxf(Mn, ml[c].x);
-        Mn = half_max(Mn);
-        float d = 0.0f;
-        int live = 0;
-#pragma unroll
-        for (int c = 0; c < kTeamSlots / 32; ++c) {
-            const float w = merge_weight(ml[c].x, Mn);
-            d = fmaf(w, ml[c].y, d);
-            const uint64_t mask = __ballot(ml[c].x != -INFINITY);
-            const uint32_t any = (uint32_t)mask | (uint32_t)(mask >> 32);   // of either head
-            const int at = live + __popc(any & ((1u << c4) - 1u));
-            if ((any >> c4) & 1u)
-                list_s[wave][half][at] = make_uint2(ml[c].x != -INFINITY ? (uint32_t)(32 * c + c4) * stride : kNoRow, __float_as_uint(w));
-            live += __popc(any);
-        }
-        if (c4 < kTeamRows) list_s[wave][half][live + c4] = make_uint2(kNoRow, 0u);
-        lds_order();
-        const float so = merge_weight(M, Mn);
-        den = fmaf(den, so, half_sum(d));
-        num = make_float4(num.x * so, num.y * so, num.z * so, num.w * so);
-        const uint32_t mine = (uint32_t)head * (kHeadDim * 4) + 16u * c4;
-        for (int k = 0; k < live; k += kTeamRows) {
-            uint4 a[kTeamRows];
-            float weight[kTeamRows];
-#pragma unroll
-            for (int r = 0; r < kTeamRows; ++r) {
-                const uint2 e = list_s[wave][half][k + r];
-                a[r] = buffer_load16_once(rows, (int)(e.x + mine), 0);
-                weight[r] = __uint_as_float(e.y);
-            }
-#pragma unroll
-            for (int r = 0; r < kTeamRows; ++r) {
-                const float w = weight[r];
-                num.x = fmaf(w, __uint_as_float(a[r].x), num.x);
-                num.y = fmaf(w, __uint_as_float(a[r].y), num.y);
-                num.z = fmaf(w, __uint_as_float(a[r].z), num.z);
-                num.w = fmaf(w, __uint_as_float(a[r].w), num.w);
-            }
-        }
-        M = Mn;
-        lds_order();
-    }
-    if constexpr (WAVES > 1) {
-        if (wave > 0) {
-            num_s[wave][lane] = num;
-            if (c4 == 0) ml_s[wave][half] = make_float2(M, den);
-        }
-        __syncthreads();
-        if (wave > 0) return;
-        float Mg = M;
-#pragma unroll
-        for (int k = 1; k < WAVES; ++k) Mg = fmaxf(Mg, ml_s[k][half].x);
-        const float w0 = merge_weight(M, Mg);
-        den *= w0;
-        num = make_float4(num.x * w0, num.y * w0, num.z * w0, num.w * w0);
-#pragma unroll
-        for (int k = 1; k < WAVES; ++k) {
-            const float2 o = ml_s[k][half];
-            const float4 a = num_s[k][lane];
-            const float w = merge_weight(o.x, Mg);
-            den = fmaf(w, o.y, den);
-            num.x = fmaf(w, a.x, num.x);
-            num.y = fmaf(w, a.y, num.y);
-            num.z = fmaf(w, a.z, num.z);
-            num.w = fmaf(w, a.w, num.w);
-        }
-    }
-    const float r = den > 0.0f ? 1.0f / den : 0.0f;
-    if (h < n_q_heads) reinterpret_cast<float4 *>(out + ((size_t)b * n_q_heads + h) * kHeadDim)[c4] = make_float4(num.x * r, num.y * r, num.z * r, num.w * r);
-}
-template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void tkv_merge_teams_kernel(MergeArgs a)
-{
-    merge_teams<WAVES>(a.acc_ws, a.ml_ws, a.seq_item_indptr, a.batch, a.n_q_heads, a.out);
-}
-
 // Sequences of hundreds of items, as a single long sequence with one kv head has them.  One workgroup of TH threads per
 // (sequence, query head, one of SL channel slices).  32 / SL lanes own an item at a time: their 16-byte loads are the item's
 // accumulators of the slice, so every partial is read once with 128-bit loads and TH * SL / 32 items are in flight per
@@ -1539,18 +1332,6 @@ __global__ __launch_bounds__(TH) void tkv_reduce_rows_kernel(MergeArgs a)
     reduce_rows(a.acc_ws, a.ml_ws, a.seq_item_indptr, a.batch * a.n_q_heads, a.n_q_heads, a.out);
 }
 
-// Whether the split kernel joins the partials of neighbouring items: where they are more than 17408 rows (9 MB) of at most
-// 3072 wavefronts, which takes eight query heads per kv head and 2176 wavefronts, and the keys are per token.  Joined and left in
-// the L2 against single and written through, us: 32 contexts of 4K to 128K 161.0 | 163.4 (on another device 161.4 | 164.5), 8 x 32768
-// 45.1 | 45.7 (46.3 | 46.2), 3 x 128000 63.8 | 63.1; joined and written through 162.9, 45.5; with per-channel keys 51.6 |
-// 51.0.  With fewer rows the barrier and the way through LDS cost more than the rows (four-layer step 75.5 | 67.9, 4 x 102400 on
-// one head 19.7 | 17.5).  More wavefronts than run at once wait for whole workgroups to end; they are single sequences
-// mostly.  (It goes by what both launches are given: split and merge agree.)
-bool in_teams(const tkv_desc *desc, int32_t n_items, int32_t n_q_heads)
-{
-    return desc->int2_key_axis == TKV_KEYS_PER_TOKEN && (int64_t)n_items * n_q_heads > 17408 && (int64_t)n_items * desc->n_kv_heads <= 3072;
-}
-
 } // namespace
 
 int tkv_launch_decode_split(const tkv_desc *desc, const void *pool, const uint8_t *bit_map, const void *q,
@@ -1562,23 +1343,21 @@ int tkv_launch_decode_split(const tkv_desc *desc, const void *pool, const uint8_
     float *acc_ws = (float *)workspace;
     float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
     const float kappa = sm_scale * 1.44269504088896340736f;
-    const bool teams = in_teams(desc, n_items, n_q_heads);
-    auto kernel = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL ? tkv_decode_kernel<true, 1>
-                                                              : (teams ? tkv_decode_kernel<false, kTeam> : tkv_decode_kernel<false, 1>);
-    const int n_groups = teams ? (n_items + kTeam - 1) / kTeam : n_items;
+    auto kernel = desc->int2_key_axis == TKV_KEYS_PER_CHANNEL ? tkv_decode_kernel<true> : tkv_decode_kernel<false>;
     int log2_r = 0;   // 1, 2, 4 or 8 query heads per kv head
     while ((desc->n_kv_heads << log2_r) < n_q_heads) ++log2_r;
     constexpr int kMaxY = 65535;
-    const dim3 grid((unsigned)desc->n_kv_heads, (unsigned)(n_groups < kMaxY ? n_groups : kMaxY), (unsigned)((n_groups + kMaxY - 1) / kMaxY));
+    const dim3 grid((unsigned)desc->n_kv_heads, (unsigned)(n_items < kMaxY ? n_items : kMaxY), (unsigned)((n_items + kMaxY - 1) / kMaxY));
     const DecodeArgs args = {(const uint8_t *)pool, bit_map, (const uint16_t *)q, page_indptr, page_ids, n_tok_int2, n_tok_int4, items, n_items, batch,
                              desc->n_kv_heads, log2_r, desc->n_pages_int2, desc->n_pages_int4, kappa, acc_ws, ml_ws, status};
-    hipLaunchKernelGGL(kernel, grid, dim3(teams ? 64 * kTeam : 64), 0, (hipStream_t)stream, args);
+    hipLaunchKernelGGL(kernel, grid, dim3(64), 0, (hipStream_t)stream, args);
     return hipGetLastError() == hipSuccess ? TKV_OK : TKV_ERR_HIP;
 }
 
 int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indptr, int32_t n_items, int32_t batch,
                              int32_t n_q_heads, float *out, const void *workspace, void *stream)
 {
+    (void)desc;
     const float *acc_ws = (const float *)workspace;
     const float *ml_ws = acc_ws + (size_t)n_items * n_q_heads * kHeadDim;
     const MergeArgs args = {acc_ws, ml_ws, seq_item_indptr, batch, n_q_heads, out};
@@ -1591,13 +1370,7 @@ int tkv_launch_decode_reduce(const tkv_desc *desc, const int32_t *seq_item_indpt
     // [2049, 11 x 32] 11.3 / 18.7), and the host cannot tell them apart.  Two channels a lane where that gives 256 workgroups:
     // 64 heads, 8 x 48 4.6 against 4.9, 4 x 96 4.2 against 4.6; 8 heads, 4 x 96 3.0 against 2.8.  (32 items of one head are
     // addressed in 32 bits.)
-    if (in_teams(desc, n_items, n_q_heads)) {
-        const bool one = (int64_t)n_items <= 64 * (int64_t)batch;
-        constexpr int kMaxY = 65535;
-        const dim3 grid((unsigned)(n_q_heads + 1) / 2, (unsigned)(batch < kMaxY ? batch : kMaxY), (unsigned)((batch + kMaxY - 1) / kMaxY));
-        hipLaunchKernelGGL(one ? tkv_merge_teams_kernel<1> : tkv_merge_teams_kernel<kTeamMergeWaves>, grid, dim3(one ? 64 : 64 * kTeamMergeWaves), 0,
-                           (hipStream_t)stream, args);
-    } else if ((int64_t)n_items <= 128 * (int64_t)batch && n_q_heads <= 1 << 17) {
+    if ((int64_t)n_items <= 128 * (int64_t)batch && n_q_heads <= 1 << 17) {
         const bool two = (int64_t)batch * n_q_heads >= 256;
         constexpr int kMaxY = 65535;
         const dim3 grid((unsigned)n_q_heads * (two ? 1 : 2), (unsigned)(batch < kMaxY ? batch : kMaxY), (unsigned)((batch + kMaxY - 1) / kMaxY));
