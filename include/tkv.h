@@ -377,6 +377,12 @@ size_t tkv_decode_workspace_bytes(const tkv_desc *desc, int32_t n_items, int32_t
  * softmax weight x V scale in fp16 and keeps it finite); with
  * TKV_KEYS_PER_CHANNEL the scales of the INT2 keys likewise up to 1023 (the
  * kernel forms q x K scale in fp16), and every n_tok_int2 is a multiple of 32.
+ * Preconditions on q: finite, and no sum of a head's q over one of the four
+ * groups of 32 channels beyond 65504 in magnitude (the kernel keeps these sums
+ * in fp16 pieces).  A query head that breaks them gives NaN; NaN and infinities
+ * in it leave the other heads alone.  The query heads of a kv head share one
+ * power of two: what is far below the largest finite |q| of theirs is rounded to
+ * 2^-30 of that (TKV_KEYS_PER_CHANNEL: 2^-24).
  * A clamped scale raises TKV_STATUS_SCALE_SATURATED: the output is then finite
  * but not the attention over the stored values.
  * n_q_heads / n_kv_heads must be 1, 2, 4 or 8.  Two launches on `stream`:

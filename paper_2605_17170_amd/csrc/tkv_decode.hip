@@ -822,7 +822,8 @@ __device__ __forceinline__ void run_pages(const ItemCtx &cx, PageBatch &batch, i
 // The rows of a partial: accumulators and (m, l) pairs of the R heads that follow head h0 in a slot.  Stores beyond them are dropped.
 // Written through the L2: with the partials left dirty there, the merge began that much later.  Before | now, us a call: 16 contexts of
 // 97 to 6011 tokens 12.45 | 11.95, 4 x 102400 on one head 18.1 | 17.5, four-layer step 74.7 | 67.8, of 23 more shapes five of 9 to 100 us
-// 1.08 to 1.11 times as fast, the others .99 to 1.03.  (Non-temporal stores .97 to 1.05 of it, .88 on some; both at once .88 to 1.06.)
+// 1.08 to 1.11 times as fast, the others .99 to 1.03; 36 shapes of about as many wavefronts as run at once and eight query heads each,
+// 20 to 193 us, .997 to 1.05.  (Non-temporal stores .97 to 1.05 of it, .88 on some; both at once .88 to 1.06.)
 struct PartialRows {
     Record acc, ml;
     __device__ __forceinline__ PartialRows(float *acc_ws, float *ml_ws, int slot, int n_q_heads, int h0, int R)
@@ -989,7 +990,8 @@ __device__ __forceinline__ void decode_item(
         }
         // The sums of q over this lane's two groups, in 32 bits: they meet zero-points of tens.  (From the staged q on the
         // matrix core, numbers far below the largest of their group or of the heads lose bits, and it is no faster.)  As
-        // three fp16 pieces to LDS, [head][hi of the four groups, mid, lo], one by each of three lanes of a quad.
+        // three fp16 pieces to LDS, [head][hi of the four groups, mid, lo], one by each of three lanes of a quad.  (A sum beyond
+        // 65504 has no such pieces: NaN.)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             float sum = ((bf16_lo(d[4 * j]) + bf16_hi(d[4 * j])) + (bf16_lo(d[4 * j + 1]) + bf16_hi(d[4 * j + 1]))) +

@@ -86,8 +86,9 @@ __device__ __forceinline__ void store_once_through(uint4 *p, uint4 v)
 }
 // A store that the L2 of the XCD passes on to memory at once (device scope), for what the next launch reads: a launch ends with the
 // write-back of the lines that are still dirty in the eight L2s, and the next one begins behind it.  Only where one store instruction
-// fills whole 128-byte lines and the launch is short (the (m, l) pairs of a partial, 64 bytes, go with its rows): parts of lines, and
-// streams that fill the memory's write path, are slower this way (packing one token for each of 32 sequences 3.83 -> 4.04 us, gathering 65536 tokens 54 -> 66).
+// fills whole 128-byte lines (the (m, l) pairs of a partial, 64 bytes, go with its rows) and they do not fill the memory's write path:
+// parts of lines, and long streams without nt, are slower this way (packing one token for each of 32 sequences 3.83 -> 4.04 us,
+// gathering 65536 tokens 54 -> 66).
 __device__ __forceinline__ void store_through(__amdgpu_buffer_rsrc_t r, uint32_t offset, float4 v)
 {
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));

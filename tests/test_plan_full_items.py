@@ -47,7 +47,8 @@ def _plan(heads, p2, p4, target, n2=None, n4=None, axis=tkv.TKV_KEYS_PER_TOKEN):
 
 def _check(items, sip, heads, p2, p4, target, axis=tkv.TKV_KEYS_PER_TOKEN):
     """The items cover the pages in order; none has more pages than the longest equal part, none costs more than the heaviest
-    (where that has four pages or more).  True if they are full."""
+    (where that has four pages or more).  True if they are full.  (Plans whose parts of one or two pages get a page more are not for
+    this function: test_plan_pairs.py.)"""
     n_equal, longest, heaviest = _equal_parts(p2.tolist(), p4.tolist(), target)
     n2, n4, per_token = p2.sum(), p4.sum(), axis == tkv.TKV_KEYS_PER_TOKEN
     roomy = per_token or 5 * sum(-(-(p2 + p4) // max(1, longest))) <= 4 * target
